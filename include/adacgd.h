@@ -123,7 +123,7 @@ enum adacgd_flags {
                                       untouched until the next adacgd_step call has completed            */
   ADACGD_FLAG_KERNEL_TIMING = 4,   /* record HIP events around every kernel (see ADACGD_F_KERNEL_MS)    */
   ADACGD_FLAG_TWO_PASS = 8,        /* always use the general two-pass kernels: neither the sampled one-pass
-                                      selection of long vectors nor the one-block kernel of short ones
+                                      selection of long vectors nor the one-launch kernel of shorter ones
                                       (same results, slower)                                            */
   ADACGD_FLAG_OVERLAP = 16         /* GRAD_EXTERNAL / DIFF_EXTERNAL: run the worker compression on a stream
                                       of the library's own, concurrently with the previous step's
@@ -266,11 +266,12 @@ enum adacgd_field {
 /* Kernel slots of ADACGD_F_KERNEL_MS.  W = worker side, M = master side.  Long vectors with
  * Top-K levels only run sample + scan (the scan also extracts the candidates); the filter slot
  * then holds the second scan that repairs a failed estimate (idle otherwise).  Other vectors run
- * scan + filter as two passes.  Vectors of at most 4096 coordinates are handled by one kernel
- * that does the whole compression step of a node, timed in the scan slot; with at most 64 workers
- * and Top-K levels only that launch also aggregates (the aggregate slot stays empty), and the
- * launch that finishes g also writes the next iterate (the xupdate slot stays empty); so does the
- * aggregation of any vector length when there is no master compressor (g is g~ then). */
+ * scan + filter as two passes.  Without Rank-K levels, vectors of at most 65536 coordinates -- and
+ * longer ones, up to 2^20, if there are few nodes -- are handled by one kernel that does the whole
+ * compression step of all nodes, timed in the scan slot; with few, short messages that launch also
+ * aggregates (the aggregate slot stays empty), and the launch that finishes g also writes the next
+ * iterate (the xupdate slot stays empty); so does the aggregation of any vector length when there
+ * is no master compressor (g is g~ then). */
 enum adacgd_kernel {
   ADACGD_K_XUPDATE = 0,
   ADACGD_K_GRAD_MARGIN = 1,

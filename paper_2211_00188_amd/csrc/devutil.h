@@ -34,6 +34,50 @@ __device__ __forceinline__ uint32_t wave_max(uint32_t v) {
   return v;
 }
 
+// Reductions and scans over a wavefront by data-parallel moves: a stage is a move and an add in the vector
+// pipe, where a shuffle is a round trip through the LDS unit (a sum of doubles: 0.05 instead of 0.3 us).
+// Stages: shifts by 1, 2, 4, 8 inside each row of 16 lanes, then the row totals are carried on, so the last lane
+// ends with the sum of all.  A lane without a source adds zero.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ uint32_t dpp_or0(uint32_t v) {
+  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, ROWS, 0xf, false);
+}
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double dpp_or0(double v) {
+  return __hiloint2double((int)dpp_or0<CTRL, ROWS>((uint32_t)__double2hiint(v)), (int)dpp_or0<CTRL, ROWS>((uint32_t)__double2loint(v)));
+}
+constexpr int kDppShr = 0x110, kDppBcast15 = 0x142, kDppBcast31 = 0x143;
+template <typename T>
+__device__ __forceinline__ T row_scan(T v) {       // inclusive prefix sums inside every row of 16 lanes
+  v += dpp_or0<kDppShr + 1, 0xf>(v);
+  v += dpp_or0<kDppShr + 2, 0xf>(v);
+  v += dpp_or0<kDppShr + 4, 0xf>(v);
+  v += dpp_or0<kDppShr + 8, 0xf>(v);
+  return v;
+}
+template <typename T>
+__device__ __forceinline__ T wave_scan(T v) {      // inclusive prefix sums over the wavefront
+  v = row_scan(v);
+  v += dpp_or0<kDppBcast15, 0xa>(v);
+  v += dpp_or0<kDppBcast31, 0xc>(v);
+  return v;
+}
+__device__ __forceinline__ uint32_t lane_value(uint32_t v, int lane) { return (uint32_t)__builtin_amdgcn_readlane((int)v, lane); }
+__device__ __forceinline__ double lane_value(double v, int lane) {
+  return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), lane), __builtin_amdgcn_readlane(__double2loint(v), lane));
+}
+template <typename T>
+__device__ __forceinline__ T wave_total(T v) { return lane_value(wave_scan(v), 63); }
+__device__ __forceinline__ uint32_t wave_top(uint32_t v) {      // maximum
+  v = max(v, dpp_or0<kDppShr + 1, 0xf>(v));
+  v = max(v, dpp_or0<kDppShr + 2, 0xf>(v));
+  v = max(v, dpp_or0<kDppShr + 4, 0xf>(v));
+  v = max(v, dpp_or0<kDppShr + 8, 0xf>(v));
+  v = max(v, dpp_or0<kDppBcast15, 0xa>(v));
+  v = max(v, dpp_or0<kDppBcast31, 0xc>(v));
+  return lane_value(v, 63);
+}
+
 // Sum over a 256-thread block in a fixed order; result valid in every thread.
 __device__ __forceinline__ double block_sum(double v, double* lds4) {
   v = wave_sum(v);
@@ -139,6 +183,32 @@ __device__ __forceinline__ void hist_add(uint32_t* hist, uint32_t bin) {
   const uint64_t same = ballot(bin == first);
   if (bin != first) atomicAdd(&hist[bin], 1u);
   else if (below(same) == 0) atomicAdd(&hist[first], popc64(same));
+}
+
+// A range of memory behind a buffer descriptor: accesses take a byte offset, need only the 4-byte alignment
+// that every row of floats has, and are checked dword by dword -- what lies at or beyond `bytes` reads as zero
+// and is not written.  Ragged ends then cost no branch, and an optional array is one of zero bytes.
+typedef uint32_t bword4 __attribute__((ext_vector_type(4)));
+typedef uint32_t bword2 __attribute__((ext_vector_type(2)));
+struct Buf {
+  __amdgpu_buffer_rsrc_t r;
+};
+__device__ __forceinline__ Buf make_buf(const void* p, uint32_t bytes) {
+  return Buf{__builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, bytes, 0x00027000)};
+}
+constexpr int kStream = 2;       // cache hint of a vector that is read or written once: do not keep
+template <int HINT = 0>
+__device__ __forceinline__ void buf_load4(const Buf& b, uint32_t off, uint32_t base, float (&o)[4]) {
+  const bword4 q = __builtin_amdgcn_raw_buffer_load_b128(b.r, off, base, HINT);
+#pragma unroll
+  for (int c = 0; c < 4; ++c) o[c] = __uint_as_float(q[c]);
+}
+template <int HINT = 0>
+__device__ __forceinline__ void buf_store4(const Buf& b, uint32_t off, uint32_t base, const float (&o)[4]) {
+  bword4 q;
+#pragma unroll
+  for (int c = 0; c < 4; ++c) q[c] = __float_as_uint(o[c]);
+  __builtin_amdgcn_raw_buffer_store_b128(q, b.r, off, base, HINT);
 }
 
 __device__ __forceinline__ uint32_t fbits(float v) { return __float_as_uint(v); }

@@ -20,8 +20,13 @@ constexpr int kShift1 = 9, kBins1 = 1024;
 constexpr int kBins2 = 512;
 
 constexpr int kMaxLevels = 16;
-constexpr int kSmallMax = 4096;         // largest d handled by the one-block-per-node kernel
-constexpr int kSmallServeMax = 64;      // ... which also aggregates when there are at most this many workers
+// One-launch compression step (node.hip): a node's vector in chunks of up to kNodeChunk coordinates, one block each,
+// at most kNodeParts of them.
+constexpr int kNodeChunk = 16384;
+constexpr int kNodeParts = 64;
+constexpr int kNodeResident = 512;      // its blocks resident at once: two per compute unit
+constexpr int kServeWorkers = 64;       // it also aggregates when there are at most this many workers of one chunk each
+constexpr int64_t kServeMax = 65536;    // ... and at most this many worker-coordinates (one block adds them up)
 constexpr int kSeg = 64;                // block-wise quantiser scales are built from maxima over segments of 64 coordinates
 constexpr int kSegPerGroup = kWaveTile / kSeg;   // 32
 
@@ -37,6 +42,7 @@ struct LevelTable {
   int rK[kMaxLevels];         // their ranks
   int p;                      // distinct Top-K sizes ("slots")
   uint32_t K[kMaxLevels];     // ascending
+  int pk;                     // how many of them are below d (the identity, K = d, needs no selection)
   int nq;                     // quantiser levels
   int qbits[kMaxLevels];
   int qblock[kMaxLevels];     // 0: one scale for the whole vector; else block length B (a power of two, 64..2048):
@@ -50,6 +56,13 @@ struct LevelTable {
   double te[kMaxLevels];
 };
 
+// Partial results a block leaves for the node's other blocks (norms, largest key, zeros; energies, counts), and words of
+// one set of what the blocks of a node meet at: the partial results and three histograms.
+__host__ __device__ inline size_t node_part_quantities(int pk, int nq) { return 4 + 1 + 3 * (size_t)pk + nq; }
+__host__ __device__ inline size_t node_meet_words(int pk, int nq, int NB) {
+  return 2 * node_part_quantities(pk, nq) * NB + kBins0 + (size_t)pk * (kBins1 + kBins2);
+}
+
 // Device arrays of one side.  nn nodes, each with a length-d vector.
 struct NodeSet {
   int nn;
@@ -60,7 +73,9 @@ struct NodeSet {
   int G2;           // blocks per node of the candidate kernels
   int GZ;           // blocks per (slot, node) of the select kernels
   int onepass;      // 1: sample + scanx sequence, 0: scan + filter sequence
-  int small;        // 1: d <= kSmallMax: one kernel, one block per node, does the whole step
+  int small;        // 1: one launch does the whole step of every node (node.hip)
+  int NB;           // ... its blocks per node
+  int chunk;        // ... coordinates per block, a multiple of kWaveTile if NB > 1
   uint32_t Kcap;    // message capacity per node = largest Top-K size (0 if none)
   LevelTable lv;
 
@@ -115,6 +130,10 @@ struct NodeSet {
   unsigned long long* repairs;     // [1] node-steps whose sampled cut was too high (second scan ran)
   int16_t* qcodes;      // [nn][d] (only with quantiser levels)
   float* qscale;        // [nn]
+  uint32_t* meet;       // [2][nn][node_meet_words] partial results and histograms of a node's blocks (NB > 1); zero at init
+  uint32_t* ticket;     // [2][kCounterStride] next (node, chunk) to be taken by a block; zero at init; null if all blocks are resident
+  float* dense;         // [nn][d] C(v) of every node that sent a message, for the aggregation inside the one-block kernel
+                        //         (null: the aggregation is a kernel of its own)
   double* accbuf;       // [d] fp64 sums of the sparse messages (only with quantiser levels)
   // Rank-K levels (allocated only when the level set has any; c = lv.rcols, nr = lv.nr)
   int GR;               // blocks per node of the Rank-K kernels
@@ -141,6 +160,7 @@ struct PassArgs {
   uint64_t seed;       // Philox key
   uint32_t step;       // Philox counter word 2
   uint32_t node_flag;  // OR-ed into counter word 1 (0 for workers, 2^31 for the master)
+  uint32_t parity;     // which of the two sets of NodeSet::meet this launch uses (alternates)
   int assign;          // 1 = the compressed start g~_i^0 = C_m(grad f_i(x^0)) (Section 2.3): h holds zeros and receives
                        // the selected values themselves, h[l] = C(v)[l], instead of fl(h[l] + C(v)[l]) (Top-K only)
   // Server work that the one-block kernel for short vectors can take over (each part optional):
@@ -153,6 +173,14 @@ struct PassArgs {
   float* xu_out;
   double xu_gamma;
 };
+
+// Right side of the trigger that guards cascade position j (0 = keep h, j = level j):
+// zeta_j ||x-y||^2 + eta_j ||x-h||^2.  Both products and the sum are rounded separately (no fused
+// multiply-add), so the bound is the same number wherever it is evaluated; with eta_j = 0 it is
+// exactly zeta_j ||x-y||^2, the trigger of Eq. (10).
+__device__ __forceinline__ double trigger_bound(const LevelTable& lv, int j, double S, double D) {
+  return __dadd_rn(__dmul_rn(lv.tz[j], D), __dmul_rn(lv.te[j], S));
+}
 
 struct LogisticData {
   const float* A;
@@ -186,7 +214,7 @@ hipError_t launch_scan(const NodeSet& ns, const PassArgs& a, hipStream_t st);
 hipError_t launch_filter(const NodeSet& ns, const PassArgs& a, hipStream_t st);
 hipError_t launch_gather(const NodeSet& ns, hipStream_t st);
 hipError_t launch_select(const NodeSet& ns, hipStream_t st);
-hipError_t launch_small(const NodeSet& ns, const PassArgs& a, hipStream_t st);
+hipError_t launch_node(const NodeSet& ns, const PassArgs& a, hipStream_t st);
 hipError_t launch_sample(const NodeSet& ns, const PassArgs& a, hipStream_t st);
 hipError_t launch_scanx(const NodeSet& ns, const PassArgs& a, bool repair, hipStream_t st);
 hipError_t launch_tally(const NodeSet& ns, hipStream_t st);

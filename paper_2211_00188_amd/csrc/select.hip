@@ -38,8 +38,8 @@
 //             epilogue: err of every level, the cascade, message layout per block
 //   compact : writes the chosen level's message in ascending coordinate and updates h
 //   qapply  : dense update and codes for nodes whose chosen level is a quantiser
-// Short vectors (d <= 4096): k_small, one block per node, does all of the above in one launch and,
-// when asked, the server aggregation (its last block) and the next iterate update.
+// Vectors of up to 65536 coordinates without Rank-K levels take none of this: node.hip does the whole step
+// of a node in one launch.
 //
 // What one block leaves for another block of the same launch (partial sums, its largest key, its
 // candidate count, histogram counts) goes through agent-scope atomic accesses on distinct
@@ -50,6 +50,7 @@
 
 #include "devutil.h"
 #include "engine.h"
+#include "quant.h"
 
 namespace adacgd {
 
@@ -59,14 +60,6 @@ namespace adacgd {
 // starting at w*2048 + k*256 + 4l.  Scalar path: component c of iteration k is
 // coordinate w*2048 + k*256 + 64c + l.
 // ---------------------------------------------------------------------------
-// Right side of the trigger that guards cascade position j (0 = keep h, j = level j):
-// zeta_j ||x-y||^2 + eta_j ||x-h||^2.  Both products and the sum are rounded separately (no fused
-// multiply-add), so the bound is the same number wherever it is evaluated; with eta_j = 0 it is
-// exactly zeta_j ||x-y||^2, the trigger of Eq. (10).
-__device__ __forceinline__ double trigger_bound(const LevelTable& lv, int j, double S, double D) {
-  return __dadd_rn(__dmul_rn(lv.tz[j], D), __dmul_rn(lv.te[j], S));
-}
-
 template <bool VEC>
 __device__ __forceinline__ int64_t comp0(int64_t base, int w, int lane, int k) {
   return VEC ? base + w * kWaveTile + k * 256 + lane * 4 : base + w * kWaveTile + k * 256 + lane;
@@ -620,51 +613,6 @@ __global__ __launch_bounds__(kBlock) void k_scanx(NodeSet ns, PassArgs a) {
     ns.redo[node] = redo ? 1u : 0u;
     if (redo && !skip) atomicAdd(ns.repairs, 1ull);
   }
-}
-
-// ---------------------------------------------------------------------------
-// Philox4x32-10 (Salmon et al., SC'11): counter (c0..c3), key (k0,k1) -> 4 words
-// ---------------------------------------------------------------------------
-__device__ __forceinline__ void philox4x32_10(uint32_t c0, uint32_t c1, uint32_t c2, uint32_t c3, uint32_t k0,
-                                              uint32_t k1, uint32_t (&out)[4]) {
-#pragma unroll
-  for (int r = 0; r < 10; ++r) {
-    const uint64_t p0 = (uint64_t)0xD2511F53u * c0;
-    const uint64_t p1 = (uint64_t)0xCD9E8D57u * c2;
-    const uint32_t n0 = (uint32_t)(p1 >> 32) ^ c1 ^ k0;
-    const uint32_t n2 = (uint32_t)(p0 >> 32) ^ c3 ^ k1;
-    c0 = n0; c1 = (uint32_t)p1; c2 = n2; c3 = (uint32_t)p0;
-    k0 += 0x9E3779B9u;
-    k1 += 0xBB67AE85u;
-  }
-  out[0] = c0; out[1] = c1; out[2] = c2; out[3] = c3;
-}
-
-// dither u in [0,1) of coordinate l: word l%4 of the block l/4, top 24 bits
-__device__ __forceinline__ float dither_of(uint32_t word) { return (float)(word >> 8) * 5.9604644775390625e-8f; }
-
-// b-bit stochastic quantiser of one coordinate from t = fl(|v| / a): the magnitude code xi (as a float) and
-// the decoded magnitude fl(xi c).  s = magnitude levels, c = fl(a / (s (1+omega))).
-__device__ __forceinline__ float quant_mag(float t, float s, float c, float u, float* xi_out) {
-  const float r = t * s;              // the second of the two rounded fp32 operations
-  const float fl = floorf(r);
-  const float pfrac = r - fl;
-  const float xi = fl + ((u < pfrac) ? 1.f : 0.f);
-  *xi_out = xi;
-  return xi * c;
-}
-
-// ... with the sign of v: returns the signed code and the decoded value.
-__device__ __forceinline__ float quant_ratio(float v, float t, float s, float c, float u, int* code) {
-  float xi;
-  const float mag = quant_mag(t, s, c, u, &xi);
-  *code = (__float_as_uint(v) >> 31) ? -(int)xi : (int)xi;
-  return copysignf(mag, v);
-}
-
-// The same with a = max |v| (> 0) given.
-__device__ __forceinline__ float quant_one(float v, float a, float s, float c, float u, int* code) {
-  return quant_ratio(v, fabsf(v) / a, s, c, u, code);
 }
 
 // Block-wise quantiser scales of one group of 2048 coordinates (one wavefront's share of a tile).
@@ -1434,302 +1382,6 @@ __global__ __launch_bounds__(kBlock) void k_qapply(NodeSet ns, PassArgs a) {
 }
 
 // ---------------------------------------------------------------------------
-// small: the whole compression step of a node in one block, for d <= kSmallMax (the scale of the
-// paper's own experiments, where a step of the general sequence is a dozen launches of a few
-// microseconds each).  The coordinates are sorted in LDS by the total order of Top-K -- key
-// descending, index ascending -- so every Top-K size is a prefix of the sorted order; errors are
-// sums over the rest; then the cascade, and the message in ascending coordinate by a scan over a
-// flag per coordinate.  Same arithmetic per element as the general kernels.
-// ---------------------------------------------------------------------------
-__device__ __forceinline__ double small_sum(double v, double* red, int nw) {
-  v = wave_sum(v);
-  __syncthreads();
-  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
-  __syncthreads();
-  double t = 0.0;
-  for (int i = 0; i < nw; ++i) t += red[i];
-  return t;
-}
-
-template <bool DIFF, bool QUANT>      // QUANT: the level set holds quantisers (otherwise their code is left out)
-__global__ __launch_bounds__(1024) void k_small(NodeSet ns, PassArgs a) {
-  __shared__ uint64_t ck[kSmallMax];       // (key << 32) | ~index, sorted descending
-  __shared__ float sv[kSmallMax];          // v by coordinate
-  __shared__ uint8_t flag[kSmallMax];      // 1 = coordinate belongs to the message
-  __shared__ double red[16];
-  __shared__ uint32_t redu[16];
-  __shared__ double s_slot_err[kMaxLevels], s_qerr[kMaxLevels];
-  __shared__ uint32_t segk[kSmallMax / kSeg];   // largest key of every 64-coordinate segment (block-wise quantiser scales)
-  __shared__ int s_slot, s_q;
-  __shared__ int s_flag;
-  const bool serve = a.agg_new != nullptr;     // what the aggregation reads goes through coherent accesses
-  const int node = blockIdx.x, tid = threadIdx.x, NT = blockDim.x, nw = NT >> 6;
-  const int lane = tid & 63, w = tid >> 6;
-  const int d = (int)ns.d;
-  const LevelTable& lv = ns.lv;
-  const int p = lv.p, nq = lv.nq;
-  const size_t row = (size_t)node * (size_t)d;
-  const float* __restrict__ x = a.x + row;
-  float* __restrict__ h = a.h + row;
-  const float* __restrict__ y = DIFF ? nullptr : a.y + row;
-  float* __restrict__ yc = a.ycopy ? a.ycopy + row : nullptr;
-  int dp = 64;
-  while (dp < d) dp <<= 1;
-
-  // ---- v, ||v||^2, ||x - y||^2, max |v|, sort keys ----
-  double S = 0.0, D = 0.0;
-  uint32_t kmax = 0;
-  const bool blockwise = QUANT && lv.nqb > 0;
-  if (blockwise) {
-    for (int i = tid; i < kSmallMax / kSeg; i += NT) segk[i] = 0u;
-    __syncthreads();
-  }
-  // scale a (as a float) of the block of B coordinates that holds coordinate i: the maximum over its segments
-  auto block_max = [&](int i, int B) {
-    const int per = B / kSeg, s0 = (i / B) * per;
-    uint32_t m = 0u;
-    for (int j = 0; j < per && (s0 + j) * kSeg < d; ++j) m = max(m, segk[s0 + j]);
-    return __uint_as_float(m);
-  };
-  for (int i = tid; i < dp; i += NT) {
-    if (i < d) {
-      const float xv = x[i];
-      const float v = DIFF ? xv : xv - h[i];
-      if (!DIFF) {
-        const double dw = (double)(xv - y[i]);
-        D = fma(dw, dw, D);
-        if (yc) yc[i] = xv;
-      }
-      const double dv = (double)v;
-      S = fma(dv, dv, S);
-      const uint32_t key = magkey(v);
-      kmax = key > kmax ? key : kmax;
-      if (blockwise) atomicMax(&segk[i >> 6], key);
-      sv[i] = v;
-      ck[i] = ((uint64_t)key << 32) | (uint64_t)(~(uint32_t)i);
-    } else {
-      ck[i] = 0;                     // sorts behind every coordinate
-    }
-  }
-  S = small_sum(S, red, nw);
-  D = small_sum(D, red, nw);
-  kmax = wave_max(kmax);
-  __syncthreads();
-  if (lane == 0) redu[w] = kmax;
-  __syncthreads();
-  for (int i = 0; i < nw; ++i) kmax = redu[i] > kmax ? redu[i] : kmax;
-  const double Dn = DIFF ? a.extD[node] : D;
-  // first condition of the cascade: nothing else is evaluated (the compressed start applies its level unconditionally)
-  const bool skip = !a.assign && S <= trigger_bound(lv, 0, S, Dn);
-
-  if (!skip) {
-    // ---- bitonic sort, descending ----
-    for (int k = 2; k <= dp; k <<= 1) {
-      for (int j = k >> 1; j > 0; j >>= 1) {
-        __syncthreads();
-        for (int t = tid; t < (dp >> 1); t += NT) {
-          const int i = ((t & ~(j - 1)) << 1) | (t & (j - 1));
-          const int l = i | j;
-          const uint64_t ai = ck[i], al = ck[l];
-          const bool desc = (i & k) == 0;
-          if (desc ? ai < al : ai > al) {
-            ck[i] = al;
-            ck[l] = ai;
-          }
-        }
-      }
-    }
-    __syncthreads();
-    // ---- realised error of every Top-K size: energy of the ranks behind it ----
-    for (int s = 0; s < p; ++s) {
-      const int K = (int)lv.K[s];
-      double e = 0.0;
-      for (int r = K + tid; r < d; r += NT) {
-        const double f = (double)__uint_as_float((uint32_t)(ck[r] >> 32));
-        e = fma(f, f, e);
-      }
-      e = small_sum(e, red, nw);
-      if (tid == 0) s_slot_err[s] = e;
-    }
-    // ---- realised error of every quantiser level ----
-    if (QUANT && nq > 0) {
-      const float qa = __uint_as_float(kmax);
-      const uint32_t k0 = (uint32_t)a.seed, k1 = (uint32_t)(a.seed >> 32);
-      const uint32_t ctr1 = (uint32_t)node | a.node_flag;
-      double qacc[kMaxLevels];
-#pragma unroll
-      for (int q = 0; q < kMaxLevels; ++q) qacc[q] = 0.0;
-      for (int i = tid; i < d; i += NT) {
-        uint32_t r4[4];
-        philox4x32_10((uint32_t)(i >> 2), ctr1, a.step, 0u, k0, k1, r4);
-        const float u = dither_of(r4[i & 3]);
-        const float v = sv[i];
-#pragma unroll
-        for (int q = 0; q < kMaxLevels; ++q) {
-          if (q < nq) {
-            const float aq = lv.qblock[q] ? block_max(i, lv.qblock[q]) : qa;
-            const float qc = aq > 0.f ? (float)((double)aq / lv.qdenom[q]) : 0.f;
-            int code;
-            const float cq = aq > 0.f ? quant_one(v, aq, lv.qs[q], qc, u, &code) : 0.f;
-            const double e = (double)v - (double)cq;
-            qacc[q] = fma(e, e, qacc[q]);
-          }
-        }
-      }
-#pragma unroll
-      for (int q = 0; q < kMaxLevels; ++q) {
-        if (q < nq) {
-          const double e = small_sum(qacc[q], red, nw);
-          if (tid == 0) s_qerr[q] = e;
-        }
-      }
-    }
-  }
-  __syncthreads();
-
-  // ---- the cascade ----
-  if (tid == 0) {
-    double err[kMaxLevels];
-    for (int j = 0; j < lv.m; ++j) {
-      if (skip) err[j] = __longlong_as_double(0x7FF8000000000000ll);
-      else err[j] = lv.kind[j] == kTopK ? s_slot_err[lv.ref[j]] : s_qerr[lv.ref[j]];
-      ns.err[node * lv.m + j] = err[j];
-    }
-    int jstar;
-    if (skip) {
-      jstar = 0;
-    } else {
-      jstar = lv.m;
-      for (int j = 1; j < lv.m; ++j)
-        if (err[j - 1] <= trigger_bound(lv, j, S, Dn)) { jstar = j; break; }
-    }
-    int slot = -1, q = -1;
-    if (jstar > 0) {
-      if (lv.kind[jstar - 1] == kTopK) slot = lv.ref[jstar - 1];
-      else q = lv.ref[jstar - 1];
-    }
-    ns.S[node] = S;
-    ns.D[node] = Dn;
-    ns.level[node] = jstar;
-    atomicAdd(&ns.level_hist[jstar], 1ull);
-    if (serve) st_coherent(&ns.sel_slot[node], slot);
-    else ns.sel_slot[node] = slot;
-    ns.sel_q[node] = q;
-    ns.msg_count[node] = slot >= 0 ? lv.K[slot] : 0u;
-    ns.qscale[node] = 0.f;
-    s_slot = slot;
-    s_q = q;
-  }
-  __syncthreads();
-  const int slot = s_slot, q = s_q;
-
-  if (slot >= 0) {
-    // ---- message of the chosen Top-K size in ascending coordinate, h <- h + C(v) ----
-    const int K = (int)lv.K[slot];
-    for (int i = tid; i < d; i += NT) flag[i] = 0;
-    __syncthreads();
-    for (int r = tid; r < K; r += NT) flag[~(uint32_t)ck[r]] = 1;
-    __syncthreads();
-    const int E = (d + NT - 1) / NT;               // consecutive coordinates per thread
-    const int lo = min(d, tid * E), hi = min(d, lo + E);
-    uint32_t cnt = 0, low = 0;
-    for (int i = lo; i < hi; ++i) {
-      cnt += flag[i];
-      if (i < kWaveTile) low += flag[i];
-    }
-    // exclusive prefix of cnt over the threads
-    uint32_t inc = cnt;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-      const uint32_t t = __shfl_up(inc, o, 64);
-      if (lane >= o) inc += t;
-    }
-    if (lane == 63) redu[w] = inc;
-    __syncthreads();
-    uint32_t pos = inc - cnt;
-    for (int i = 0; i < w; ++i) pos += redu[i];
-    __syncthreads();
-    int32_t* __restrict__ midx = ns.msg_idx + (size_t)node * ns.Kcap;
-    float* __restrict__ mval = ns.msg_val + (size_t)node * ns.Kcap;
-    for (int i = lo; i < hi; ++i) {
-      if (flag[i]) {
-        const float v = sv[i];
-        if (serve) {
-          st_coherent(&midx[pos], (int32_t)i);
-          st_coherent(&mval[pos], v);
-        } else {
-          midx[pos] = i;
-          mval[pos] = v;
-        }
-        h[i] = a.assign ? v : h[i] + v;
-        ++pos;
-      }
-    }
-    // message offsets of the groups of 2048 coordinates (the aggregation reads them)
-    const double lowsum = small_sum((double)low, red, nw);
-    if (tid == 0) {
-      uint32_t* go = ns.grp_off + (size_t)node * (ns.groups + 1);
-      go[0] = 0;
-      if (ns.groups == 2) go[1] = (uint32_t)lowsum;
-      go[ns.groups] = (uint32_t)K;
-    }
-  } else if (QUANT && q >= 0) {
-    // ---- dense update and codes of the chosen quantiser level ----
-    const int B = lv.qblock[q];
-    const float qa_node = B ? 0.f : __uint_as_float(kmax);
-    const float qs = lv.qs[q];
-    const float qc_node = qa_node > 0.f ? (float)((double)qa_node / lv.qdenom[q]) : 0.f;
-    const uint32_t k0 = (uint32_t)a.seed, k1 = (uint32_t)(a.seed >> 32);
-    const uint32_t ctr1 = (uint32_t)node | a.node_flag;
-    int16_t* __restrict__ codes = ns.qcodes + row;
-    if (tid == 0) ns.qscale[node] = qc_node;
-    for (int i = tid; i < d; i += NT) {
-      uint32_t r4[4];
-      philox4x32_10((uint32_t)(i >> 2), ctr1, a.step, 0u, k0, k1, r4);
-      float qa = qa_node, qc = qc_node;
-      if (B) {
-        qa = block_max(i, B);
-        qc = qa > 0.f ? (float)((double)qa / lv.qdenom[q]) : 0.f;
-        if (i % B == 0) ns.qbscale[(size_t)node * ns.nseg + i / B] = qc;
-      }
-      int code = 0;
-      const float cq = qa > 0.f ? quant_one(sv[i], qa, qs, qc, dither_of(r4[i & 3]), &code) : 0.f;
-      h[i] = h[i] + cq;
-      codes[i] = (int16_t)code;
-    }
-  }
-
-  // ---- iterate update that opens the next step, from this node's new estimator (the master) ----
-  if (a.xu_out && !serve) {
-    __syncthreads();                               // h is complete
-    if (node == 0)
-      for (int i = tid; i < d; i += NT) a.xu_out[i] = (float)((double)a.xu_x[i] - a.xu_gamma * (double)h[i]);
-  }
-  if (!serve) return;
-
-  // ---- server aggregation, by the block that finishes last (Top-K messages only) ----
-  if (!arrive_last(ns.done, (uint32_t)ns.nn, (uint32_t)node, &s_flag)) return;
-  double* acc = reinterpret_cast<double*>(ck);     // the sort buffer is free now
-  for (int i = tid; i < d; i += NT) acc[i] = 0.0;
-  __syncthreads();
-  for (int i = 0; i < ns.nn; ++i) {
-    const int sl = ld_coherent(&ns.sel_slot[i]);
-    if (sl < 0) continue;                          // same in every thread
-    const int K = (int)lv.K[sl];
-    const int32_t* __restrict__ mi = ns.msg_idx + (size_t)i * ns.Kcap;
-    const float* __restrict__ mv = ns.msg_val + (size_t)i * ns.Kcap;
-    for (int e = tid; e < K; e += NT) acc[ld_coherent(&mi[e])] += (double)ld_coherent(&mv[e]);   // distinct coordinates
-    __syncthreads();
-  }
-  const double nn = (double)ns.nn;
-  for (int i = tid; i < d; i += NT) {
-    const float gn = (float)((double)a.agg_old[i] + acc[i] / nn);
-    a.agg_new[i] = gn;
-    if (a.xu_out) a.xu_out[i] = (float)((double)a.xu_x[i] - a.xu_gamma * (double)gn);
-  }
-}
-
-// ---------------------------------------------------------------------------
 // launchers
 // ---------------------------------------------------------------------------
 static inline bool vec_ok(const NodeSet& ns, const PassArgs& a) {
@@ -1778,23 +1430,6 @@ hipError_t launch_filter(const NodeSet& ns, const PassArgs& a, hipStream_t st) {
   } else {
     if (v) launch_filter_q<false, true>(ns, a, st);
     else launch_filter_q<false, false>(ns, a, st);
-  }
-  return hipGetLastError();
-}
-
-hipError_t launch_small(const NodeSet& ns, const PassArgs& a, hipStream_t st) {
-  (void)hipGetLastError();
-  int dp = 64;
-  while (dp < ns.d) dp <<= 1;
-  int nt = dp / 2;                       // one compare-exchange per thread and sort stage
-  nt = nt < 64 ? 64 : (nt > 1024 ? 1024 : nt);
-  const dim3 grid(ns.nn), block(nt);
-  if (ns.lv.nq > 0) {
-    if (a.diff) hipLaunchKernelGGL((k_small<true, true>), grid, block, 0, st, ns, a);
-    else hipLaunchKernelGGL((k_small<false, true>), grid, block, 0, st, ns, a);
-  } else {
-    if (a.diff) hipLaunchKernelGGL((k_small<true, false>), grid, block, 0, st, ns, a);
-    else hipLaunchKernelGGL((k_small<false, false>), grid, block, 0, st, ns, a);
   }
   return hipGetLastError();
 }
