@@ -131,7 +131,7 @@ struct NodeSet {
   int16_t* qcodes;      // [nn][d] (only with quantiser levels)
   float* qscale;        // [nn]
   uint32_t* meet;       // [2][nn][node_meet_words] partial results and histograms of a node's blocks (NB > 1); zero at init
-  uint32_t* ticket;     // [2][kCounterStride] next (node, chunk) to be taken by a block; zero at init; null if all blocks are resident
+  uint32_t* ticket;     // [2][kCounterStride] next (node, chunk) to be taken by a block; zero at init; null up to kNodeParts blocks
   float* dense;         // [nn][d] C(v) of every node that sent a message, for the aggregation inside the one-block kernel
                         //         (null: the aggregation is a kernel of its own)
   double* accbuf;       // [d] fp64 sums of the sparse messages (only with quantiser levels)

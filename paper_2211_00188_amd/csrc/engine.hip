@@ -163,7 +163,7 @@ void carve_nodeset(Carver& c, NodeSet& ns) {
   ns.agg_done = ns.AS > 1 ? c.take<uint32_t>((size_t)ns.groups * (kArriveFan + 1) * kCounterStride) : nullptr;
   const bool chunks = ns.small && ns.NB > 1;
   ns.meet = chunks ? c.take<uint32_t>(2 * nn * node_meet_words(ns.lv.pk, (int)nq, ns.NB)) : nullptr;
-  ns.ticket = chunks && nn * ns.NB > kNodeResident / 2 ? c.take<uint32_t>(2 * kCounterStride) : nullptr;
+  ns.ticket = chunks && nn * ns.NB > kNodeParts ? c.take<uint32_t>(2 * kCounterStride) : nullptr;
   ns.level_hist = c.take<unsigned long long>(m + 2);
   ns.repairs = ns.level_hist ? ns.level_hist + m + 1 : nullptr;   // (null when only measuring)
   // everything up to here must start at zero

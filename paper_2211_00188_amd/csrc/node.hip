@@ -13,10 +13,11 @@
 // third digit) is complete when its counts add up to the number of keys that go into it, which every block knows,
 // and a partial result (never negative) is stored negated, so that it differs from the zero that was there before.
 // A meeting is then one atomic or store on its way to memory and one load coming back.
-// Waiting.  A block only waits for blocks of its own node.  When the launch has more blocks than are resident at
-// once, blocks take their (node, chunk) by an atomic ticket, so the waiting blocks of the lowest unfinished node
-// need at most NB <= kNodeParts resident blocks in all to finish, whatever the order of dispatch; a compute unit
-// holds two blocks, the device 512, so even several such launches running side by side leave one of them enough.
+// Waiting.  A block only waits for blocks of its own node.  Blocks take their (node, chunk) by an atomic ticket, so the
+// waiting blocks of the lowest unfinished node need at most NB <= kNodeParts resident blocks in all to finish,
+// whatever the order of dispatch; a launch of no more than kNodeParts blocks needs that many anyway and goes without.
+// A compute unit holds two blocks, the device 512, so eight such launches running side by side (of other contexts on
+// other streams) leave one of them enough, however they are mixed on the device.
 // Other kernels never wait, so they end and free their units.
 // What is polled exists twice: a launch uses one set and clears the other, which the previous launch of the node
 // set has left behind (launches of a node set are ordered on a stream).
@@ -146,7 +147,7 @@ __global__ __launch_bounds__(NT, NT >= 512 ? 4 : 1) void k_node(NodeSet ns, Pass
   const int nq = lv.nq, pk = lv.pk;
   const uint32_t d = (uint32_t)ns.d;
   uint32_t blk = blockIdx.x;
-  if (MULTI && ns.ticket) {                // (more blocks than are resident at once)
+  if (MULTI && ns.ticket) {
     if (tid == 0) s_blk = __hip_atomic_fetch_add(&ns.ticket[a.parity * kCounterStride], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     __syncthreads();
     blk = __builtin_amdgcn_readfirstlane(s_blk);
