@@ -275,7 +275,7 @@ enum adacgd_field {
 enum adacgd_kernel {
   ADACGD_K_XUPDATE = 0,
   ADACGD_K_GRAD_MARGIN = 1,
-  ADACGD_K_GRAD_COLS = 2,
+  ADACGD_K_GRAD_COLS = 2,  /* ... or the whole gradient, where one launch does it                */
   ADACGD_K_AGGREGATE = 3,
   ADACGD_K_W_SAMPLE = 4,   /* histogram of a sample of the vector: candidate cut estimate     */
   ADACGD_K_W_SCAN = 5,     /* differences, norms, first-digit histogram (+ candidates)        */

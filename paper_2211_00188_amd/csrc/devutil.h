@@ -214,4 +214,10 @@ __device__ __forceinline__ void buf_store4(const Buf& b, uint32_t off, uint32_t 
 __device__ __forceinline__ uint32_t fbits(float v) { return __float_as_uint(v); }
 __device__ __forceinline__ uint32_t magkey(float v) { return __float_as_uint(v) & 0x7FFFFFFFu; }
 
+// d/dx_j of the regulariser lambda sum_j x_j^2 / (1 + x_j^2)
+__device__ __forceinline__ double reg_grad(double lambda, double xj) {
+  const double q = 1.0 + xj * xj;
+  return 2.0 * lambda * xj / (q * q);
+}
+
 }  // namespace adacgd

@@ -25,6 +25,10 @@ constexpr int kMaxLevels = 16;
 constexpr int kNodeChunk = 16384;
 constexpr int kNodeParts = 64;
 constexpr int kNodeResident = 512;      // its blocks resident at once: two per compute unit
+// One-launch gradient (k_grad): up to kGradCols columns a block, up to kNodeParts such parts of a row.
+constexpr int kGradCols = 2048;
+constexpr int kGradRows = 16;           // rows a group of wavefronts holds at a time
+__host__ __device__ constexpr int grad_col_waves(int64_t cols) { return cols <= 256 ? 1 : cols <= 512 ? 2 : cols <= 1024 ? 4 : 8; }
 constexpr int kServeWorkers = 64;       // it also aggregates when there are at most this many workers of one chunk each
 constexpr int64_t kServeMax = 65536;    // ... and at most this many worker-coordinates (one block adds them up)
 constexpr int kSeg = 64;                // block-wise quantiser scales are built from maxima over segments of 64 coordinates
@@ -194,6 +198,14 @@ struct LogisticData {
   double* part;            // [n][row_chunks][d] when row_chunks > 1
   uint32_t* col_done;      // [n][column blocks] arrival counters when row_chunks > 1; zero between launches
   int row_chunks;
+  // One-launch gradient of dense features (k_grad): a shard's rows in row_chunks chunks of chunk_rows, its columns in
+  // col_parts parts of part_cols, one block each; col_parts = 0: the two-kernel form.
+  int col_parts;
+  int part_cols;
+  int chunk_rows;          // a multiple of the rows a block holds at a time
+  uint32_t parity;         // which of the two sets of `meet` and `ticket` this launch uses (alternates)
+  double* meet;            // [2][n * row_chunks * chunk_rows][col_parts] partial products a_l^T x (col_parts > 1); zero at init
+  uint32_t* ticket;        // [2][kCounterStride] see NodeSet::ticket; null up to kNodeParts blocks
   // Sparse features (GRAD_LOGISTIC_CSR): device copies made at init.  The transposed copy holds
   // every worker's entries sorted by column, then by row, so that one thread sums a column of a
   // shard in a fixed order.
@@ -237,6 +249,7 @@ hipError_t launch_aggregate(const NodeSet& ws, const float* gt_old, float* gt_ne
                             hipStream_t st);
 hipError_t launch_fill_u32(uint32_t* p, uint32_t v, size_t count, hipStream_t st);
 hipError_t launch_copy_f32(float* dst, const float* src, size_t count, hipStream_t st);
+hipError_t launch_grad(const LogisticData& ld, const float* x, float* grads, int n, int64_t d, hipStream_t st);
 hipError_t launch_grad_margins(const LogisticData& ld, const float* x, int64_t d, hipStream_t st);
 hipError_t launch_grad_cols(const LogisticData& ld, const float* x, float* grads, int n, int64_t d, hipStream_t st);
 

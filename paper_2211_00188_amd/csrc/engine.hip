@@ -331,7 +331,7 @@ struct adacgd_ctx {
   LogisticData ld;
   int64_t step;
   uint64_t w_zero_bytes, m_zero_bytes;
-  uint32_t w_parity = 0, m_parity = 0;   // see PassArgs::parity
+  uint32_t w_parity = 0, m_parity = 0, g_parity = 0;   // see PassArgs::parity, LogisticData::parity
   char err[256];
   // kernel timing
   bool timing;
@@ -449,7 +449,10 @@ size_t carve_all(char* base, const adacgd_config* cfg, NodeSet& W, NodeSet& M, L
     const size_t rows = cfg->shard_offsets[n];
     L.offsets = c.take<int64_t>(n + 1);
     L.row_node = c.take<int32_t>(rows);
-    L.margins = c.take<double>(rows);
+    L.margins = ld.col_parts ? nullptr : c.take<double>(rows);
+    const size_t blocks = n * ld.row_chunks * ld.col_parts;
+    ld.meet = ld.col_parts > 1 ? c.take<double>(2 * blocks * ld.chunk_rows) : nullptr;
+    ld.ticket = ld.col_parts > 1 && blocks > kNodeParts ? c.take<uint32_t>(2 * kCounterStride) : nullptr;
     L.part = ld.row_chunks > 1 ? c.take<double>(n * ld.row_chunks * d) : nullptr;
     L.col_done = ld.row_chunks > 1 ? c.take<uint32_t>(n * ((d + 63) / 64)) : nullptr;
   } else {
@@ -481,12 +484,30 @@ void shape_logistic(const adacgd_config* cfg, LogisticData& ld) {
     return;
   }
   int64_t mx = 0;
+  ld.lambda = (double)cfg->lambda;
   for (int64_t i = 0; i < cfg->n; ++i) mx = std::max<int64_t>(mx, cfg->shard_offsets[i + 1] - cfg->shard_offsets[i]);
   ld.max_rows = mx;
+  if (cfg->d <= (int64_t)kGradCols * kNodeParts) {
+    // Features read once (k_grad).  Row chunks as far as that keeps the launch within one round of blocks.
+    const int64_t n = cfg->n, d = cfg->d;
+    int64_t parts = (d + kGradCols - 1) / kGradCols;
+    ld.part_cols = (int)(parts == 1 ? d : ((d + parts - 1) / parts + 15) / 16 * 16);
+    parts = (d + ld.part_cols - 1) / ld.part_cols;
+    const int64_t held = kGradRows * (8 / grad_col_waves(ld.part_cols));      // rows a block holds at a time
+    const int64_t iters = (mx + held - 1) / held;
+    int64_t chunks = std::min(iters, std::max<int64_t>(1, kNodeResident / (n * parts)));
+    const int64_t per = (iters + chunks - 1) / chunks;
+    chunks = (iters + per - 1) / per;
+    if (n * chunks * parts < (int64_t(1) << 31) && chunks * per * held < (int64_t(1) << 31) && ld.rows < (int64_t(1) << 31)) {
+      ld.col_parts = (int)parts;
+      ld.row_chunks = (int)chunks;
+      ld.chunk_rows = (int)(per * held);
+      return;
+    }
+  }
   int64_t chunks = (mx + 255) / 256;    // about 256 rows per block (64 per wavefront) ...
   if (chunks > 64) chunks = 64;         // ... but a bounded number of partial sums
   ld.row_chunks = (int)chunks;
-  ld.lambda = (double)cfg->lambda;
 }
 
 #define HIPCHK(ctx, call)                                                            \
@@ -533,6 +554,34 @@ int drain_spans(adacgd_ctx* c) {
   return ADACGD_OK;
 }
 
+// A stream capture records launches that may be replayed in any number, so what the blocks of a launch meet at cannot
+// rely on the alternation of two sets: the captured launch is enclosed by fills of both.  (Nothing can be captured on the
+// null stream, and to ask about it would disturb a capture elsewhere.)
+bool capturing(hipStream_t st) {
+  if (!st) return false;
+  hipStreamCaptureStatus s = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(st, &s) != hipSuccess) { (void)hipGetLastError(); return false; }
+  return s == hipStreamCaptureStatusActive;
+}
+
+template <typename F>
+hipError_t launch_meeting(hipStream_t st, uint32_t& parity, void* meet, size_t meet_words, uint32_t* ticket, F&& launch) {
+  const uint32_t p = parity;
+  const bool clear = meet && capturing(st);
+  auto fill = [&]() -> hipError_t {
+    hipError_t e = launch_fill_u32((uint32_t*)meet, 0u, meet_words, st);
+    if (e == hipSuccess && ticket) e = launch_fill_u32(ticket, 0u, 2 * kCounterStride, st);
+    return e;
+  };
+  if (!clear) {
+    parity ^= 1u;
+    return launch(p);
+  }
+  hipError_t e = fill();
+  if (e == hipSuccess) e = launch(p);
+  return e == hipSuccess ? fill() : e;
+}
+
 // One application of the AdaCGD compressor to every node of a set, on the stream c->cs.
 // `before_tally`, if set, is an event the stream waits for before the kernels that overwrite the
 // message tables (tally, compact, qapply): in overlap mode the previous step's aggregation, which
@@ -540,11 +589,14 @@ int drain_spans(adacgd_ctx* c) {
 int compress(adacgd_ctx* c, NodeSet& ns, PassArgs a, int slot0, hipEvent_t before_tally) {
   int rc;
   if (ns.small) {      // the whole step in one launch (timed in the scan's slot)
-    uint32_t& parity = slot0 == ADACGD_K_W_SAMPLE ? c->w_parity : c->m_parity;
-    a.parity = parity;
-    parity ^= 1u;
     if (before_tally) HIPCHK(c, hipStreamWaitEvent(c->cs, before_tally, 0));
-    return timed(c, slot0 + 1, [&] { return launch_node(ns, a, c->cs); });
+    const size_t words = 2 * (size_t)ns.nn * node_meet_words(ns.lv.pk, ns.lv.nq, ns.NB);
+    return timed(c, slot0 + 1, [&] {
+      return launch_meeting(c->cs, slot0 == ADACGD_K_W_SAMPLE ? c->w_parity : c->m_parity, ns.meet, words, ns.ticket, [&](uint32_t p) {
+        a.parity = p;
+        return launch_node(ns, a, c->cs);
+      });
+    });
   }
   if (ns.onepass) {
     if ((rc = timed(c, slot0 + 0, [&] { return launch_sample(ns, a, c->cs); }))) return rc;
@@ -573,8 +625,18 @@ int compress(adacgd_ctx* c, NodeSet& ns, PassArgs a, int slot0, hipEvent_t befor
   return ADACGD_OK;
 }
 
+hipError_t launch_one_gradient(adacgd_ctx* c, float* out, hipStream_t st) {
+  LogisticData& ld = c->ld;
+  const size_t words = 4 * (size_t)c->n * ld.row_chunks * ld.chunk_rows * ld.col_parts;
+  return launch_meeting(st, c->g_parity, ld.meet, words, ld.ticket, [&](uint32_t p) {
+    ld.parity = p;
+    return launch_grad(ld, c->x, out, (int)c->n, c->d, st);
+  });
+}
+
 int gradients(adacgd_ctx* c, float* out) {
   int rc;
+  if (c->ld.col_parts > 0) return timed(c, ADACGD_K_GRAD_COLS, [&] { return launch_one_gradient(c, out, c->cs); });
   if ((rc = timed(c, ADACGD_K_GRAD_MARGIN, [&] { return launch_grad_margins(c->ld, c->x, c->d, c->cs); }))) return rc;
   return timed(c, ADACGD_K_GRAD_COLS, [&] { return launch_grad_cols(c->ld, c->x, out, (int)c->n, c->d, c->cs); });
 }
@@ -940,8 +1002,14 @@ static int init_impl(const adacgd_config* cfg, adacgd_ctx** out, int static_dev)
                            c->st));
     INITCHK(hipMemcpyAsync(L.row_node, rn.data(), rn.size() * sizeof(int32_t), hipMemcpyHostToDevice, c->st));
     INITCHK(hipStreamSynchronize(c->st));   // rn goes out of scope
-    INITCHK(launch_grad_margins(c->ld, c->x, c->d, c->st));
-    INITCHK(launch_grad_cols(c->ld, c->x, c->yb[0], (int)c->n, c->d, c->st));
+    if (c->ld.col_parts > 0) {
+      if (c->ld.meet) INITCHK(launch_fill_u32((uint32_t*)c->ld.meet, 0u, 4 * (size_t)c->n * c->ld.row_chunks * c->ld.chunk_rows * c->ld.col_parts, c->st));
+      if (c->ld.ticket) INITCHK(launch_fill_u32(c->ld.ticket, 0u, 2 * kCounterStride, c->st));
+      INITCHK(launch_one_gradient(c, c->yb[0], c->st));
+    } else {
+      INITCHK(launch_grad_margins(c->ld, c->x, c->d, c->st));
+      INITCHK(launch_grad_cols(c->ld, c->x, c->yb[0], (int)c->n, c->d, c->st));
+    }
   } else if (cfg->grad_mode == ADACGD_GRAD_EXTERNAL) {
     INITCHK(launch_copy_f32(c->yb[0], cfg->grad0, nd, c->st));
   }

@@ -1,0 +1,223 @@
+// Gradients of the logistic objective from dense features, in one launch (server.hip has the two-kernel form for rows too
+// long for it, and the sparse one).
+#include "devutil.h"
+#include "engine.h"
+
+namespace adacgd {
+
+// ---------------------------------------------------------------------------
+// The same gradient with the features read once (dense features, d <= kGradCols * kNodeParts).
+// A block keeps kGradRows rows at a time of its columns in registers: forms their products with x, turns the
+// complete products into the weights s_l, and adds s_l a_l to its column sums before it lets go of them.
+// CW wavefronts of 256 columns share a row, 8 / CW groups of them hold different rows.  Rows longer than a block's
+// columns are spread over col_parts blocks that leave each other their partial products; those are polled
+// themselves: a slot holds zero until its value (a zero is stored as -0) is there, and a launch clears the set that
+// the previous one used.  Waiting: blocks take their place by ticket and wait only for the col_parts <= kNodeParts
+// blocks of their own row chunk, as those of the one-launch compression step do (node.hip).
+// Bound by the read of the features where that is long; two blocks a compute unit (16 rows x 4 columns a lane are half
+// the registers), so that one reads while the other meets.  Measured against the two kernels that read the features
+// twice: 1000 workers x 32 rows x 65536 columns 2.00 ms a gradient (2.90), 20 x 2500 x 300 19 us (29), 10 x 203 x 5003
+// 28 us (37), 4 x 64 x 100 4.6 us (7.9).
+// ---------------------------------------------------------------------------
+
+// Lane by lane: a + (a of the partner lane) where the lane's bit O is clear, b + (b of the partner lane) where it is
+// set; partners are O = 32 or 16 lanes apart.  One swap a word (of the upper half -- or odd rows -- of a with the lower
+// half -- or even rows -- of b) and one addition.
+template <int O>
+__device__ __forceinline__ double halves_sum(double a, double b) {
+  const uint32_t al = (uint32_t)__double2loint(a), ah = (uint32_t)__double2hiint(a), bl = (uint32_t)__double2loint(b), bh = (uint32_t)__double2hiint(b);
+  if constexpr (O == 32) {
+    const auto lo = __builtin_amdgcn_permlane32_swap(al, bl, false, false), hi = __builtin_amdgcn_permlane32_swap(ah, bh, false, false);
+    return __hiloint2double((int)hi[0], (int)lo[0]) + __hiloint2double((int)hi[1], (int)lo[1]);
+  } else {
+    const auto lo = __builtin_amdgcn_permlane16_swap(al, bl, false, false), hi = __builtin_amdgcn_permlane16_swap(ah, bh, false, false);
+    return __hiloint2double((int)hi[0], (int)lo[0]) + __hiloint2double((int)hi[1], (int)lo[1]);
+  }
+}
+
+template <int CW>
+__global__ __launch_bounds__(512, 4) void k_grad(LogisticData ld, const float* __restrict__ x, float* __restrict__ grads, int64_t d) {
+  constexpr int RG = 8 / CW, R = kGradRows;
+  constexpr bool MULTI = CW == 8;
+  __shared__ double red[8][R], s_m[RG][R];
+  __shared__ double s_acc[RG > 1 ? RG : 1][RG > 1 ? CW * 256 : 1];
+  __shared__ uint32_t s_blk;
+  __shared__ int s_flag;
+  const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), cw = w % CW, rg = w / CW;
+  const uint32_t lane = tid & 63;
+  const uint32_t P = MULTI ? (uint32_t)ld.col_parts : 1u;
+  uint32_t blk = blockIdx.x;
+  if (MULTI && ld.ticket) {
+    if (tid == 0) s_blk = __hip_atomic_fetch_add(&ld.ticket[ld.parity * kCounterStride], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __syncthreads();
+    blk = s_blk;
+    if (blk == 0 && tid == 0) ld.ticket[(ld.parity ^ 1) * kCounterStride] = 0;
+  }
+  // (kept in scalar registers, also the results of divisions and loads, and without 64-bit comparisons: buffer
+  // descriptors made from vector registers would be taken apart lane by lane)
+  auto scalar = [](uint32_t v) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)v); };
+  blk = scalar(blk);
+  const uint32_t group = scalar(blk / P), part = blk - group * P;
+  const int node = (int)scalar(group / (uint32_t)ld.row_chunks), rc = (int)group - node * ld.row_chunks;
+  const uint32_t c0 = part * (uint32_t)ld.part_cols;
+  const uint32_t len = min((uint32_t)ld.part_cols, (uint32_t)d - c0);
+  // (a row number fits 31 bits: the host's choice of this kernel)
+  const uint32_t r_first = scalar((uint32_t)ld.offsets[node]);
+  const int count = (int)(scalar((uint32_t)ld.offsets[node + 1]) - r_first);
+  const int skip = rc * ld.chunk_rows, rows = max(0, min(count - skip, ld.chunk_rows));
+  const uint32_t r_begin = r_first + (uint32_t)skip;
+  const double N = (double)count;
+  const uint32_t off = (uint32_t)(cw * 64 + (int)lane) * 16u;       // byte offset of this lane's four columns
+  const size_t set = (size_t)(gridDim.x / P) * ld.chunk_rows * P;
+  double* __restrict__ slots = MULTI && P > 1 ? ld.meet + ld.parity * set + (size_t)group * ld.chunk_rows * P : nullptr;
+  if (MULTI && P > 1) {       // the set the previous launch used, cleared for the next one
+    double* __restrict__ old = ld.meet + (ld.parity ^ 1) * set + (size_t)group * ld.chunk_rows * P;
+    for (int i = tid; i < rows; i += 512) old[(size_t)i * P + part] = 0.0;
+  }
+  float xq[4];
+  buf_load4(make_buf(x + c0, 4 * len), off, 0, xq);
+  auto label = [&](int row) { return row < rows ? ld.labels[r_begin + (uint32_t)row] : 0.f; };      // (asked for before it is needed)
+  auto weight = [&](double yl, double z) { return -yl / (1.0 + exp(yl * z)) / N; };
+  double acc[4] = {0.0, 0.0, 0.0, 0.0};
+  for (int base = 0; base < rows; base += R * RG) {
+    // rows base + r RG + rg of the chunk (rows beyond its end read as zero and get weight zero)
+    float a[R][4];
+    const float* __restrict__ ap = ld.A + (size_t)(r_begin + (uint32_t)(base + rg)) * (size_t)d + c0;
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      const bool live = base + r * RG + rg < rows;
+      buf_load4(make_buf(live ? ap + (size_t)(r * RG) * (size_t)d : ld.A, live ? 4 * len : 0u), off, 0, a[r]);
+    }
+    // products with x, eight rows at a time: of their sums over the wavefront every exchange halves the rows that a
+    // lane carries; lane l ends with row l / 8
+#pragma unroll
+    for (int r0 = 0; r0 < R; r0 += 8) {
+      double p[8];
+#pragma unroll
+      for (int c = 0; c < 4; ++c) asm volatile("" : "+v"(xq[c]));     // (not widened once and for all)
+#pragma unroll
+      for (int r = 0; r < 8; ++r) {
+        if (r % 4 == 0) __builtin_amdgcn_sched_barrier(0);       // (values widened a few rows at a time: more would spill)
+        p[r] = (double)a[r0 + r][0] * (double)xq[0];
+#pragma unroll
+        for (int c = 1; c < 4; ++c) p[r] = fma((double)a[r0 + r][c], (double)xq[c], p[r]);
+      }
+#pragma unroll
+      for (int i = 0; i < 4; ++i) p[i] = halves_sum<32>(p[i], p[i + 4]);
+#pragma unroll
+      for (int i = 0; i < 2; ++i) p[i] = halves_sum<16>(p[i], p[i + 2]);
+      {
+        const bool up = (lane & 8u) != 0;
+        double a0 = p[0], a1 = p[1];
+        asm volatile("" : "+v"(a0), "+v"(a1));      // (else: a select of addresses, and from that one of every element)
+        p[0] = (up ? a1 : a0) + dpp_or0<0x128, 0xf>(up ? a0 : a1);      // row_ror:8
+      }
+      p[0] += dpp_or0<0x141, 0xf>(p[0]);       // row_half_mirror
+      p[0] += dpp_or0<0x4e, 0xf>(p[0]);        // quad_perm 2 3 0 1
+      p[0] += dpp_or0<0xb1, 0xf>(p[0]);        // quad_perm 1 0 3 2
+      if ((lane & 7u) == 0) red[w][r0 + (lane >> 3)] = p[0];
+    }
+    // (the values widened to fp64 are formed anew below: carrying them along would not fit the registers)
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+#pragma unroll
+      for (int c = 0; c < 4; ++c) asm volatile("" : "+v"(a[r][c]));
+    __syncthreads();
+    if (MULTI && P > 1) {
+      if (tid < R && base + tid < rows) {
+        double z = 0.0;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) z += red[j][tid];
+        st_coherent(&slots[(size_t)(base + tid) * P + part], z == 0.0 ? -0.0 : z);
+      }
+      const int r = tid >> 5, j = tid & 31;
+      const bool live = base + r < rows;
+      const float yl = label(base + r);
+      double z = 0.0;
+      if (live) {
+        for (uint32_t q = (uint32_t)j; q < P; q += 32) {
+          double t;
+          do t = ld_coherent(&slots[(size_t)(base + r) * P + q]); while (__double_as_longlong(t) == 0);
+          z += t;
+        }
+      }
+      z += dpp_or0<0x128, 0xf>(z);             // row_ror: the sum over 16 lanes, in all of them
+      z += dpp_or0<0x124, 0xf>(z);
+      z += dpp_or0<0x122, 0xf>(z);
+      z += dpp_or0<0x121, 0xf>(z);
+      z += __shfl_xor(z, 16, 64);
+      if (j == 0) s_m[0][r] = live ? weight((double)yl, z) : 0.0;
+    } else if (tid < R * RG) {
+      const int g = tid / R, r = tid % R, row = base + r * RG + g;
+      double z = 0.0;
+#pragma unroll
+      for (int j = 0; j < CW; ++j) z += red[g * CW + j][r];
+      s_m[g][r] = row < rows ? weight((double)label(row), z) : 0.0;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      if (r % 4 == 0) __builtin_amdgcn_sched_barrier(0);
+      const double s = s_m[rg][r];
+#pragma unroll
+      for (int c = 0; c < 4; ++c) acc[c] = fma(s, (double)a[r][c], acc[c]);
+    }
+  }
+  if (RG > 1) {
+#pragma unroll
+    for (int c = 0; c < 4; ++c) s_acc[rg][cw * 256 + (int)lane * 4 + c] = acc[c];
+    __syncthreads();
+    if (rg == 0) {
+#pragma unroll
+      for (int g = 1; g < RG; ++g)
+#pragma unroll
+        for (int c = 0; c < 4; ++c) acc[c] += s_acc[g][cw * 256 + (int)lane * 4 + c];
+    }
+  }
+  const uint32_t l0 = off / 4;
+  if (ld.row_chunks > 1) {
+    // several blocks share the shard's rows: each leaves its sums, the last to arrive adds them in chunk order
+    const size_t cp = (size_t)node * ld.row_chunks * (size_t)d + (size_t)c0 + l0;
+    if (rg == 0) {
+#pragma unroll
+      for (int c = 0; c < 4; ++c)
+        if (l0 + c < len) st_coherent(&ld.part[cp + (size_t)rc * (size_t)d + c], acc[c]);
+    }
+    if (!arrive_last_few(&ld.col_done[(size_t)node * P + part], (uint32_t)ld.row_chunks, &s_flag)) return;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) acc[c] = 0.0;
+    if (rg == 0) {
+      for (int r0 = 0; r0 < ld.row_chunks; r0 += 8) {        // eight chunks' loads in flight, added in chunk order
+        double v[8][4];
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+#pragma unroll
+          for (int c = 0; c < 4; ++c)
+            v[u][c] = r0 + u < ld.row_chunks && l0 + c < len ? ld_coherent(&ld.part[cp + (size_t)(r0 + u) * (size_t)d + c]) : 0.0;
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+#pragma unroll
+          for (int c = 0; c < 4; ++c) acc[c] += v[u][c];
+      }
+    }
+  }
+  if (rg != 0) return;
+  float g[4];
+#pragma unroll
+  for (int c = 0; c < 4; ++c) g[c] = (float)(acc[c] + reg_grad(ld.lambda, (double)xq[c]));
+  buf_store4(make_buf(grads + (size_t)node * (size_t)d + c0, 4 * len), off, 0, g);
+}
+
+hipError_t launch_grad(const LogisticData& ld, const float* x, float* grads, int n, int64_t d, hipStream_t st) {
+  (void)hipGetLastError();   // drop a stale error left by earlier runtime calls of this thread
+  const dim3 grid((unsigned)((size_t)n * ld.row_chunks * ld.col_parts));
+  switch (grad_col_waves(ld.part_cols)) {
+    case 1: hipLaunchKernelGGL((k_grad<1>), grid, dim3(512), 0, st, ld, x, grads, d); break;
+    case 2: hipLaunchKernelGGL((k_grad<2>), grid, dim3(512), 0, st, ld, x, grads, d); break;
+    case 4: hipLaunchKernelGGL((k_grad<4>), grid, dim3(512), 0, st, ld, x, grads, d); break;
+    default: hipLaunchKernelGGL((k_grad<8>), grid, dim3(512), 0, st, ld, x, grads, d); break;
+  }
+  return hipGetLastError();
+}
+
+}  // namespace adacgd

@@ -261,7 +261,7 @@ __global__ __launch_bounds__(64 * kDenseWaves) void k_aggregate_dense(NodeSet ws
 }
 
 // ---------------------------------------------------------------------------
-// logistic gradient, Section 6:
+// logistic gradient, Section 6, of features too long for the one-launch form (grad.hip):
 //   grad f_i(x) = -(1/N_i) sum_l y_l a_l / (1 + exp(y_l a_l^T x)) + 2 lambda x_j / (1 + x_j^2)^2
 // margins: LPR lanes per sample (64, or 16 for rows shorter than 1024 so that a wavefront works on four
 //          rows at once) compute a_l^T x in fp64 and s_l = -y_l/(1+exp(y_l z_l))/N_i.
@@ -301,11 +301,6 @@ __global__ __launch_bounds__(kBlock) void k_grad_margins(LogisticData ld, const 
     const double yl = (double)ld.labels[l];
     ld.margins[l] = -yl / (1.0 + exp(yl * z)) / N;
   }
-}
-
-__device__ __forceinline__ double reg_grad(double lambda, double xj) {
-  const double q = 1.0 + xj * xj;
-  return 2.0 * lambda * xj / (q * q);
 }
 
 template <bool VEC>

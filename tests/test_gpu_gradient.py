@@ -1,0 +1,41 @@
+"""The one-launch gradient of dense features at the edges of its layout: columns around every switch of the number of
+wavefronts that share a row and of blocks that share a row, rows around what a block holds at a time, ragged shards
+and the first length that takes the two-kernel form; the gradients of two points against fp64."""
+import numpy as np
+import pytest
+
+from test_gpu_parity import _cuda, _eng
+
+pytestmark = pytest.mark.gpu
+
+SHAPES = [(3, 1, 5), (2, 20, 300), (4, 256, 128), (3, 257, 129), (2, 511, 65), (2, 513, 33), (3, 1024, 31), (2, 1025, 17), (5, 2048, 16),
+          (3, 2049, 40), (2, 5003, 203), (1, 20000, 9), (40, 4099, 33), (70, 65536, 5), (2, 131072, 3), (2, 131073, 3), (600, 40, 7)]
+
+
+@pytest.mark.parametrize("n,d,rows", SHAPES)
+def test_gradient_at_the_edges_of_its_layout(n, d, rows):
+    E = _eng()
+    rng = np.random.default_rng(d * 7 + rows)
+    cnt = rows - rng.integers(0, max(1, rows // 2), size=n)
+    cnt[0] = rows
+    off = np.concatenate([[0], np.cumsum(cnt)]).astype(np.int64)
+    A = rng.standard_normal((int(off[-1]), d), dtype=np.float32)
+    y = np.where(rng.random(int(off[-1])) < 0.5, 1.0, -1.0).astype(np.float32)
+    x0 = (rng.standard_normal(d) / np.sqrt(d)).astype(np.float32)
+    eng = E.AdaCGD(n=n, d=d, gamma=0.3, lam=0.1, worker_levels=[(E.TOPK, max(1, d // 10)), (E.TOPK, d)], zeta_worker=0.0,
+                   master_levels=[], grad_mode=E.GRAD_LOGISTIC, A=_cuda(A), labels=_cuda(y), shard_offsets=off, x0=_cuda(x0),
+                   flags=E.FLAG_ANY_LEVEL_ORDER)
+    for step in range(4):        # (both sets of what blocks meet at are used twice)
+        if step:
+            eng.step()
+        x = eng.state(E.F_X).astype(np.float64)
+        got = eng.state(E.F_GRAD).reshape(n, d)
+        for i in range(n):
+            a = A[off[i]:off[i + 1]].astype(np.float64)
+            yi = y[off[i]:off[i + 1]].astype(np.float64)
+            s = -yi / (1.0 + np.exp(yi * (a @ x))) / len(yi)
+            want = s @ a + 2 * np.float64(np.float32(0.1)) * x / (1 + x * x) ** 2
+            # fp64 sums rounded once: half a unit of the result, and what the sums themselves may lose (2^-52 a term)
+            bound = np.abs(want) * 2.0 ** -23 + (np.abs(s) @ np.abs(a)) * (d + len(yi)) * 2.0 ** -52
+            assert (np.abs(got[i] - want) <= bound).all(), (n, d, rows, step, i)
+    eng.close()
