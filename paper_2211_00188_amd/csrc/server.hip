@@ -81,15 +81,27 @@ __global__ __launch_bounds__(kBlock) void k_aggregate(NodeSet ws, const float* _
     s_pre[tid] = pre;
     if (tid == 0) s_pre[kBlock] = total;
     __syncthreads();
-    for (uint32_t e = tid; e < total; e += kBlock) {
-      // the worker whose range holds flattened entry e: last j with s_pre[j] <= e
-      int lo_j = 0, hi_j = kBlock;
-      while (hi_j - lo_j > 1) {
-        const int mid = (lo_j + hi_j) >> 1;
-        if (s_pre[mid] <= e) lo_j = mid; else hi_j = mid;
+    // (four entries a thread side by side: one after the other, the search and the loads of each would be waited for)
+    for (uint32_t e0 = tid; e0 < total; e0 += 4 * kBlock) {
+      int32_t idx[4];
+      float val[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const uint32_t e = min(e0 + u * kBlock, total - 1);
+        // the worker whose range holds flattened entry e: last j with s_pre[j] <= e
+        int lo_j = 0, hi_j = kBlock;
+#pragma unroll
+        for (int step = kBlock / 2; step > 0; step >>= 1) {
+          const int mid = (lo_j + hi_j) >> 1;
+          if (s_pre[mid] <= e) lo_j = mid; else hi_j = mid;
+        }
+        const size_t off = (size_t)(n0 + lo_j) * ws.Kcap + s_lo[lo_j] + (e - s_pre[lo_j]);
+        idx[u] = ws.msg_idx[off];
+        val[u] = ws.msg_val[off];
       }
-      const size_t off = (size_t)(n0 + lo_j) * ws.Kcap + s_lo[lo_j] + (e - s_pre[lo_j]);
-      unsafeAtomicAdd(&acc[ws.msg_idx[off] - base], (double)ws.msg_val[off]);
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+        if (e0 + u * kBlock < total) unsafeAtomicAdd(&acc[idx[u] - base], (double)val[u]);
     }
     __syncthreads();
   }
@@ -98,11 +110,25 @@ __global__ __launch_bounds__(kBlock) void k_aggregate(NodeSet ws, const float* _
     for (int c = tid; c < kWaveTile; c += kBlock)
       st_coherent(&ws.agg_part[((size_t)blockIdx.y * ws.groups + g) * kWaveTile + c], acc[c]);
     if (!arrive_last(&ws.agg_done[(size_t)g * (kArriveFan + 1) * kCounterStride], (uint32_t)AS, blockIdx.y, &s_flag)) return;
-    for (int c = tid; c < kWaveTile; c += kBlock) {
-      double t = 0.0;
-      for (int b = 0; b < AS; ++b) t += ld_coherent(&ws.agg_part[((size_t)b * ws.groups + g) * kWaveTile + c]);
-      acc[c] = t;       // thread tid wrote and reads the same entries: no barrier needed
+    // (sixteen loads in flight a thread: one after the other, each was waited for)
+    constexpr int PER = kWaveTile / kBlock, U = 2;
+    double t[PER];
+#pragma unroll
+    for (int k = 0; k < PER; ++k) t[k] = 0.0;
+    for (int b0 = 0; b0 < AS; b0 += U) {
+      double v[U][PER];
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+#pragma unroll
+        for (int k = 0; k < PER; ++k)
+          v[u][k] = b0 + u < AS ? ld_coherent(&ws.agg_part[((size_t)(b0 + u) * ws.groups + g) * kWaveTile + k * kBlock + tid]) : 0.0;
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+#pragma unroll
+        for (int k = 0; k < PER; ++k) t[k] += v[u][k];
     }
+#pragma unroll
+    for (int k = 0; k < PER; ++k) acc[k * kBlock + tid] = t[k];       // thread tid wrote and reads the same entries: no barrier needed
   }
   if (DENSE_LATER) {
     for (int c = tid; c < kWaveTile; c += kBlock)
@@ -186,66 +212,102 @@ __global__ __launch_bounds__(kBlock) void k_aggregate_ordered(NodeSet ws, const 
   }
 }
 
-// Dense (quantised) messages: a block owns 128 coordinates, each lane two of them (one 4-byte
-// load per worker); its eight wavefronts take one eighth of the workers each, in ascending order,
-// eight workers' loads in flight at a time, and their partial sums are combined in wavefront
-// order: g~_new = fl(g~_old + (sparse sums + dense sums) / n).
-constexpr int kDenseCols = 128;
+// Dense (quantised, Rank-K) messages: a block owns 256 coordinates, each lane four of them; its eight wavefronts take
+// one eighth of the workers each, in ascending order, and their partial sums are combined in wavefront order:
+// g~_new = fl(g~_old + (sparse sums + dense sums) / n).  What the workers chose is read for 64 of them at a time, so
+// that only the messages themselves are waited for, eight workers' at a time: with two coordinates a lane and the
+// chain choice -> scale -> codes for every eight workers it took 53 us for 32 workers of 2^20 coordinates.
+constexpr int kDenseCols = 256;
 constexpr int kDenseWaves = 8;
 __global__ __launch_bounds__(64 * kDenseWaves) void k_aggregate_dense(NodeSet ws, const float* __restrict__ gt_old,
                                                                       float* __restrict__ gt_new, IterateUpdate xu) {
   __shared__ double part[kDenseWaves][kDenseCols];
-  const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63;
+  const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
   const int64_t d = ws.d;
-  const int64_t c0 = (int64_t)blockIdx.x * kDenseCols + 2 * lane;
-  const bool ok0 = c0 < d, ok1 = c0 + 1 < d;
-  const bool pair = ok1 && (d % 2 == 0);       // rows are then 4-byte aligned at c0
+  const int64_t c0 = (int64_t)blockIdx.x * kDenseCols + 4 * lane;
+  const bool quad = d % 4 == 0;       // rows of codes are then 8-byte aligned at c0, and four coordinates exist or none
   const int q = (ws.nn + kDenseWaves - 1) / kDenseWaves;
   const int i0 = w * q, i1 = min(ws.nn, i0 + q);
-  double a0 = 0.0, a1 = 0.0;
-  auto decode = [](int code, float sc) {
-    const float mag = (float)(code < 0 ? -code : code) * sc;
-    return (double)(code < 0 ? -mag : mag);
-  };
-  // Rank-K messages are dense fp32 vectors: workers that chose one, in ascending order after this
-  // wavefront's quantised ones
-  if (ws.lv.nr > 0) {
-    for (int i = i0; i < i1; ++i) {
-      if (ws.sel_rk[i] < 0) continue;
-      const float* __restrict__ rd = ws.rdense + (size_t)i * d;
-      if (ok0) a0 += (double)rd[c0];
-      if (ok1) a1 += (double)rd[c0 + 1];
-    }
-  }
   constexpr int U = 8;
-  for (int i = i0; i < i1; i += U) {
-    int k0[U], k1[U];
-    float sc[U];
+  double a[4] = {0.0, 0.0, 0.0, 0.0};
+  // Rank-K messages are dense fp32 vectors (d is a multiple of 16 then): workers that chose one, in ascending order,
+  // before this wavefront's quantised ones
+  if (ws.lv.nr > 0) {
+    for (int ib = i0; ib < i1; ib += 64) {
+      uint64_t m = ballot(ib + lane < i1 && ws.sel_rk[ib + lane] >= 0);
+      while (m) {
+        float4 v[U];
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int ii = i + u;
-      const int qi = (ii < i1 && ws.lv.nq > 0) ? ws.sel_q[ii] : -1;
-      const bool dense = qi >= 0;
-      const int B = dense ? ws.lv.qblock[qi] : 0;          // block-wise level: the scale of this coordinate pair's block
-      sc[u] = !dense ? 0.f : (B ? ws.qbscale[(size_t)ii * ws.nseg + (ok0 ? c0 / B : 0)] : ws.qscale[ii]);
-      const int16_t* __restrict__ codes = ws.qcodes + (size_t)(dense ? ii : 0) * d;
-      if (pair) {
-        const uint32_t two = dense ? *reinterpret_cast<const uint32_t*>(codes + c0) : 0u;
-        k0[u] = (int)(int16_t)(two & 0xFFFFu);
-        k1[u] = (int)(int16_t)(two >> 16);
-      } else {
-        k0[u] = (dense && ok0) ? (int)codes[c0] : 0;
-        k1[u] = (dense && ok1) ? (int)codes[c0 + 1] : 0;
+        for (int u = 0; u < U; ++u) {
+          v[u] = make_float4(0.f, 0.f, 0.f, 0.f);
+          if (m) {
+            const int i = ib + __builtin_ctzll(m);
+            m &= m - 1;
+            if (c0 < d) v[u] = *reinterpret_cast<const float4*>(ws.rdense + (size_t)i * d + c0);
+          }
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          a[0] += (double)v[u].x;
+          a[1] += (double)v[u].y;
+          a[2] += (double)v[u].z;
+          a[3] += (double)v[u].w;
+        }
       }
     }
+  }
+  if (ws.lv.nq > 0) {
+    for (int ib = i0; ib < i1; ib += 64) {
+      const int i = ib + lane;
+      const int qi = i < i1 ? ws.sel_q[i] : -1;
+      const uint32_t Bl = qi >= 0 && ws.lv.nqb > 0 ? (uint32_t)ws.lv.qblock[qi] : 0u;      // block-wise level: its block length
+      const uint32_t scl = i < i1 ? fbits(ws.qscale[i]) : 0u;
+      uint64_t m = ballot(qi >= 0);
+      while (m) {
+        uint32_t k01[U], k23[U];
+        float sc[U];
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      a0 += decode(k0[u], sc[u]);
-      a1 += decode(k1[u], sc[u]);
+        for (int u = 0; u < U; ++u) {
+          k01[u] = k23[u] = 0;
+          sc[u] = 0.f;
+          if (m) {
+            const int j = __builtin_ctzll(m);
+            m &= m - 1;
+            const uint32_t B = lane_value(Bl, j);
+            const int16_t* __restrict__ codes = ws.qcodes + (size_t)(ib + j) * d + c0;
+            sc[u] = __uint_as_float(lane_value(scl, j));
+            if (B) sc[u] = ws.qbscale[(size_t)(ib + j) * ws.nseg + (c0 < d ? (uint32_t)c0 / B : 0u)];
+            if (quad) {
+              if (c0 < d) {
+                const uint2 two = *reinterpret_cast<const uint2*>(codes);
+                k01[u] = two.x;
+                k23[u] = two.y;
+              }
+            } else {
+              uint32_t k[4];
+#pragma unroll
+              for (int c = 0; c < 4; ++c) k[c] = c0 + c < d ? (uint32_t)(uint16_t)codes[c] : 0u;
+              k01[u] = k[0] | (k[1] << 16);
+              k23[u] = k[2] | (k[3] << 16);
+            }
+          }
+        }
+        auto decode = [](int code, float s) {
+          const float mag = (float)(code < 0 ? -code : code) * s;
+          return (double)(code < 0 ? -mag : mag);
+        };
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          a[0] += decode((int)(int16_t)(k01[u] & 0xFFFFu), sc[u]);
+          a[1] += decode((int)(int16_t)(k01[u] >> 16), sc[u]);
+          a[2] += decode((int)(int16_t)(k23[u] & 0xFFFFu), sc[u]);
+          a[3] += decode((int)(int16_t)(k23[u] >> 16), sc[u]);
+        }
+      }
     }
   }
-  part[w][2 * lane] = a0;
-  part[w][2 * lane + 1] = a1;
+#pragma unroll
+  for (int c = 0; c < 4; ++c) part[w][4 * lane + c] = a[c];
   __syncthreads();
   if (tid < kDenseCols) {
     const int64_t c = (int64_t)blockIdx.x * kDenseCols + tid;
