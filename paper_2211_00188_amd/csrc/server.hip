@@ -441,6 +441,10 @@ __global__ __launch_bounds__(kBlock) void k_csr_margins(LogisticData ld, const f
   const int sub = threadIdx.x % LPR;
   const bool live = l < ld.rows;
   const int64_t b = live ? ld.rp[l] : 0, e = live ? ld.rp[l + 1] : 0;
+  // (what the row's weight needs beside its product, asked for before the product and not after it)
+  const int node = live ? ld.row_node[l] : 0;
+  const double yl = live ? (double)ld.labels[l] : 0.0;
+  const double N = (double)(ld.offsets[node + 1] - ld.offsets[node]);
   double acc = 0.0;
   int64_t k = b + sub;
   for (; k + 3 * LPR < e; k += 4 * LPR) {          // four entries at a time: their gathers overlap
@@ -460,12 +464,7 @@ __global__ __launch_bounds__(kBlock) void k_csr_margins(LogisticData ld, const f
   }
 #pragma unroll
   for (int o = LPR >> 1; o > 0; o >>= 1) acc += __shfl_xor(acc, o);
-  if (live && sub == 0) {
-    const int node = ld.row_node[l];
-    const double N = (double)(ld.offsets[node + 1] - ld.offsets[node]);
-    const double yl = (double)ld.labels[l];
-    ld.margins[l] = -yl / (1.0 + exp(yl * acc)) / N;
-  }
+  if (live && sub == 0) ld.margins[l] = -yl / (1.0 + exp(yl * acc)) / N;
 }
 
 template <int LPC>   // lanes per column, a power of two: long columns are shared by 16 or 64 lanes
@@ -491,37 +490,51 @@ __global__ __launch_bounds__(kBlock) void k_csr_cols(LogisticData ld, const floa
 // Short columns (a few entries per worker-column): one thread owns four columns, 64 apart, and walks
 // them side by side, so that four independent chains of gathers (row of the entry, then its margin)
 // are in flight instead of one.  Same order of summation per column as k_csr_cols<1>.
+template <bool BINARY>
 __global__ __launch_bounds__(kBlock) void k_csr_cols4(LogisticData ld, const float* __restrict__ x,
                                                        float* __restrict__ grads, int64_t d) {
   const int node = blockIdx.y, w = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int64_t j0 = ((int64_t)blockIdx.x * 4 + w) * 256 + lane;      // columns j0, j0+64, j0+128, j0+192
   const uint32_t* __restrict__ cp = ld.cptr + (size_t)node * (size_t)(d + 1);
-  const int64_t w0 = ld.wbase[node];
-  int64_t b[4], e[4];
+  const int32_t* __restrict__ trow = ld.trow + ld.wbase[node];
+  const float* __restrict__ tval = BINARY ? nullptr : ld.tval + ld.wbase[node];
+  uint32_t b[4], e[4];
   double acc[4];
 #pragma unroll
   for (int c = 0; c < 4; ++c) {
     const int64_t j = j0 + 64 * c;
     const bool live = j < d;
-    b[c] = live ? w0 + cp[j] : 0;
-    e[c] = live ? w0 + cp[j + 1] : 0;
+    b[c] = live ? cp[j] : 0u;
+    e[c] = live ? cp[j + 1] : 0u;
     acc[c] = 0.0;
   }
-  int64_t longest = 0;
+  uint32_t longest = 0;
 #pragma unroll
   for (int c = 0; c < 4; ++c) longest = max(longest, e[c] - b[c]);
-  for (int64_t t = 0; t < longest; ++t) {
-    int32_t r[4];
-    float a[4];
+  // (kDeep entries of every column at a time: entry after entry, the longest of the wavefront's 256 columns -- five entries
+  // where the mean is one -- makes it wait for as many pairs of dependent gathers)
+  constexpr int kDeep = 4;
+  for (uint32_t t = 0; t < longest; t += kDeep) {
+    int32_t r[kDeep][4];
+    float a[kDeep][4];
+    double m[kDeep][4];
 #pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      const bool on = b[c] + t < e[c];
-      r[c] = on ? ld.trow[b[c] + t] : -1;
-      a[c] = (on && !ld.binary) ? ld.tval[b[c] + t] : 1.f;
-    }
+    for (int u = 0; u < kDeep; ++u)
 #pragma unroll
-    for (int c = 0; c < 4; ++c)
-      if (r[c] >= 0) acc[c] = fma(ld.margins[r[c]], (double)a[c], acc[c]);
+      for (int c = 0; c < 4; ++c) {
+        const bool on = t + u < e[c] - b[c];
+        r[u][c] = on ? trow[b[c] + t + u] : -1;
+        a[u][c] = (on && !BINARY) ? tval[b[c] + t + u] : 1.f;
+      }
+#pragma unroll
+    for (int u = 0; u < kDeep; ++u)
+#pragma unroll
+      for (int c = 0; c < 4; ++c) m[u][c] = r[u][c] >= 0 ? ld.margins[r[u][c]] : 0.0;
+#pragma unroll
+    for (int u = 0; u < kDeep; ++u)
+#pragma unroll
+      for (int c = 0; c < 4; ++c)
+        if (r[u][c] >= 0) acc[c] = fma(m[u][c], (double)a[u][c], acc[c]);
   }
 #pragma unroll
   for (int c = 0; c < 4; ++c) {
@@ -616,7 +629,8 @@ hipError_t launch_grad_cols(const LogisticData& ld, const float* x, float* grads
     const dim3 grid((unsigned)((d * lpc + kBlock - 1) / kBlock), n);
     if (lpc == 64) hipLaunchKernelGGL((k_csr_cols<64>), grid, dim3(kBlock), 0, st, ld, x, grads, d);
     else if (lpc == 16) hipLaunchKernelGGL((k_csr_cols<16>), grid, dim3(kBlock), 0, st, ld, x, grads, d);
-    else hipLaunchKernelGGL(k_csr_cols4, dim3((unsigned)((d + 1023) / 1024), n), dim3(kBlock), 0, st, ld, x, grads, d);
+    else if (ld.binary) hipLaunchKernelGGL((k_csr_cols4<true>), dim3((unsigned)((d + 1023) / 1024), n), dim3(kBlock), 0, st, ld, x, grads, d);
+    else hipLaunchKernelGGL((k_csr_cols4<false>), dim3((unsigned)((d + 1023) / 1024), n), dim3(kBlock), 0, st, ld, x, grads, d);
     return hipGetLastError();
   }
   const bool vec = (d % 4 == 0) && ((reinterpret_cast<uintptr_t>(ld.A) & 15u) == 0);
