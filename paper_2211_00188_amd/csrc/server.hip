@@ -215,11 +215,12 @@ __global__ __launch_bounds__(kBlock) void k_aggregate_ordered(NodeSet ws, const 
 // Dense (quantised, Rank-K) messages: a block owns 256 coordinates, each lane four of them; its eight wavefronts take
 // one eighth of the workers each, in ascending order, and their partial sums are combined in wavefront order:
 // g~_new = fl(g~_old + (sparse sums + dense sums) / n).  What the workers chose is read for 64 of them at a time, so
-// that only the messages themselves are waited for, eight workers' at a time: with two coordinates a lane and the
-// chain choice -> scale -> codes for every eight workers it took 53 us for 32 workers of 2^20 coordinates.
+// that only the messages themselves are waited for, four workers' at a time (eight would halve the wavefronts in flight): with two coordinates a lane and the
+// chain choice -> scale -> codes for every eight workers it took 53 us for 32 workers of 2^20 coordinates (now 20) and
+// 135 us for 1000 of 65536 (now 45).
 constexpr int kDenseCols = 256;
 constexpr int kDenseWaves = 8;
-__global__ __launch_bounds__(64 * kDenseWaves) void k_aggregate_dense(NodeSet ws, const float* __restrict__ gt_old,
+__global__ __launch_bounds__(64 * kDenseWaves, 8) void k_aggregate_dense(NodeSet ws, const float* __restrict__ gt_old,
                                                                       float* __restrict__ gt_new, IterateUpdate xu) {
   __shared__ double part[kDenseWaves][kDenseCols];
   const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
@@ -228,7 +229,12 @@ __global__ __launch_bounds__(64 * kDenseWaves) void k_aggregate_dense(NodeSet ws
   const bool quad = d % 4 == 0;       // rows of codes are then 8-byte aligned at c0, and four coordinates exist or none
   const int q = (ws.nn + kDenseWaves - 1) / kDenseWaves;
   const int i0 = w * q, i1 = min(ws.nn, i0 + q);
-  constexpr int U = 8;
+  constexpr int U = 4;
+  // (what the last part needs, asked for now)
+  const int64_t col = (int64_t)blockIdx.x * kDenseCols + tid;
+  const bool mine = tid < kDenseCols && col < d;
+  const double sparse = mine ? ws.accbuf[col] : 0.0;
+  const float gt = mine ? gt_old[col] : 0.f;
   double a[4] = {0.0, 0.0, 0.0, 0.0};
   // Rank-K messages are dense fp32 vectors (d is a multiple of 16 then): workers that chose one, in ascending order,
   // before this wavefront's quantised ones
@@ -309,16 +315,13 @@ __global__ __launch_bounds__(64 * kDenseWaves) void k_aggregate_dense(NodeSet ws
 #pragma unroll
   for (int c = 0; c < 4; ++c) part[w][4 * lane + c] = a[c];
   __syncthreads();
-  if (tid < kDenseCols) {
-    const int64_t c = (int64_t)blockIdx.x * kDenseCols + tid;
-    if (c < d) {
-      double tot = ws.accbuf[c];
+  if (mine) {
+    double tot = sparse;
 #pragma unroll
-      for (int j = 0; j < kDenseWaves; ++j) tot += part[j][tid];
-      const float gn = (float)((double)gt_old[c] + tot / (double)ws.nn);
-      gt_new[c] = gn;
-      if (xu.out) xu.out[c] = (float)((double)xu.x[c] - xu.gamma * (double)gn);
-    }
+    for (int j = 0; j < kDenseWaves; ++j) tot += part[j][tid];
+    const float gn = (float)((double)gt + tot / (double)ws.nn);
+    gt_new[col] = gn;
+    if (xu.out) xu.out[col] = (float)((double)xu.x[col] - xu.gamma * (double)gn);
   }
 }
 
