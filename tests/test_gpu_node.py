@@ -39,3 +39,49 @@ def test_one_launch_step_at_the_edges_of_its_layout(n, d, kind):
             eng.step(_cuda(g))
             compare_step(eng, orc, res, rm, ("node", n, d, kind, t))
     eng.close()
+
+
+@pytest.mark.parametrize("n,d,logistic", [(3, 20000, False), (12, 65000, False), (2, 5003, True), (3, 65000, True)])
+def test_captured_steps_replay(n, d, logistic):
+    """Two captured steps (they lead back to the buffers they began with) replayed any number of times between eager
+    ones: what the blocks of a launch meet at is cleared around a captured launch."""
+    import torch
+    E = _eng()
+    rng = np.random.default_rng(d)
+    st = torch.cuda.Stream()
+    kw = dict(n=n, d=d, gamma=0.05, worker_levels=[(E.TOPK, d // 100), (E.TOPK, d // 10)], zeta_worker=0.3,
+              master_levels=[(E.TOPK, d // 20)], zeta_master=0.0, seed=5, x0=_cuda(rng.standard_normal(d).astype(np.float32)))
+    if logistic:
+        rows = 9
+        kw.update(grad_mode=E.GRAD_LOGISTIC, A=_cuda(rng.standard_normal((n * rows, d)).astype(np.float32)), lam=0.1,
+                  labels=_cuda(np.where(rng.random(n * rows) < 0.5, 1.0, -1.0).astype(np.float32)),
+                  shard_offsets=np.arange(n + 1, dtype=np.int64) * rows)
+        args = [(), ()]
+    else:
+        g = [_cuda(rng.standard_normal((n, d)).astype(np.float32)) for _ in range(3)]
+        kw.update(grad_mode=E.GRAD_EXTERNAL, grad0=g[2], flags=E.FLAG_RETAIN_EXT)
+        args = [(g[0],), (g[1],)]
+    torch.cuda.synchronize()
+    with torch.cuda.stream(st):
+        eng, ref = E.AdaCGD(**kw), E.AdaCGD(**kw)
+        both = lambda e: [e.step(*a) for a in args]
+        both(eng)
+        both(ref)
+        graph = torch.cuda.CUDAGraph()
+        st.synchronize()
+        with torch.cuda.graph(graph, stream=st):
+            both(eng)
+        for replays in (1, 2, 1):
+            for _ in range(replays):
+                graph.replay()
+                both(ref)
+            both(eng)
+            both(ref)
+            eng.step(*args[0])
+            eng.step(*args[1])
+            both(ref)
+            st.synchronize()
+            for f in (E.F_X, E.F_GI, E.F_GTILDE, E.F_G):
+                np.testing.assert_array_equal(eng.state(f), ref.state(f), err_msg=str((replays, f)))
+    eng.close()
+    ref.close()
