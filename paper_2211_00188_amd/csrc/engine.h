@@ -64,7 +64,7 @@ struct LevelTable {
 // one set of what the blocks of a node meet at: the partial results and three histograms.
 __host__ __device__ inline size_t node_part_quantities(int pk, int nq) { return 4 + 1 + 3 * (size_t)pk + nq; }
 __host__ __device__ inline size_t node_meet_words(int pk, int nq, int NB) {
-  return 2 * node_part_quantities(pk, nq) * NB + kBins0 + (size_t)pk * (kBins1 + kBins2);
+  return 2 * node_part_quantities(pk, nq) * NB + (pk > 0 ? kBins0 : 0) + (size_t)pk * (kBins1 + kBins2);
 }
 
 // Device arrays of one side.  nn nodes, each with a length-d vector.

@@ -225,7 +225,7 @@ void carve_nodeset(Carver& c, NodeSet& ns) {
   ns.agg_part = ns.AS > 1 ? c.take<double>((size_t)ns.AS * ns.groups * kWaveTile) : nullptr;
 }
 
-void shape_nodeset(NodeSet& ns, int nn, int64_t d, bool force_two_pass) {
+void shape_nodeset(NodeSet& ns, int nn, int64_t d, bool force_two_pass, bool chunks) {
   ns.nn = nn;
   ns.d = d;
   ns.tiles = (int)((d + kTile - 1) / kTile);
@@ -252,7 +252,7 @@ void shape_nodeset(NodeSet& ns, int nn, int64_t d, bool force_two_pass) {
   ns.chunk = (int)d;
   if (!force_two_pass && d <= kNodeChunk) {
     ns.small = 1;
-  } else if (!force_two_pass && d <= (int64_t)kNodeChunk * kNodeParts) {
+  } else if (!force_two_pass && chunks && d <= (int64_t)kNodeChunk * kNodeParts) {
     auto parts = [&](int64_t chunk) { return (d + chunk - 1) / chunk; };
     int64_t chunk = 4096;
     while (chunk < kNodeChunk && (parts(chunk) > kNodeParts || nn * parts(chunk) > kNodeResident)) chunk *= 2;
@@ -508,6 +508,28 @@ void shape_logistic(const adacgd_config* cfg, LogisticData& ld) {
   int64_t chunks = (mx + 255) / 256;    // about 256 rows per block (64 per wavefront) ...
   if (chunks > 64) chunks = 64;         // ... but a bounded number of partial sums
   ld.row_chunks = (int)chunks;
+}
+
+// Layout of both sides and of the objective; returns the bytes of workspace.  Several blocks per node that meet need
+// some memory that the general kernels do without (the next iterate's buffer, what they meet at): a configuration that
+// fits the static workspace only without them does without them, whichever workspace it gets.
+size_t shape_all(const adacgd_config* cfg, const LevelTable& wl, const LevelTable& ml, NodeSet& W, NodeSet& M, LogisticData& ld) {
+  const bool two_pass = (cfg->flags & ADACGD_FLAG_TWO_PASS) != 0;
+  auto shape = [&](bool chunks) {
+    W = NodeSet{};
+    M = NodeSet{};
+    W.lv = wl;
+    M.lv = ml;
+    shape_nodeset(W, (int)cfg->n, cfg->d, two_pass, chunks);
+    shape_nodeset(M, 1, cfg->d, two_pass, chunks);
+    shape_logistic(cfg, ld);
+    Layout L{};
+    return carve_all(nullptr, cfg, W, M, ld, L);
+  };
+  const size_t need = shape(true);
+  if (need <= (size_t)ADACGD_STATIC_WORKSPACE_BYTES) return need;
+  const size_t less = shape(false);
+  return less <= (size_t)ADACGD_STATIC_WORKSPACE_BYTES ? less : shape(true);
 }
 
 #define HIPCHK(ctx, call)                                                            \
@@ -818,14 +840,9 @@ int adacgd_workspace_bytes(const adacgd_config* cfg, int64_t* bytes) {
   int rc = validate(cfg, &wl, &ml, g_err);
   if (rc) return rc;
   if (!bytes) { set_err(g_err, "bytes is null"); return ADACGD_ERR_ARG; }
-  NodeSet W{}, M{};
-  W.lv = wl; M.lv = ml;
-  shape_nodeset(W, (int)cfg->n, cfg->d, (cfg->flags & ADACGD_FLAG_TWO_PASS) != 0);
-  shape_nodeset(M, 1, cfg->d, (cfg->flags & ADACGD_FLAG_TWO_PASS) != 0);
+  NodeSet W, M;
   LogisticData ld;
-  shape_logistic(cfg, ld);
-  Layout L{};
-  *bytes = (int64_t)carve_all(nullptr, cfg, W, M, ld, L);
+  *bytes = (int64_t)shape_all(cfg, wl, ml, W, M, ld);
   return ADACGD_OK;
 }
 
@@ -914,11 +931,7 @@ static int init_impl(const adacgd_config* cfg, adacgd_ctx** out, int static_dev)
   c->cs = c->st; c->wst = nullptr; c->ev_worker = nullptr; c->ev_agg = nullptr; c->agg_recorded = false;
   std::memset(c->ms_sum, 0, sizeof(c->ms_sum));
   std::memset(c->ms_cnt, 0, sizeof(c->ms_cnt));
-  c->W = NodeSet{}; c->M = NodeSet{};
-  c->W.lv = wl; c->M.lv = ml;
-  shape_nodeset(c->W, (int)cfg->n, cfg->d, (cfg->flags & ADACGD_FLAG_TWO_PASS) != 0);
-  shape_nodeset(c->M, 1, cfg->d, (cfg->flags & ADACGD_FLAG_TWO_PASS) != 0);
-  shape_logistic(cfg, c->ld);
+  shape_all(cfg, wl, ml, c->W, c->M, c->ld);
   Layout L{};
   const size_t need = carve_all(c->ws_base, cfg, c->W, c->M, c->ld, L);
   if ((int64_t)need > workspace_bytes) {

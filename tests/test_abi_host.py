@@ -155,3 +155,15 @@ def test_header_is_plain_c_and_matches_the_binding(tmp_path):
     out = subprocess.run([str(exe)], check=True, capture_output=True, text=True).stdout.split()
     assert [int(v) for v in out[:3]] == [C.sizeof(E.Config), C.sizeof(E.Level), C.sizeof(E.Trigger)]
     assert [int(v) for v in out[3:]] == [getattr(E.Config, f).offset for f in fields]
+
+
+def test_a_configuration_near_the_static_workspace_keeps_fitting_it():
+    """Blocks that meet need some more memory than the general kernels: 8 x 575000 with a quantiser on both sides takes
+    65.8 MB without them, 68.0 MB with them, and the static workspace holds 67.1 MB."""
+    levels = dict(worker_levels=[(E.QUANT, 4)], master_levels=[(E.QUANT, 4)], flags=E.FLAG_RETAIN_EXT)
+    near = E.adacgd_workspace_bytes(_cfg(n=8, d=575000, **levels)[0])
+    assert 65_000_000 < near <= E.STATIC_WORKSPACE_BYTES
+    two_pass = E.adacgd_workspace_bytes(_cfg(n=8, d=575000, **dict(levels, flags=E.FLAG_RETAIN_EXT | E.FLAG_TWO_PASS))[0])
+    assert near == two_pass
+    assert E.adacgd_workspace_bytes(_cfg(n=8, d=560000, **levels)[0]) > E.adacgd_workspace_bytes(
+        _cfg(n=8, d=560000, **dict(levels, flags=E.FLAG_RETAIN_EXT | E.FLAG_TWO_PASS))[0])
