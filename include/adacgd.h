@@ -29,6 +29,10 @@
  *  - All work is enqueued on the caller's stream; adacgd_step does not
  *    synchronise.  adacgd_state synchronises the stream before copying.
  *  - One context must not be used from two threads at once.
+ *  - Steps may be captured into a graph on the caller's stream, an even number of them (two steps lead back to
+ *    the buffers they began with) by one or several adacgd_step calls, at any time after init, and replayed any
+ *    number of times between other calls.  With ADACGD_FLAG_RETAIN_EXT the first captured step compares with the
+ *    array of the step before the capture.
  *  - Server aggregation: every coordinate's sum over the workers' messages is taken in fp64 and rounded
  *    to fp32 once.  With Top-K levels only and at most 64 workers the messages are added in ascending
  *    worker index (the sequential sum, reproducible for any data).  With more workers, or with quantiser

@@ -237,7 +237,7 @@ hipError_t launch_rank_eig(const NodeSet& ns, const PassArgs& a, hipStream_t st)
 hipError_t launch_rank_errors(const NodeSet& ns, const PassArgs& a, hipStream_t st);
 hipError_t launch_rank_apply(const NodeSet& ns, const PassArgs& a, hipStream_t st);
 
-hipError_t launch_xupdate(float* x, const float* g, double gamma, int64_t d, hipStream_t st);
+hipError_t launch_xupdate(float* out, const float* x, const float* g, double gamma, int64_t d, hipStream_t st);
 hipError_t launch_mean(const float* gi, float* out0, float* out1, float* out2, int n, int64_t d, hipStream_t st);
 // optional extra of a kernel that finishes g: x_next = fl(x - gamma g) (out == nullptr: not asked for)
 struct IterateUpdate {

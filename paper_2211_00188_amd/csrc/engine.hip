@@ -319,8 +319,10 @@ struct adacgd_ctx {
   NodeSet W, M;
   bool has_master;
   float* x;
-  float* x_next;    // x - gamma g, when the kernel that produced g has already written it (short vectors)
-  bool x_next_valid;
+  float* x_next;    // x - gamma g wherever the kernel that finishes g writes it (no master compressor, or one that runs in
+                    // one launch), else null.  It is there between any two calls, not only after a step, so that every step
+                    // makes the same launches on the same two buffers in turn: a captured pair of steps can be replayed
+                    // whatever came before it.
   float* g_own;     // master estimator g when the master compresses
   float* gt[2];     // g~^t and g~^{t-1}; cur indexes g~^t
   int cur;
@@ -433,7 +435,7 @@ size_t carve_all(char* base, const adacgd_config* cfg, NodeSet& W, NodeSet& M, L
     L.m_zero = base ? (size_t)((char*)M.prefix - (char*)M.hist0) : 0;
   }
   L.x = c.take<float>(d);
-  L.x_next = (W.small || M.small || M.lv.m == 0) ? c.take<float>(d) : nullptr;
+  L.x_next = (M.small || M.lv.m == 0) ? c.take<float>(d) : nullptr;
   L.g_own = M.lv.m > 0 ? c.take<float>(d) : nullptr;
   L.gt0 = c.take<float>(d);
   L.gt1 = c.take<float>(d);
@@ -670,11 +672,10 @@ int one_step(adacgd_ctx* c, const float* ext, const double* extD) {
   // depend on the server chain of step t (gradients are supplied), so the two run concurrently.
   const bool ov = c->wst != nullptr;
   c->cs = c->st;
-  // x^{t+1} = x^t - gamma g^t (already there if the kernel that finished g^t wrote it as well)
-  if (c->x_next_valid) {
+  // x^{t+1} = x^t - gamma g^t (already there if the kernel that finished g^t writes it as well)
+  if (c->x_next) {
     std::swap(c->x, c->x_next);
-    c->x_next_valid = false;
-  } else if ((rc = timed(c, ADACGD_K_XUPDATE, [&] { return launch_xupdate(c->x, c->g(), c->gamma, c->d, c->cs); }))) {
+  } else if ((rc = timed(c, ADACGD_K_XUPDATE, [&] { return launch_xupdate(c->x, c->x, c->g(), c->gamma, c->d, c->cs); }))) {
     return rc;
   }
   // Short vectors, few workers, Top-K messages only: the one-block kernel of the workers also does the
@@ -708,7 +709,6 @@ int one_step(adacgd_ctx* c, const float* ext, const double* extD) {
       a.xu_x = c->x;
       a.xu_out = c->x_next;
       a.xu_gamma = c->gamma;
-      c->x_next_valid = true;
     }
   }
   // g~_i^{t+1} = C^AC_{g~_i^t, grad f_i(x^t)}(grad f_i(x^{t+1}))
@@ -732,7 +732,6 @@ int one_step(adacgd_ctx* c, const float* ext, const double* extD) {
       xu.x = c->x;
       xu.out = c->x_next;
       xu.gamma = c->gamma;
-      c->x_next_valid = true;
     }
     if ((rc = timed(c, ADACGD_K_AGGREGATE, [&] { return launch_aggregate(c->W, gt_old, gt_new, xu, c->cs); }))) return rc;
   }
@@ -750,11 +749,10 @@ int one_step(adacgd_ctx* c, const float* ext, const double* extD) {
     m.seed = c->seed;
     m.step = (uint32_t)c->step;
     m.node_flag = 0x80000000u;
-    if (c->M.small) {
+    if (c->x_next) {
       m.xu_x = c->x;
       m.xu_out = c->x_next;
       m.xu_gamma = c->gamma;
-      c->x_next_valid = true;
     }
     if ((rc = compress(c, c->M, m, ADACGD_K_M_SAMPLE, nullptr))) return rc;
   }
@@ -943,7 +941,7 @@ static int init_impl(const adacgd_config* cfg, adacgd_ctx** out, int static_dev)
     release_ctx(c, false);
     return ADACGD_ERR_ALLOC;
   }
-  c->x = L.x; c->x_next = L.x_next; c->x_next_valid = false; c->g_own = L.g_own; c->gt[0] = L.gt0; c->gt[1] = L.gt1; c->gi = L.gi;
+  c->x = L.x; c->x_next = L.x_next; c->g_own = L.g_own; c->gt[0] = L.gt0; c->gt[1] = L.gt1; c->gi = L.gi;
   c->yb[0] = L.yb0; c->yb[1] = L.yb1;
   c->ld.A = cfg->A; c->ld.labels = cfg->labels; c->ld.offsets = L.offsets; c->ld.row_node = L.row_node;
   c->ld.margins = L.margins; c->ld.part = L.part; c->ld.col_done = L.col_done;
@@ -1055,6 +1053,7 @@ static int init_impl(const adacgd_config* cfg, adacgd_ctx** out, int static_dev)
     INITCHK(launch_fill_u32((uint32_t*)c->W.level_hist, 0u, (size_t)(lv.m + 2) * 2, c->st));
   }
   INITCHK(launch_mean(c->gi, c->gt[0], c->gt[1], c->g_own, (int)c->n, c->d, c->st));
+  if (c->x_next) INITCHK(launch_xupdate(c->x_next, c->x, c->g(), c->gamma, c->d, c->st));
   // message tables start empty
   INITCHK(launch_fill_u32((uint32_t*)c->W.sel_slot, 0xFFFFFFFFu, (size_t)c->n, c->st));
   INITCHK(launch_fill_u32((uint32_t*)c->W.sel_q, 0xFFFFFFFFu, (size_t)c->n, c->st));
@@ -1283,16 +1282,15 @@ int adacgd_set_state(adacgd_ctx* c, int32_t field, const void* src, int64_t src_
     HIPCHK(c, hipStreamSynchronize(c->st));
     return ADACGD_OK;
   };
+  auto put_ahead = [&](float* dst) -> int {      // a vector of which the iterate written ahead is made
+    const int rc = put(dst, d * 4);
+    if (rc == ADACGD_OK && c->x_next) HIPCHK(c, launch_xupdate(c->x_next, c->x, c->g(), c->gamma, c->d, c->st));
+    return rc;
+  };
   switch (field) {
-    case ADACGD_F_X:
-      c->x_next_valid = false;      // the iterate written ahead belonged to the old x
-      return put(c->x, d * 4);
-    case ADACGD_F_G:
-      c->x_next_valid = false;
-      return put(c->has_master ? c->g_own : nullptr, d * 4);
-    case ADACGD_F_GTILDE:
-      if (!c->has_master) c->x_next_valid = false;   // g is g~ then
-      return put(c->gt[c->cur], d * 4);
+    case ADACGD_F_X: return put_ahead(c->x);
+    case ADACGD_F_G: return put_ahead(c->has_master ? c->g_own : nullptr);
+    case ADACGD_F_GTILDE: return put_ahead(c->gt[c->cur]);      // (g is g~ without a master compressor)
     case ADACGD_F_GTILDE_PREV: return put(c->gt[c->cur ^ 1], d * 4);
     case ADACGD_F_GI: return put(c->gi, n * d * 4);
     case ADACGD_F_PREV_GRAD:

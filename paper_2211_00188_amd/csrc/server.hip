@@ -10,10 +10,11 @@ namespace adacgd {
 // ---------------------------------------------------------------------------
 // small dense kernels
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(kBlock) void k_xupdate(float* __restrict__ x, const float* __restrict__ g, double gamma,
+// (out may be x)
+__global__ __launch_bounds__(kBlock) void k_xupdate(float* out, const float* x, const float* __restrict__ g, double gamma,
                                                      int64_t d) {
   const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-  if (i < d) x[i] = (float)((double)x[i] - gamma * (double)g[i]);   // one rounding
+  if (i < d) out[i] = (float)((double)x[i] - gamma * (double)g[i]);   // one rounding
 }
 
 // g~^0 = (1/n) sum_i g~_i^0, summed in ascending i in fp64; written to up to three vectors
@@ -556,9 +557,9 @@ static inline unsigned blocks_for(size_t count, unsigned cap = 65535u * 16u) {
   return (unsigned)(b > cap ? cap : b);
 }
 
-hipError_t launch_xupdate(float* x, const float* g, double gamma, int64_t d, hipStream_t st) {
+hipError_t launch_xupdate(float* out, const float* x, const float* g, double gamma, int64_t d, hipStream_t st) {
   (void)hipGetLastError();   // drop a stale error left by earlier runtime calls of this thread
-  hipLaunchKernelGGL(k_xupdate, dim3((unsigned)((d + kBlock - 1) / kBlock)), dim3(kBlock), 0, st, x, g, gamma, d);
+  hipLaunchKernelGGL(k_xupdate, dim3((unsigned)((d + kBlock - 1) / kBlock)), dim3(kBlock), 0, st, out, x, g, gamma, d);
   return hipGetLastError();
 }
 

@@ -85,3 +85,53 @@ def test_captured_steps_replay(n, d, logistic):
                 np.testing.assert_array_equal(eng.state(f), ref.state(f), err_msg=str((replays, f)))
     eng.close()
     ref.close()
+
+
+@pytest.mark.parametrize("n,d,logistic,master", [(3, 900, False, True), (3, 5003, True, True), (2, 20000, False, True), (70, 20000, False, True),
+                                                 (3, 900, True, False), (2, 20000, True, False), (2, 1100000, False, True)])
+def test_captured_steps_without_a_step_before_them_and_with_a_state_set_between_replays(n, d, logistic, master):
+    """Two steps captured right after init, and a state written between two replays: the iterate that a launch writes ahead
+    is there at the first step too, and follows what is set."""
+    import torch
+    E = _eng()
+    rng = np.random.default_rng(d + master)
+    st = torch.cuda.Stream()
+    kw = dict(n=n, d=d, gamma=0.05, worker_levels=[(E.TOPK, d // 100), (E.TOPK, d // 10)], zeta_worker=0.3,
+              master_levels=[(E.TOPK, d // 20)] if master else [], zeta_master=0.0, seed=5,
+              x0=_cuda(rng.standard_normal(d).astype(np.float32)))
+    if logistic:
+        rows = 9
+        kw.update(grad_mode=E.GRAD_LOGISTIC, A=_cuda(rng.standard_normal((n * rows, d)).astype(np.float32)), lam=0.1,
+                  labels=_cuda(np.where(rng.random(n * rows) < 0.5, 1.0, -1.0).astype(np.float32)),
+                  shard_offsets=np.arange(n + 1, dtype=np.int64) * rows)
+        args = [(), ()]
+    else:
+        g = [_cuda(rng.standard_normal((n, d)).astype(np.float32)) for _ in range(3)]
+        kw.update(grad_mode=E.GRAD_EXTERNAL, grad0=g[2])
+        args = [(g[0],), (g[1],)]
+    torch.cuda.synchronize()
+    same = lambda what: [np.testing.assert_array_equal(eng.state(f), ref.state(f), err_msg=str((what, f)))
+                         for f in (E.F_X, E.F_GI, E.F_GTILDE) + ((E.F_G,) if master else ())]
+    with torch.cuda.stream(st):
+        eng, ref = E.AdaCGD(**kw), E.AdaCGD(**kw)
+        both = lambda e: [e.step(*a) for a in args]
+        graph = torch.cuda.CUDAGraph()
+        st.synchronize()
+        with torch.cuda.graph(graph, stream=st):
+            both(eng)
+        for turn in range(3):
+            graph.replay()
+            both(ref)
+            same(("replay", turn))
+        for f in (E.F_X, E.F_G if master else E.F_GTILDE):
+            v = rng.standard_normal(d).astype(np.float32)
+            for e in (eng, ref):
+                e.set_state(f, v)
+            graph.replay()
+            both(ref)
+            same(("set", f))
+            both(eng)
+            both(ref)
+            same(("eager", f))
+    eng.close()
+    ref.close()
