@@ -14,6 +14,7 @@
 #include "../../include/adacgd.h"
 #include "devutil.h"
 #include "engine.h"
+#include "meeting.h"
 
 using namespace adacgd;
 
@@ -333,7 +334,7 @@ struct adacgd_ctx {
   LogisticData ld;
   int64_t step;
   uint64_t w_zero_bytes, m_zero_bytes;
-  uint32_t w_parity = 0, m_parity = 0, g_parity = 0;   // see PassArgs::parity, LogisticData::parity
+  MeetingSets w_meet, m_meet, g_meet;       // workers, master, gradients: see PassArgs::parity, LogisticData::parity
   char err[256];
   // kernel timing
   bool timing;
@@ -578,9 +579,7 @@ int drain_spans(adacgd_ctx* c) {
   return ADACGD_OK;
 }
 
-// A stream capture records launches that may be replayed in any number, so what the blocks of a launch meet at cannot
-// rely on the alternation of two sets: the captured launch is enclosed by fills of both.  (Nothing can be captured on the
-// null stream, and to ask about it would disturb a capture elsewhere.)
+// (Nothing can be captured on the null stream, and to ask about it would disturb a capture elsewhere.)
 bool capturing(hipStream_t st) {
   if (!st) return false;
   hipStreamCaptureStatus s = hipStreamCaptureStatusNone;
@@ -588,22 +587,16 @@ bool capturing(hipStream_t st) {
   return s == hipStreamCaptureStatusActive;
 }
 
+// A launch whose blocks may meet at `words` words of memory at `meet`, and at tickets (either null: they do not).
 template <typename F>
-hipError_t launch_meeting(hipStream_t st, uint32_t& parity, void* meet, size_t meet_words, uint32_t* ticket, F&& launch) {
-  const uint32_t p = parity;
-  const bool clear = meet && capturing(st);
-  auto fill = [&]() -> hipError_t {
-    hipError_t e = launch_fill_u32((uint32_t*)meet, 0u, meet_words, st);
+hipError_t launch_meeting(hipStream_t st, MeetingSets& sets, void* meet, size_t words, uint32_t* ticket, F&& launch) {
+  if (!meet) return launch(0u);
+  auto clear = [&]() -> hipError_t {
+    hipError_t e = launch_fill_u32((uint32_t*)meet, 0u, words, st);
     if (e == hipSuccess && ticket) e = launch_fill_u32(ticket, 0u, 2 * kCounterStride, st);
     return e;
   };
-  if (!clear) {
-    parity ^= 1u;
-    return launch(p);
-  }
-  hipError_t e = fill();
-  if (e == hipSuccess) e = launch(p);
-  return e == hipSuccess ? fill() : e;
+  return adacgd::launch_meeting(sets, capturing(st), clear, launch);
 }
 
 // One application of the AdaCGD compressor to every node of a set, on the stream c->cs.
@@ -616,7 +609,7 @@ int compress(adacgd_ctx* c, NodeSet& ns, PassArgs a, int slot0, hipEvent_t befor
     if (before_tally) HIPCHK(c, hipStreamWaitEvent(c->cs, before_tally, 0));
     const size_t words = 2 * (size_t)ns.nn * node_meet_words(ns.lv.pk, ns.lv.nq, ns.NB);
     return timed(c, slot0 + 1, [&] {
-      return launch_meeting(c->cs, slot0 == ADACGD_K_W_SAMPLE ? c->w_parity : c->m_parity, ns.meet, words, ns.ticket, [&](uint32_t p) {
+      return launch_meeting(c->cs, slot0 == ADACGD_K_W_SAMPLE ? c->w_meet : c->m_meet, ns.meet, words, ns.ticket, [&](uint32_t p) {
         a.parity = p;
         return launch_node(ns, a, c->cs);
       });
@@ -652,7 +645,7 @@ int compress(adacgd_ctx* c, NodeSet& ns, PassArgs a, int slot0, hipEvent_t befor
 hipError_t launch_one_gradient(adacgd_ctx* c, float* out, hipStream_t st) {
   LogisticData& ld = c->ld;
   const size_t words = 4 * (size_t)c->n * ld.row_chunks * ld.chunk_rows * ld.col_parts;
-  return launch_meeting(st, c->g_parity, ld.meet, words, ld.ticket, [&](uint32_t p) {
+  return launch_meeting(st, c->g_meet, ld.meet, words, ld.ticket, [&](uint32_t p) {
     ld.parity = p;
     return launch_grad(ld, c->x, out, (int)c->n, c->d, st);
   });

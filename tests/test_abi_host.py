@@ -3,6 +3,7 @@ symbol the header declares, and rejects bad configurations with the documented c
 import ctypes as C
 import os
 import re
+import subprocess
 
 import numpy as np
 import pytest
@@ -136,7 +137,6 @@ def test_header_is_plain_c_and_matches_the_binding(tmp_path):
     """The header compiles as C99 on its own, and the configuration struct has the size and field
     offsets the ctypes binding assumes."""
     import shutil
-    import subprocess
     if shutil.which("gcc") is None:
         pytest.skip("no C compiler")
     fields = [name for name, _ in E.Config._fields_]
@@ -167,3 +167,42 @@ def test_a_configuration_near_the_static_workspace_keeps_fitting_it():
     assert near == two_pass
     assert E.adacgd_workspace_bytes(_cfg(n=8, d=560000, **levels)[0]) > E.adacgd_workspace_bytes(
         _cfg(n=8, d=560000, **dict(levels, flags=E.FLAG_RETAIN_EXT | E.FLAG_TWO_PASS))[0])
+
+
+def test_what_blocks_meet_at_is_clear_whatever_launches_failed_before(tmp_path):
+    """The two sets of polled memory in a model of the device: a launch needs its set clear, leaves it used and clears the
+    other; a launch may fail (before it ran, or after), be captured, and captured launches be replayed."""
+    src = tmp_path / "meet.cpp"
+    src.write_text(r"""
+        #include "meeting.h"
+        #include <cstdio>
+        #include <cstdlib>
+        #include <vector>
+        using namespace adacgd;
+        int used[2] = {0, 0};
+        bool run(unsigned s) { if (used[s]) return false; used[s] = 1; used[s ^ 1] = 0; return true; }
+        int main() {
+          MeetingSets m;
+          std::vector<int> graph;          // -1: clear, else a launch with that set
+          srand(7);
+          for (int step = 0; step < 100000; ++step) {
+            const int what = rand() % 8;
+            bool good = true;
+            if (what == 0) {               // capture one or two launches
+              graph.clear();
+              for (int k = rand() % 2; k >= 0; --k)
+                launch_meeting(m, true, [&] { graph.push_back(-1); return 0; }, [&](unsigned s) { graph.push_back((int)s); return 0; });
+            } else if (what == 1) {        // replay
+              for (int g : graph) { if (g < 0) used[0] = used[1] = 0; else good = good && run((unsigned)g); }
+            } else {
+              const int fate = what < 4 ? what : 1;        // 2: fails before it ran, 3: after
+              launch_meeting(m, false, [&] { used[0] = used[1] = 0; return 0; },
+                             [&](unsigned s) { if (fate != 2) good = run(s); return fate == 1 ? 0 : 5; });
+            }
+            if (!good) { printf("step %d: a launch met what another had left\n", step); return 1; }
+          }
+          return 0;
+        }""")
+    exe = tmp_path / "meet"
+    subprocess.run(["g++", "-std=c++17", "-Wall", "-I", os.path.join(ROOT, "paper_2211_00188_amd", "csrc"), str(src), "-o", str(exe)], check=True)
+    subprocess.run([str(exe)], check=True)
