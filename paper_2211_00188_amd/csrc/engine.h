@@ -28,6 +28,7 @@ constexpr int kNodeResident = 512;      // its blocks resident at once: two per 
 // One-launch gradient (k_grad): up to kGradCols columns a block, up to kNodeParts such parts of a row.
 constexpr int kGradCols = 2048;
 constexpr int kGradRows = 16;           // rows a group of wavefronts holds at a time
+constexpr int kGradFold = 16;           // partial sums that one block adds up
 __host__ __device__ constexpr int grad_col_waves(int64_t cols) { return cols <= 256 ? 1 : cols <= 512 ? 2 : cols <= 1024 ? 4 : 8; }
 constexpr int kServeWorkers = 64;       // it also aggregates when there are at most this many workers of one chunk each
 constexpr int64_t kServeMax = 65536;    // ... and at most this many worker-coordinates (one block adds them up)
@@ -195,16 +196,21 @@ struct LogisticData {
   int64_t max_rows;        // largest shard
   double lambda;
   double* margins;         // [rows]  s_l = -y_l / (1 + exp(y_l a_l^T x)) / N_i
-  double* part;            // [n][row_chunks][d] when row_chunks > 1
-  uint32_t* col_done;      // [n][column blocks] arrival counters when row_chunks > 1; zero between launches
-  int row_chunks;
-  // One-launch gradient of dense features (k_grad): a shard's rows in row_chunks chunks of chunk_rows, its columns in
+  double* part;            // [n][row_chunks][d] when row_chunks > 1; k_grad: [part_slots][grad_slot_len]
+  uint32_t* col_done;      // [n][column blocks] arrival counters when row_chunks > 1; k_grad: [2][part_slots][col_parts];
+                           // zero between launches
+  int row_chunks;          // chunks of a shard's rows; k_grad: 0 = not the same number for all shards (`chunks` tells)
+  // One-launch gradient of dense features (k_grad): every shard's rows in chunks of chunk_rows, its columns in
   // col_parts parts of part_cols, one block each; col_parts = 0: the two-kernel form.
   int col_parts;
   int part_cols;
+  int row_groups;          // groups of wavefronts of a block that hold different rows
   int chunk_rows;          // a multiple of the rows a block holds at a time
+  int groups;              // row chunks of all shards together
+  int part_slots;          // ... of the shards that have more than one: they leave partial sums
+  const int4* chunks;      // [groups] {shard, chunk, chunks of the shard, partial sums of the shards before it}, row_chunks = 0
   uint32_t parity;         // which of the two sets of `meet` and `ticket` this launch uses (alternates)
-  double* meet;            // [2][n * row_chunks * chunk_rows][col_parts] partial products a_l^T x (col_parts > 1); zero at init
+  double* meet;            // [2][rows][col_parts] partial products a_l^T x (col_parts > 1); zero at init
   uint32_t* ticket;        // [2][kCounterStride] see NodeSet::ticket; null up to kNodeParts blocks
   // Sparse features (GRAD_LOGISTIC_CSR): device copies made at init.  The transposed copy holds
   // every worker's entries sorted by column, then by row, so that one thread sums a column of a
@@ -220,6 +226,9 @@ struct LogisticData {
   const int32_t* trow;     // [nnz] row (global) of each transposed entry
   const float* tval;       // [nnz]
 };
+
+// columns of a partial sum: every part's, in whole quads
+inline size_t grad_slot_len(const LogisticData& ld) { return (size_t)ld.col_parts * ((ld.part_cols + 3) / 4) * 4; }
 
 // launchers (each enqueues on the stream and returns the launch status)
 hipError_t launch_scan(const NodeSet& ns, const PassArgs& a, hipStream_t st);
@@ -249,7 +258,7 @@ hipError_t launch_aggregate(const NodeSet& ws, const float* gt_old, float* gt_ne
                             hipStream_t st);
 hipError_t launch_fill_u32(uint32_t* p, uint32_t v, size_t count, hipStream_t st);
 hipError_t launch_copy_f32(float* dst, const float* src, size_t count, hipStream_t st);
-hipError_t launch_grad(const LogisticData& ld, const float* x, float* grads, int n, int64_t d, hipStream_t st);
+hipError_t launch_grad(const LogisticData& ld, const float* x, float* grads, int64_t d, hipStream_t st);
 hipError_t launch_grad_margins(const LogisticData& ld, const float* x, int64_t d, hipStream_t st);
 hipError_t launch_grad_cols(const LogisticData& ld, const float* x, float* grads, int n, int64_t d, hipStream_t st);
 

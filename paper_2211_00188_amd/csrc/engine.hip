@@ -416,12 +416,18 @@ struct Layout {
   double* margins;
   double* part;
   uint32_t* col_done;
+  int4* chunks;
   int64_t *rp, *wbase;
   int32_t *ci, *trow;
   float *cv, *tval;
   uint32_t* cptr;
   size_t w_zero, m_zero;
 };
+
+// arrival counters of the gradient's row chunks
+size_t col_counters(const LogisticData& ld, int64_t n, int64_t d) {
+  return ld.col_parts ? 2 * (size_t)ld.part_slots * ld.col_parts : (size_t)n * ((d + 63) / 64);
+}
 
 size_t carve_all(char* base, const adacgd_config* cfg, NodeSet& W, NodeSet& M, LogisticData& ld, Layout& L) {
   Carver c{base};
@@ -453,13 +459,15 @@ size_t carve_all(char* base, const adacgd_config* cfg, NodeSet& W, NodeSet& M, L
     L.offsets = c.take<int64_t>(n + 1);
     L.row_node = c.take<int32_t>(rows);
     L.margins = ld.col_parts ? nullptr : c.take<double>(rows);
-    const size_t blocks = n * ld.row_chunks * ld.col_parts;
-    ld.meet = ld.col_parts > 1 ? c.take<double>(2 * blocks * ld.chunk_rows) : nullptr;
-    ld.ticket = ld.col_parts > 1 && blocks > kNodeParts ? c.take<uint32_t>(2 * kCounterStride) : nullptr;
-    L.part = ld.row_chunks > 1 ? c.take<double>(n * ld.row_chunks * d) : nullptr;
-    L.col_done = ld.row_chunks > 1 ? c.take<uint32_t>(n * ((d + 63) / 64)) : nullptr;
+    ld.meet = ld.col_parts > 1 ? c.take<double>(2 * rows * ld.col_parts) : nullptr;
+    ld.ticket = ld.col_parts > 1 && (size_t)ld.groups * ld.col_parts > kNodeParts ? c.take<uint32_t>(2 * kCounterStride) : nullptr;
+    L.chunks = ld.col_parts && !ld.row_chunks ? c.take<int4>(ld.groups) : nullptr;
+    const size_t sums = ld.col_parts ? ld.part_slots * grad_slot_len(ld) : ld.row_chunks > 1 ? n * ld.row_chunks * d : 0;
+    L.part = sums ? c.take<double>(sums) : nullptr;
+    L.col_done = sums ? c.take<uint32_t>(col_counters(ld, (int64_t)n, (int64_t)d)) : nullptr;
   } else {
     L.offsets = nullptr; L.row_node = nullptr; L.margins = nullptr; L.part = nullptr; L.col_done = nullptr;
+    L.chunks = nullptr;
   }
   if (ld.csr) {
     const size_t rows = cfg->shard_offsets[n], nnz = (size_t)ld.nnz;
@@ -491,20 +499,48 @@ void shape_logistic(const adacgd_config* cfg, LogisticData& ld) {
   for (int64_t i = 0; i < cfg->n; ++i) mx = std::max<int64_t>(mx, cfg->shard_offsets[i + 1] - cfg->shard_offsets[i]);
   ld.max_rows = mx;
   if (cfg->d <= (int64_t)kGradCols * kNodeParts) {
-    // Features read once (k_grad).  Row chunks as far as that keeps the launch within one round of blocks.
+    // Features read once (k_grad).  As many groups of wavefronts a block as the longest shard has rows for; chunks as short
+    // as one round of wavefronts allows, of the same length for all shards, so that a long shard among short ones is
+    // spread over the device.
     const int64_t n = cfg->n, d = cfg->d;
     int64_t parts = (d + kGradCols - 1) / kGradCols;
     ld.part_cols = (int)(parts == 1 ? d : ((d + parts - 1) / parts + 15) / 16 * 16);
     parts = (d + ld.part_cols - 1) / ld.part_cols;
-    const int64_t held = kGradRows * (8 / grad_col_waves(ld.part_cols));      // rows a block holds at a time
-    const int64_t iters = (mx + held - 1) / held;
-    int64_t chunks = std::min(iters, std::max<int64_t>(1, kNodeResident / (n * parts)));
-    const int64_t per = (iters + chunks - 1) / chunks;
-    chunks = (iters + per - 1) / per;
-    if (n * chunks * parts < (int64_t(1) << 31) && chunks * per * held < (int64_t(1) << 31) && ld.rows < (int64_t(1) << 31)) {
+    const int waves = grad_col_waves(ld.part_cols);
+    ld.row_groups = 1;
+    while (ld.row_groups * waves < 8 && ld.row_groups * kGradRows < mx) ld.row_groups *= 2;
+    const int64_t held = kGradRows * ld.row_groups;                      // rows a block holds at a time
+    auto parted = [&](int64_t l) {                                       // chunks of l times that, of all shards together
+      int64_t c = 0;
+      for (int64_t i = 0; i < n; ++i) c += (cfg->shard_offsets[i + 1] - cfg->shard_offsets[i] + l * held - 1) / (l * held);
+      return c;
+    };
+    const int64_t round = (int64_t)kNodeResident * 8 / (waves * ld.row_groups);     // blocks resident at once
+    const int64_t all = parted(1), longest = (mx + held - 1) / held;
+    int64_t per = (all * parts + round - 1) / round;
+    if (longest * n <= 2 * all) {
+      // Shards of similar length: their remainders must not make a second round (400 x 500 rows x 300 columns in 800 blocks
+      // 66 us, in 400 43 us); more shards than that stay whole.
+      if (n * parts > round) per = std::max(per, longest);
+      for (int64_t lo = per, hi = std::max(per, longest); lo < hi;) {
+        const int64_t mid = (lo + hi) / 2;
+        if (parted(mid) * parts > round) lo = mid + 1;
+        else hi = mid;
+        per = hi;
+      }
+    }
+    if (per * held < (int64_t(1) << 31) && ld.rows < (int64_t(1) << 31)) {
       ld.col_parts = (int)parts;
-      ld.row_chunks = (int)chunks;
       ld.chunk_rows = (int)(per * held);
+      ld.groups = (int)parted(per);
+      ld.row_chunks = (int)((cfg->shard_offsets[1] + ld.chunk_rows - 1) / ld.chunk_rows);
+      int64_t slots = 0;
+      for (int64_t i = 0; i < n; ++i) {
+        const int64_t c = (cfg->shard_offsets[i + 1] - cfg->shard_offsets[i] + ld.chunk_rows - 1) / ld.chunk_rows;
+        if (c > 1) slots += c;
+        if (c != ld.row_chunks) ld.row_chunks = 0;
+      }
+      ld.part_slots = (int)slots;
       return;
     }
   }
@@ -644,10 +680,9 @@ int compress(adacgd_ctx* c, NodeSet& ns, PassArgs a, int slot0, hipEvent_t befor
 
 hipError_t launch_one_gradient(adacgd_ctx* c, float* out, hipStream_t st) {
   LogisticData& ld = c->ld;
-  const size_t words = 4 * (size_t)c->n * ld.row_chunks * ld.chunk_rows * ld.col_parts;
-  return launch_meeting(st, c->g_meet, ld.meet, words, ld.ticket, [&](uint32_t p) {
+  return launch_meeting(st, c->g_meet, ld.meet, 4 * (size_t)ld.rows * ld.col_parts, ld.ticket, [&](uint32_t p) {
     ld.parity = p;
-    return launch_grad(ld, c->x, out, (int)c->n, c->d, st);
+    return launch_grad(ld, c->x, out, c->d, st);
   });
 }
 
@@ -938,6 +973,7 @@ static int init_impl(const adacgd_config* cfg, adacgd_ctx** out, int static_dev)
   c->yb[0] = L.yb0; c->yb[1] = L.yb1;
   c->ld.A = cfg->A; c->ld.labels = cfg->labels; c->ld.offsets = L.offsets; c->ld.row_node = L.row_node;
   c->ld.margins = L.margins; c->ld.part = L.part; c->ld.col_done = L.col_done;
+  c->ld.chunks = L.chunks;
   if (c->ld.csr) {
     c->ld.rp = L.rp; c->ld.wbase = L.wbase; c->ld.cptr = L.cptr; c->ld.ci = L.ci; c->ld.trow = L.trow;
     c->ld.cv = L.cv; c->ld.tval = L.tval;
@@ -997,7 +1033,7 @@ static int init_impl(const adacgd_config* cfg, adacgd_ctx** out, int static_dev)
     wbase[(size_t)c->n] = rp[rows];
     INITCHK(hipMemcpy(L.wbase, wbase.data(), wbase.size() * sizeof(int64_t), hipMemcpyHostToDevice));
   }
-  if (L.col_done) INITCHK(launch_fill_u32(L.col_done, 0u, (size_t)c->n * (size_t)((c->d + 63) / 64), c->st));
+  if (L.col_done) INITCHK(launch_fill_u32(L.col_done, 0u, col_counters(c->ld, c->n, c->d), c->st));
   if (logistic_mode(cfg->grad_mode)) {
     std::vector<int32_t> rn((size_t)c->ld.rows);
     for (int64_t i = 0; i < c->n; ++i)
@@ -1005,9 +1041,19 @@ static int init_impl(const adacgd_config* cfg, adacgd_ctx** out, int static_dev)
     INITCHK(hipMemcpyAsync(L.offsets, cfg->shard_offsets, (size_t)(c->n + 1) * sizeof(int64_t), hipMemcpyHostToDevice,
                            c->st));
     INITCHK(hipMemcpyAsync(L.row_node, rn.data(), rn.size() * sizeof(int32_t), hipMemcpyHostToDevice, c->st));
-    INITCHK(hipStreamSynchronize(c->st));   // rn goes out of scope
+    std::vector<int4> chunks;
+    if (L.chunks) {
+      int slot = 0;
+      for (int64_t i = 0; i < c->n; ++i) {
+        const int k = (int)((cfg->shard_offsets[i + 1] - cfg->shard_offsets[i] + c->ld.chunk_rows - 1) / c->ld.chunk_rows);
+        for (int j = 0; j < k; ++j) chunks.push_back(make_int4((int)i, j, k, slot));
+        if (k > 1) slot += k;
+      }
+      INITCHK(hipMemcpyAsync(L.chunks, chunks.data(), chunks.size() * sizeof(int4), hipMemcpyHostToDevice, c->st));
+    }
+    INITCHK(hipStreamSynchronize(c->st));   // rn and chunks go out of scope
     if (c->ld.col_parts > 0) {
-      if (c->ld.meet) INITCHK(launch_fill_u32((uint32_t*)c->ld.meet, 0u, 4 * (size_t)c->n * c->ld.row_chunks * c->ld.chunk_rows * c->ld.col_parts, c->st));
+      if (c->ld.meet) INITCHK(launch_fill_u32((uint32_t*)c->ld.meet, 0u, 4 * (size_t)c->ld.rows * c->ld.col_parts, c->st));
       if (c->ld.ticket) INITCHK(launch_fill_u32(c->ld.ticket, 0u, 2 * kCounterStride, c->st));
       INITCHK(launch_one_gradient(c, c->yb[0], c->st));
     } else {

@@ -9,7 +9,7 @@ namespace adacgd {
 // The same gradient with the features read once (dense features, d <= kGradCols * kNodeParts).
 // A block keeps kGradRows rows at a time of its columns in registers: forms their products with x, turns the
 // complete products into the weights s_l, and adds s_l a_l to its column sums before it lets go of them.
-// CW wavefronts of 256 columns share a row, 8 / CW groups of them hold different rows.  Rows longer than a block's
+// CW wavefronts of 256 columns share a row, RG groups of them hold different rows.  Rows longer than a block's
 // columns are spread over col_parts blocks that leave each other their partial products; those are polled
 // themselves: a slot holds zero until its value (a zero is stored as -0) is there, and a launch clears the set that
 // the previous one used.  Waiting: blocks take their place by ticket and wait only for the col_parts <= kNodeParts
@@ -17,7 +17,8 @@ namespace adacgd {
 // Bound by the read of the features where that is long; two blocks a compute unit (16 rows x 4 columns a lane are half
 // the registers), so that one reads while the other meets.  Measured against the two kernels that read the features
 // twice: 1000 workers x 32 rows x 65536 columns 2.00 ms a gradient (2.90), 20 x 2500 x 300 19 us (29), 10 x 203 x 5003
-// 28 us (37), 4 x 64 x 100 4.6 us (7.9).
+// 28 us (37), 4 x 64 x 100 4.6 us (7.9).  Blocks have no more groups of wavefronts than a shard has rows for: with eight,
+// 2000 x 8 x 300 took 24 us (18 with two kernels), now 10 us.
 // ---------------------------------------------------------------------------
 
 // Lane by lane: a + (a of the partner lane) where the lane's bit O is clear, b + (b of the partner lane) where it is
@@ -35,11 +36,11 @@ __device__ __forceinline__ double halves_sum(double a, double b) {
   }
 }
 
-template <int CW>
-__global__ __launch_bounds__(512, 4) void k_grad(LogisticData ld, const float* __restrict__ x, float* __restrict__ grads, int64_t d) {
-  constexpr int RG = 8 / CW, R = kGradRows;
+template <int CW, int RG>
+__global__ __launch_bounds__(64 * CW * RG, 4) void k_grad(LogisticData ld, const float* __restrict__ x, float* __restrict__ grads, int64_t d) {
+  constexpr int R = kGradRows, NT = 64 * CW * RG;
   constexpr bool MULTI = CW == 8;
-  __shared__ double red[8][R], s_m[RG][R];
+  __shared__ double red[CW * RG][R], s_m[RG][R];
   __shared__ double s_acc[RG > 1 ? RG : 1][RG > 1 ? CW * 256 : 1];
   __shared__ uint32_t s_blk;
   __shared__ int s_flag;
@@ -58,7 +59,20 @@ __global__ __launch_bounds__(512, 4) void k_grad(LogisticData ld, const float* _
   auto scalar = [](uint32_t v) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)v); };
   blk = scalar(blk);
   const uint32_t group = scalar(blk / P), part = blk - group * P;
-  const int node = (int)scalar(group / (uint32_t)ld.row_chunks), rc = (int)group - node * ld.row_chunks;
+  // shard, chunk of its rows, number of its chunks, where their partial sums begin
+  int node, rc, nchunks, slot0;
+  if (ld.row_chunks) {
+    nchunks = ld.row_chunks;
+    node = (int)scalar(group / (uint32_t)nchunks);
+    rc = (int)group - node * nchunks;
+    slot0 = node * nchunks;
+  } else {
+    const int4 t = ld.chunks[group];
+    node = (int)scalar((uint32_t)t.x);
+    rc = (int)scalar((uint32_t)t.y);
+    nchunks = (int)scalar((uint32_t)t.z);
+    slot0 = (int)scalar((uint32_t)t.w);
+  }
   const uint32_t c0 = part * (uint32_t)ld.part_cols;
   const uint32_t len = min((uint32_t)ld.part_cols, (uint32_t)d - c0);
   // (a row number fits 31 bits: the host's choice of this kernel)
@@ -68,11 +82,11 @@ __global__ __launch_bounds__(512, 4) void k_grad(LogisticData ld, const float* _
   const uint32_t r_begin = r_first + (uint32_t)skip;
   const double N = (double)count;
   const uint32_t off = (uint32_t)(cw * 64 + (int)lane) * 16u;       // byte offset of this lane's four columns
-  const size_t set = (size_t)(gridDim.x / P) * ld.chunk_rows * P;
-  double* __restrict__ slots = MULTI && P > 1 ? ld.meet + ld.parity * set + (size_t)group * ld.chunk_rows * P : nullptr;
+  const size_t set = (size_t)ld.rows * P;
+  double* __restrict__ slots = MULTI && P > 1 ? ld.meet + ld.parity * set + (size_t)r_begin * P : nullptr;
   if (MULTI && P > 1) {       // the set the previous launch used, cleared for the next one
-    double* __restrict__ old = ld.meet + (ld.parity ^ 1) * set + (size_t)group * ld.chunk_rows * P;
-    for (int i = tid; i < rows; i += 512) old[(size_t)i * P + part] = 0.0;
+    double* __restrict__ old = ld.meet + (ld.parity ^ 1) * set + (size_t)r_begin * P;
+    for (int i = tid; i < rows; i += NT) old[(size_t)i * P + part] = 0.0;
   }
   float xq[4];
   buf_load4(make_buf(x + c0, 4 * len), off, 0, xq);
@@ -175,30 +189,48 @@ __global__ __launch_bounds__(512, 4) void k_grad(LogisticData ld, const float* _
     }
   }
   const uint32_t l0 = off / 4;
-  if (ld.row_chunks > 1) {
-    // several blocks share the shard's rows: each leaves its sums, the last to arrive adds them in chunk order
-    const size_t cp = (size_t)node * ld.row_chunks * (size_t)d + (size_t)c0 + l0;
-    if (rg == 0) {
+  if (nchunks > 1) {
+    // Several blocks share the shard's rows: each leaves its sums, and the last to arrive adds them in chunk order --
+    // kGradFold of them; of more chunks, the last of every kGradFold leaves their sum, and the last of those adds these
+    // (one block adding all of them took 140 us for 1 x 4000 rows x 2048 columns, 250 chunks).
+    // (columns l, l + 4, l + 8, ... of a part lie side by side, so that a wavefront's accesses do)
+    const uint32_t quads = ((uint32_t)ld.part_cols + 3) / 4;
+    const size_t slot_len = (size_t)P * quads * 4;
+    double* __restrict__ sums = ld.part + (size_t)part * quads * 4 + off / 16;
+    auto leave = [&](int slot) {
+      if (rg == 0) {
 #pragma unroll
-      for (int c = 0; c < 4; ++c)
-        if (l0 + c < len) st_coherent(&ld.part[cp + (size_t)rc * (size_t)d + c], acc[c]);
-    }
-    if (!arrive_last_few(&ld.col_done[(size_t)node * P + part], (uint32_t)ld.row_chunks, &s_flag)) return;
-#pragma unroll
-    for (int c = 0; c < 4; ++c) acc[c] = 0.0;
-    if (rg == 0) {
-      for (int r0 = 0; r0 < ld.row_chunks; r0 += 8) {        // eight chunks' loads in flight, added in chunk order
-        double v[8][4];
-#pragma unroll
-        for (int u = 0; u < 8; ++u)
-#pragma unroll
-          for (int c = 0; c < 4; ++c)
-            v[u][c] = r0 + u < ld.row_chunks && l0 + c < len ? ld_coherent(&ld.part[cp + (size_t)(r0 + u) * (size_t)d + c]) : 0.0;
-#pragma unroll
-        for (int u = 0; u < 8; ++u)
-#pragma unroll
-          for (int c = 0; c < 4; ++c) acc[c] += v[u][c];
+        for (int c = 0; c < 4; ++c)
+          if (l0 + c < len) st_coherent(&sums[(size_t)slot * slot_len + c * quads], acc[c]);
       }
+    };
+    auto add = [&](int slot, int count, int stride) {
+#pragma unroll
+      for (int c = 0; c < 4; ++c) acc[c] = 0.0;
+      if (rg == 0) {
+        for (int r0 = 0; r0 < count; r0 += 8) {        // eight loads of a column in flight
+          double v[8][4];
+#pragma unroll
+          for (int u = 0; u < 8; ++u)
+#pragma unroll
+            for (int c = 0; c < 4; ++c)
+              v[u][c] = r0 + u < count && l0 + c < len ? ld_coherent(&sums[(size_t)(slot + (r0 + u) * stride) * slot_len + c * quads]) : 0.0;
+#pragma unroll
+          for (int u = 0; u < 8; ++u)
+#pragma unroll
+            for (int c = 0; c < 4; ++c) acc[c] += v[u][c];
+        }
+      }
+    };
+    leave(slot0 + rc);
+    const int sub = rc - rc % kGradFold, members = min(kGradFold, nchunks - sub);
+    if (!arrive_last_few(&ld.col_done[(size_t)(slot0 + sub) * P + part], (uint32_t)members, &s_flag)) return;
+    add(slot0 + sub, members, 1);
+    if (nchunks > kGradFold) {
+      leave(slot0 + sub);
+      const int subs = (nchunks + kGradFold - 1) / kGradFold;
+      if (!arrive_last_few(&ld.col_done[(size_t)(ld.part_slots + slot0) * P + part], (uint32_t)subs, &s_flag)) return;
+      add(slot0, subs, kGradFold);
     }
   }
   if (rg != 0) return;
@@ -208,16 +240,20 @@ __global__ __launch_bounds__(512, 4) void k_grad(LogisticData ld, const float* _
   buf_store4(make_buf(grads + (size_t)node * (size_t)d + c0, 4 * len), off, 0, g);
 }
 
-hipError_t launch_grad(const LogisticData& ld, const float* x, float* grads, int n, int64_t d, hipStream_t st) {
+hipError_t launch_grad(const LogisticData& ld, const float* x, float* grads, int64_t d, hipStream_t st) {
   (void)hipGetLastError();   // drop a stale error left by earlier runtime calls of this thread
-  const dim3 grid((unsigned)((size_t)n * ld.row_chunks * ld.col_parts));
+  const dim3 grid((unsigned)((size_t)ld.groups * ld.col_parts));
+  auto go = [&](auto kern, int waves) -> hipError_t {
+    hipLaunchKernelGGL(kern, grid, dim3(64 * waves), 0, st, ld, x, grads, d);
+    return hipGetLastError();
+  };
+  const int rg = ld.row_groups;
   switch (grad_col_waves(ld.part_cols)) {
-    case 1: hipLaunchKernelGGL((k_grad<1>), grid, dim3(512), 0, st, ld, x, grads, d); break;
-    case 2: hipLaunchKernelGGL((k_grad<2>), grid, dim3(512), 0, st, ld, x, grads, d); break;
-    case 4: hipLaunchKernelGGL((k_grad<4>), grid, dim3(512), 0, st, ld, x, grads, d); break;
-    default: hipLaunchKernelGGL((k_grad<8>), grid, dim3(512), 0, st, ld, x, grads, d); break;
+    case 1: return rg == 1 ? go(k_grad<1, 1>, 1) : rg == 2 ? go(k_grad<1, 2>, 2) : rg == 4 ? go(k_grad<1, 4>, 4) : go(k_grad<1, 8>, 8);
+    case 2: return rg == 1 ? go(k_grad<2, 1>, 2) : rg == 2 ? go(k_grad<2, 2>, 4) : go(k_grad<2, 4>, 8);
+    case 4: return rg == 1 ? go(k_grad<4, 1>, 4) : go(k_grad<4, 2>, 8);
+    default: return go(k_grad<8, 1>, 8);
   }
-  return hipGetLastError();
 }
 
 }  // namespace adacgd

@@ -206,3 +206,17 @@ def test_what_blocks_meet_at_is_clear_whatever_launches_failed_before(tmp_path):
     exe = tmp_path / "meet"
     subprocess.run(["g++", "-std=c++17", "-Wall", "-I", os.path.join(ROOT, "paper_2211_00188_amd", "csrc"), str(src), "-o", str(exe)], check=True)
     subprocess.run([str(exe)], check=True)
+
+
+@pytest.mark.parametrize("n,d,rows,short", [(100, 2049, 200000, 50), (1000, 65536, 20000, 4), (20, 100, 1000000, 100), (35, 2176, 1700, 1650),
+                                            (1, 1699, 5336, 0), (1, 16384, 500000, 0)])
+def test_workspace_of_the_gradient_grows_with_the_rows_and_not_with_the_longest_shard(n, d, rows, short):
+    """What the gradient needs on top of vectors and level sets (those of a run with one row a shard): tables of the rows,
+    two sets of their partial products, and partial sums of at most two rounds of blocks."""
+    need = lambda cnt: E.adacgd_workspace_bytes(_cfg(n=n, d=d, grad_mode=E.GRAD_LOGISTIC,
+                                                     shard_offsets=np.concatenate([[0], np.cumsum(cnt)]).astype(np.int64))[0])
+    cnt = np.full(n, short)
+    cnt[n // 2] = rows
+    parts = (d + 2047) // 2048
+    bound = int(cnt.sum()) * (4 + 16 * parts) + 2 * 4096 * 2048 * 8 // 8 + 16 * (n + 1024) + (1 << 16)
+    assert need(cnt) - need(np.ones(n)) <= bound, (need(cnt), need(np.ones(n)), bound)

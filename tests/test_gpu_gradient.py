@@ -14,10 +14,26 @@ SHAPES = [(3, 1, 5), (2, 20, 300), (4, 256, 128), (3, 257, 129), (2, 511, 65), (
 
 @pytest.mark.parametrize("n,d,rows", SHAPES)
 def test_gradient_at_the_edges_of_its_layout(n, d, rows):
-    E = _eng()
     rng = np.random.default_rng(d * 7 + rows)
     cnt = rows - rng.integers(0, max(1, rows // 2), size=n)
     cnt[0] = rows
+    check_gradient(n, d, rows, cnt, rng)
+
+
+# one shard of `rows` rows among shards of `short`: chunks by a table; chunk counts around what one block adds up; blocks with
+# one group of wavefronts
+@pytest.mark.parametrize("n,d,rows,short", [(40, 300, 9000, 3), (100, 2049, 3000, 5), (3, 65536, 300, 1), (5, 16384, 700, 40), (300, 17, 5000, 8),
+                                            (1, 2048, 4000, 0), (1, 2048, 256, 0), (1, 2048, 257, 0), (1, 2048, 272, 0), (1, 2048, 273, 0),
+                                            (2, 3, 40000, 39999), (1500, 30, 8, 8), (1100, 700, 17, 1), (1, 5003, 2000, 0)])
+def test_gradient_of_a_long_shard_among_short_ones(n, d, rows, short):
+    rng = np.random.default_rng(d * 11 + rows)
+    cnt = np.full(n, short)
+    cnt[n // 2] = rows
+    check_gradient(n, d, rows, cnt, rng)
+
+
+def check_gradient(n, d, rows, cnt, rng):
+    E = _eng()
     off = np.concatenate([[0], np.cumsum(cnt)]).astype(np.int64)
     A = rng.standard_normal((int(off[-1]), d), dtype=np.float32)
     y = np.where(rng.random(int(off[-1])) < 0.5, 1.0, -1.0).astype(np.float32)
