@@ -129,12 +129,16 @@ enum adacgd_flags {
   ADACGD_FLAG_TWO_PASS = 8,        /* always use the general two-pass kernels: neither the sampled one-pass
                                       selection of long vectors nor the one-launch kernel of shorter ones
                                       (same results, slower)                                            */
-  ADACGD_FLAG_OVERLAP = 16         /* GRAD_EXTERNAL / DIFF_EXTERNAL: run the worker compression on a stream
+  ADACGD_FLAG_OVERLAP = 16,        /* GRAD_EXTERNAL / DIFF_EXTERNAL: run the worker compression on a stream
                                       of the library's own, concurrently with the previous step's
                                       aggregation and master compression on the caller's stream (same
                                       results).  The arrays passed to adacgd_step must then be complete
                                       when the call is made, not merely enqueued on the caller's stream;
                                       the caller's stream still orders after everything a step enqueues */
+  ADACGD_FLAG_NO_WAIT = 32         /* blocks that share a vector in one launch do not wait for each other to begin: the
+                                      last of them does the work alone, as it otherwise does only where the others
+                                      have not begun for some 30 ms because the device is full (same results,
+                                      much slower; for tests)                                             */
 };
 
 typedef struct {

@@ -119,6 +119,23 @@ __device__ __forceinline__ void st_coherent(T* p, T v) {
   __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+// A group of blocks that meet: every block adds one to the group's word as it begins.  Nobody waits for the group until the word
+// says that all `count` blocks have begun, or that the group is given up: where it is `late`, the word is marked unless it
+// is complete by then, and a mark is final, as completeness is -- all blocks of the group learn the same.  A complete group
+// is running, so that its blocks may wait for each other from then on.  Called by whole wavefronts; returns the word.
+constexpr uint32_t kGivenUp = 1u << 31;
+__device__ __forceinline__ uint32_t poll_begun(uint32_t* word, uint32_t count, bool late) {
+  uint32_t v = ld_coherent(word);
+  if (late && v < count) {
+    if (lane_id() == 0) {
+      uint32_t there = v;
+      if (__hip_atomic_compare_exchange_strong(word, &there, v | kGivenUp, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) there |= kGivenUp;
+      v = there;
+    }
+  }
+  return (uint32_t)__builtin_amdgcn_readfirstlane((int)v);
+}
+
 // Every block of a node calls this once after its last coherent write.  Returns true in
 // all threads of exactly one block per node: the one that arrived last.  That block may
 // then read what the others wrote (with ld_coherent) and finish the node's work; the

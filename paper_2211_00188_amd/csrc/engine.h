@@ -24,7 +24,8 @@ constexpr int kMaxLevels = 16;
 // at most kNodeParts of them.
 constexpr int kNodeChunk = 16384;
 constexpr int kNodeParts = 64;
-constexpr int kNodeResident = 512;      // its blocks resident at once: two per compute unit
+constexpr int kNodeResident = 512;      // its blocks resident at once: two per compute unit (layouts follow it, nothing depends on it)
+constexpr uint32_t kPolls = 1u << 15;   // a block waits that many polls (of about 1 us) for others to begin, then does without them
 // One-launch gradient (k_grad): up to kGradCols columns a block, up to kNodeParts such parts of a row.
 constexpr int kGradCols = 2048;
 constexpr int kGradRows = 16;           // rows a group of wavefronts holds at a time
@@ -212,6 +213,9 @@ struct LogisticData {
   uint32_t parity;         // which of the two sets of `meet` and `ticket` this launch uses (alternates)
   double* meet;            // [2][rows][col_parts] partial products a_l^T x (col_parts > 1); zero at init
   uint32_t* ticket;        // [2][kCounterStride] see NodeSet::ticket; null up to kNodeParts blocks
+  uint32_t* begun;         // [2][groups][kCounterStride] blocks of the chunk that have begun, see poll_begun (behind `meet`)
+  uint32_t* alone;         // [groups] blocks that have left a chunk that was given up (col_parts > 1); zero between launches
+  uint32_t polls;          // polls before a chunk is given up
   // Sparse features (GRAD_LOGISTIC_CSR): device copies made at init.  The transposed copy holds
   // every worker's entries sorted by column, then by row, so that one thread sums a column of a
   // shard in a fixed order.
@@ -229,6 +233,9 @@ struct LogisticData {
 
 // columns of a partial sum: every part's, in whole quads
 inline size_t grad_slot_len(const LogisticData& ld) { return (size_t)ld.col_parts * ((ld.part_cols + 3) / 4) * 4; }
+
+// words of memory at LogisticData::meet
+inline size_t grad_meet_words(const LogisticData& ld) { return 4 * (size_t)ld.rows * ld.col_parts + 2 * (size_t)ld.groups * kCounterStride; }
 
 // launchers (each enqueues on the stream and returns the launch status)
 hipError_t launch_scan(const NodeSet& ns, const PassArgs& a, hipStream_t st);

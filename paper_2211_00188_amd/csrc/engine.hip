@@ -459,8 +459,10 @@ size_t carve_all(char* base, const adacgd_config* cfg, NodeSet& W, NodeSet& M, L
     L.offsets = c.take<int64_t>(n + 1);
     L.row_node = c.take<int32_t>(rows);
     L.margins = ld.col_parts ? nullptr : c.take<double>(rows);
-    ld.meet = ld.col_parts > 1 ? c.take<double>(2 * rows * ld.col_parts) : nullptr;
+    ld.meet = ld.col_parts > 1 ? c.take<double>((grad_meet_words(ld) + 1) / 2) : nullptr;
+    ld.begun = ld.meet ? reinterpret_cast<uint32_t*>(ld.meet + 2 * rows * ld.col_parts) : nullptr;
     ld.ticket = ld.col_parts > 1 && (size_t)ld.groups * ld.col_parts > kNodeParts ? c.take<uint32_t>(2 * kCounterStride) : nullptr;
+    ld.alone = ld.col_parts > 1 ? c.take<uint32_t>(ld.groups) : nullptr;
     L.chunks = ld.col_parts && !ld.row_chunks ? c.take<int4>(ld.groups) : nullptr;
     const size_t sums = ld.col_parts ? ld.part_slots * grad_slot_len(ld) : ld.row_chunks > 1 ? n * ld.row_chunks * d : 0;
     L.part = sums ? c.take<double>(sums) : nullptr;
@@ -496,6 +498,7 @@ void shape_logistic(const adacgd_config* cfg, LogisticData& ld) {
   }
   int64_t mx = 0;
   ld.lambda = (double)cfg->lambda;
+  ld.polls = cfg->flags & ADACGD_FLAG_NO_WAIT ? 0u : kPolls;
   for (int64_t i = 0; i < cfg->n; ++i) mx = std::max<int64_t>(mx, cfg->shard_offsets[i + 1] - cfg->shard_offsets[i]);
   ld.max_rows = mx;
   if (cfg->d <= (int64_t)kGradCols * kNodeParts) {
@@ -680,7 +683,7 @@ int compress(adacgd_ctx* c, NodeSet& ns, PassArgs a, int slot0, hipEvent_t befor
 
 hipError_t launch_one_gradient(adacgd_ctx* c, float* out, hipStream_t st) {
   LogisticData& ld = c->ld;
-  return launch_meeting(st, c->g_meet, ld.meet, 4 * (size_t)ld.rows * ld.col_parts, ld.ticket, [&](uint32_t p) {
+  return launch_meeting(st, c->g_meet, ld.meet, grad_meet_words(ld), ld.ticket, [&](uint32_t p) {
     ld.parity = p;
     return launch_grad(ld, c->x, out, c->d, st);
   });
@@ -1053,7 +1056,8 @@ static int init_impl(const adacgd_config* cfg, adacgd_ctx** out, int static_dev)
     }
     INITCHK(hipStreamSynchronize(c->st));   // rn and chunks go out of scope
     if (c->ld.col_parts > 0) {
-      if (c->ld.meet) INITCHK(launch_fill_u32((uint32_t*)c->ld.meet, 0u, 4 * (size_t)c->ld.rows * c->ld.col_parts, c->st));
+      if (c->ld.meet) INITCHK(launch_fill_u32((uint32_t*)c->ld.meet, 0u, grad_meet_words(c->ld), c->st));
+      if (c->ld.alone) INITCHK(launch_fill_u32(c->ld.alone, 0u, (size_t)c->ld.groups, c->st));
       if (c->ld.ticket) INITCHK(launch_fill_u32(c->ld.ticket, 0u, 2 * kCounterStride, c->st));
       INITCHK(launch_one_gradient(c, c->yb[0], c->st));
     } else {

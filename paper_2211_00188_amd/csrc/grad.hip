@@ -12,8 +12,11 @@ namespace adacgd {
 // CW wavefronts of 256 columns share a row, RG groups of them hold different rows.  Rows longer than a block's
 // columns are spread over col_parts blocks that leave each other their partial products; those are polled
 // themselves: a slot holds zero until its value (a zero is stored as -0) is there, and a launch clears the set that
-// the previous one used.  Waiting: blocks take their place by ticket and wait only for the col_parts <= kNodeParts
-// blocks of their own row chunk, as those of the one-launch compression step do (node.hip).
+// the previous one used.
+// Waiting.  Blocks take their place by ticket and wait only for the col_parts <= kNodeParts blocks of their own row chunk.
+// Those need not be running all at once (other launches may have filled the device): a block counts itself as it begins,
+// and where the count is not complete after some time the chunk is given up, its blocks leave, and the last of them to
+// come forms its sums alone.
 // Bound by the read of the features where that is long; two blocks a compute unit (16 rows x 4 columns a lane are half
 // the registers), so that one reads while the other meets.  Measured against the two kernels that read the features
 // twice: 1000 workers x 32 rows x 65536 columns 2.00 ms a gradient (2.90), 20 x 2500 x 300 19 us (29), 10 x 203 x 5003
@@ -36,19 +39,108 @@ __device__ __forceinline__ double halves_sum(double a, double b) {
   }
 }
 
-template <int CW, int RG>
+__device__ __forceinline__ double grad_weight(double yl, double z, double N) { return -yl / (1.0 + exp(yl * z)) / N; }
+
+// What a block does with its column sums (four a lane, in the wavefronts that `hold` them): the gradient, or with several
+// chunks a shard -- each leaves its sums, and the last to arrive adds them in chunk order: kGradFold of them; of more
+// chunks, the last of every kGradFold leaves their sum, and the last of those adds these (one block adding all of them
+// took 140 us for 1 x 4000 rows x 2048 columns, 250 chunks).
+__device__ __forceinline__ void finish(const LogisticData& ld, float* __restrict__ grads, int64_t d, int node, int rc, int nchunks, int slot0,
+                                       uint32_t P, uint32_t part, uint32_t len, uint32_t off, bool hold, const float (&xq)[4], double (&acc)[4],
+                                       int* flag) {
+  const uint32_t l0 = off / 4;
+  if (nchunks > 1) {
+    // (columns l, l + 4, l + 8, ... of a part lie side by side, so that a wavefront's accesses do)
+    const uint32_t quads = ((uint32_t)ld.part_cols + 3) / 4;
+    const size_t slot_len = (size_t)P * quads * 4;
+    double* __restrict__ sums = ld.part + (size_t)part * quads * 4 + off / 16;
+    auto leave = [&](int slot) {
+      if (hold) {
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
+          if (l0 + c < len) st_coherent(&sums[(size_t)slot * slot_len + c * quads], acc[c]);
+      }
+    };
+    auto add = [&](int slot, int count, int stride) {
+#pragma unroll
+      for (int c = 0; c < 4; ++c) acc[c] = 0.0;
+      if (hold) {
+        for (int r0 = 0; r0 < count; r0 += 8) {        // eight loads of a column in flight
+          double v[8][4];
+#pragma unroll
+          for (int u = 0; u < 8; ++u)
+#pragma unroll
+            for (int c = 0; c < 4; ++c)
+              v[u][c] = r0 + u < count && l0 + c < len ? ld_coherent(&sums[(size_t)(slot + (r0 + u) * stride) * slot_len + c * quads]) : 0.0;
+#pragma unroll
+          for (int u = 0; u < 8; ++u)
+#pragma unroll
+            for (int c = 0; c < 4; ++c) acc[c] += v[u][c];
+        }
+      }
+    };
+    leave(slot0 + rc);
+    const int sub = rc - rc % kGradFold, members = min(kGradFold, nchunks - sub);
+    if (!arrive_last_few(&ld.col_done[(size_t)(slot0 + sub) * P + part], (uint32_t)members, flag)) return;
+    add(slot0 + sub, members, 1);
+    if (nchunks > kGradFold) {
+      leave(slot0 + sub);
+      const int subs = (nchunks + kGradFold - 1) / kGradFold;
+      if (!arrive_last_few(&ld.col_done[(size_t)(ld.part_slots + slot0) * P + part], (uint32_t)subs, flag)) return;
+      add(slot0, subs, kGradFold);
+    }
+  }
+  if (!hold) return;
+  float g[4];
+#pragma unroll
+  for (int c = 0; c < 4; ++c) g[c] = (float)(acc[c] + reg_grad(ld.lambda, (double)xq[c]));
+  buf_store4(make_buf(grads + (size_t)node * (size_t)d + part * (uint32_t)ld.part_cols, 4 * len), off, 0, g);
+}
+
+// A whole row chunk by one block of eight wavefronts: the weights of its rows, left where the products were (nobody polls
+// them any more), then one part of the columns after the other.
+__device__ __forceinline__ void grad_alone(const LogisticData& ld, const float* __restrict__ x, float* __restrict__ grads, int64_t d, int node, int rc,
+                                        int nchunks, int slot0, uint32_t r_begin, int rows, double N, double* slots, int* flag) {
+  const uint32_t P = (uint32_t)ld.col_parts, lane = threadIdx.x & 63;
+  const uint32_t off = threadIdx.x * 16u;
+  for (int row = (int)(threadIdx.x >> 6); row < rows; row += 8) {
+    const float* __restrict__ a = ld.A + (size_t)(r_begin + (uint32_t)row) * (size_t)d;
+    double z = 0.0;
+    for (uint32_t l = lane; l < (uint32_t)d; l += 64) z = fma((double)a[l], (double)x[l], z);
+    z = wave_total(z);
+    if (lane == 0) st_coherent(&slots[(size_t)row * P], grad_weight((double)ld.labels[r_begin + (uint32_t)row], z, N));
+  }
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  __syncthreads();
+  for (uint32_t p = 0; p < P; ++p) {
+    const uint32_t c0 = p * (uint32_t)ld.part_cols, len = min((uint32_t)ld.part_cols, (uint32_t)d - c0);
+    float xq[4];
+    buf_load4(make_buf(x + c0, 4 * len), off, 0, xq);
+    double acc[4] = {0.0, 0.0, 0.0, 0.0};
+    for (int row = 0; row < rows; ++row) {
+      float a[4];
+      buf_load4(make_buf(ld.A + (size_t)(r_begin + (uint32_t)row) * (size_t)d + c0, 4 * len), off, 0, a);
+      const double s = ld_coherent(&slots[(size_t)row * P]);
+#pragma unroll
+      for (int c = 0; c < 4; ++c) acc[c] = fma(s, (double)a[c], acc[c]);
+    }
+    finish(ld, grads, d, node, rc, nchunks, slot0, P, p, len, off, true, xq, acc, flag);
+  }
+}
+
+// PARTED: rows are longer than a block's columns (CW = 8, RG = 1)
+template <int CW, int RG, bool PARTED>
 __global__ __launch_bounds__(64 * CW * RG, 4) void k_grad(LogisticData ld, const float* __restrict__ x, float* __restrict__ grads, int64_t d) {
   constexpr int R = kGradRows, NT = 64 * CW * RG;
-  constexpr bool MULTI = CW == 8;
   __shared__ double red[CW * RG][R], s_m[RG][R];
   __shared__ double s_acc[RG > 1 ? RG : 1][RG > 1 ? CW * 256 : 1];
   __shared__ uint32_t s_blk;
-  __shared__ int s_flag;
+  __shared__ int s_flag, s_quit;
   const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), cw = w % CW, rg = w / CW;
   const uint32_t lane = tid & 63;
-  const uint32_t P = MULTI ? (uint32_t)ld.col_parts : 1u;
+  const uint32_t P = PARTED ? (uint32_t)ld.col_parts : 1u;
   uint32_t blk = blockIdx.x;
-  if (MULTI && ld.ticket) {
+  if (PARTED && ld.ticket) {
     if (tid == 0) s_blk = __hip_atomic_fetch_add(&ld.ticket[ld.parity * kCounterStride], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     __syncthreads();
     blk = s_blk;
@@ -83,15 +175,20 @@ __global__ __launch_bounds__(64 * CW * RG, 4) void k_grad(LogisticData ld, const
   const double N = (double)count;
   const uint32_t off = (uint32_t)(cw * 64 + (int)lane) * 16u;       // byte offset of this lane's four columns
   const size_t set = (size_t)ld.rows * P;
-  double* __restrict__ slots = MULTI && P > 1 ? ld.meet + ld.parity * set + (size_t)r_begin * P : nullptr;
-  if (MULTI && P > 1) {       // the set the previous launch used, cleared for the next one
+  double* __restrict__ slots = PARTED ? ld.meet + ld.parity * set + (size_t)r_begin * P : nullptr;
+  if (PARTED) {       // the set the previous launch used, cleared for the next one
     double* __restrict__ old = ld.meet + (ld.parity ^ 1) * set + (size_t)r_begin * P;
     for (int i = tid; i < rows; i += NT) old[(size_t)i * P + part] = 0.0;
+    if (tid == 0) {
+      atomicAdd(&ld.begun[((size_t)ld.parity * ld.groups + group) * kCounterStride], 1u);
+      if (part == 0) ld.begun[((size_t)(ld.parity ^ 1) * ld.groups + group) * kCounterStride] = 0;
+    }
   }
+  if (tid == 0) s_quit = 0;
   float xq[4];
   buf_load4(make_buf(x + c0, 4 * len), off, 0, xq);
   auto label = [&](int row) { return row < rows ? ld.labels[r_begin + (uint32_t)row] : 0.f; };      // (asked for before it is needed)
-  auto weight = [&](double yl, double z) { return -yl / (1.0 + exp(yl * z)) / N; };
+  auto weight = [&](double yl, double z) { return grad_weight(yl, z, N); };
   double acc[4] = {0.0, 0.0, 0.0, 0.0};
   for (int base = 0; base < rows; base += R * RG) {
     // rows base + r RG + rg of the chunk (rows beyond its end read as zero and get weight zero)
@@ -137,7 +234,7 @@ __global__ __launch_bounds__(64 * CW * RG, 4) void k_grad(LogisticData ld, const
 #pragma unroll
       for (int c = 0; c < 4; ++c) asm volatile("" : "+v"(a[r][c]));
     __syncthreads();
-    if (MULTI && P > 1) {
+    if (PARTED) {
       if (tid < R && base + tid < rows) {
         double z = 0.0;
 #pragma unroll
@@ -147,14 +244,29 @@ __global__ __launch_bounds__(64 * CW * RG, 4) void k_grad(LogisticData ld, const
       const int r = tid >> 5, j = tid & 31;
       const bool live = base + r < rows;
       const float yl = label(base + r);
-      double z = 0.0;
-      if (live) {
-        for (uint32_t q = (uint32_t)j; q < P; q += 32) {
-          double t;
-          do t = ld_coherent(&slots[(size_t)(base + r) * P + q]); while (__double_as_longlong(t) == 0);
-          z += t;
+      // (a wavefront leaves the loop as one)
+      static_assert(kNodeParts <= 64, "two blocks a lane");
+      double t[2] = {0.0, 0.0};                // of blocks j and j + 32
+      auto none = [](double v) { return __double_as_longlong(v) == 0; };
+      uint32_t begun = base == 0 && w == 0 ? 0u : P;
+      for (uint32_t polls = 0;; ++polls) {
+        bool open = false;
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+          if (live && (uint32_t)(j + 32 * k) < P && none(t[k])) {
+            t[k] = ld_coherent(&slots[(size_t)(base + r) * P + j + 32 * k]);
+            open = open || none(t[k]);
+          }
         }
+        if (begun != P) begun = poll_begun(&ld.begun[((size_t)ld.parity * ld.groups + group) * kCounterStride], P, polls >= ld.polls);
+        if (begun & kGivenUp) {
+          if (lane == 0) __hip_atomic_store(&s_quit, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+          break;
+        }
+        if (begun == P && !ballot(open)) break;
+        if (base == 0 && w != 0 && __hip_atomic_load(&s_quit, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)) break;
       }
+      double z = t[0] + t[1];
       z += dpp_or0<0x128, 0xf>(z);             // row_ror: the sum over 16 lanes, in all of them
       z += dpp_or0<0x124, 0xf>(z);
       z += dpp_or0<0x122, 0xf>(z);
@@ -169,6 +281,10 @@ __global__ __launch_bounds__(64 * CW * RG, 4) void k_grad(LogisticData ld, const
       s_m[g][r] = row < rows ? weight((double)label(row), z) : 0.0;
     }
     __syncthreads();
+    if (PARTED && base == 0 && __builtin_expect(s_quit, 0)) {
+      if (arrive_last_few(&ld.alone[group], P, &s_flag)) grad_alone(ld, x, grads, d, node, rc, nchunks, slot0, r_begin, rows, N, slots, &s_flag);
+      return;
+    }
 #pragma unroll
     for (int r = 0; r < R; ++r) {
       if (r % 4 == 0) __builtin_amdgcn_sched_barrier(0);
@@ -188,56 +304,7 @@ __global__ __launch_bounds__(64 * CW * RG, 4) void k_grad(LogisticData ld, const
         for (int c = 0; c < 4; ++c) acc[c] += s_acc[g][cw * 256 + (int)lane * 4 + c];
     }
   }
-  const uint32_t l0 = off / 4;
-  if (nchunks > 1) {
-    // Several blocks share the shard's rows: each leaves its sums, and the last to arrive adds them in chunk order --
-    // kGradFold of them; of more chunks, the last of every kGradFold leaves their sum, and the last of those adds these
-    // (one block adding all of them took 140 us for 1 x 4000 rows x 2048 columns, 250 chunks).
-    // (columns l, l + 4, l + 8, ... of a part lie side by side, so that a wavefront's accesses do)
-    const uint32_t quads = ((uint32_t)ld.part_cols + 3) / 4;
-    const size_t slot_len = (size_t)P * quads * 4;
-    double* __restrict__ sums = ld.part + (size_t)part * quads * 4 + off / 16;
-    auto leave = [&](int slot) {
-      if (rg == 0) {
-#pragma unroll
-        for (int c = 0; c < 4; ++c)
-          if (l0 + c < len) st_coherent(&sums[(size_t)slot * slot_len + c * quads], acc[c]);
-      }
-    };
-    auto add = [&](int slot, int count, int stride) {
-#pragma unroll
-      for (int c = 0; c < 4; ++c) acc[c] = 0.0;
-      if (rg == 0) {
-        for (int r0 = 0; r0 < count; r0 += 8) {        // eight loads of a column in flight
-          double v[8][4];
-#pragma unroll
-          for (int u = 0; u < 8; ++u)
-#pragma unroll
-            for (int c = 0; c < 4; ++c)
-              v[u][c] = r0 + u < count && l0 + c < len ? ld_coherent(&sums[(size_t)(slot + (r0 + u) * stride) * slot_len + c * quads]) : 0.0;
-#pragma unroll
-          for (int u = 0; u < 8; ++u)
-#pragma unroll
-            for (int c = 0; c < 4; ++c) acc[c] += v[u][c];
-        }
-      }
-    };
-    leave(slot0 + rc);
-    const int sub = rc - rc % kGradFold, members = min(kGradFold, nchunks - sub);
-    if (!arrive_last_few(&ld.col_done[(size_t)(slot0 + sub) * P + part], (uint32_t)members, &s_flag)) return;
-    add(slot0 + sub, members, 1);
-    if (nchunks > kGradFold) {
-      leave(slot0 + sub);
-      const int subs = (nchunks + kGradFold - 1) / kGradFold;
-      if (!arrive_last_few(&ld.col_done[(size_t)(ld.part_slots + slot0) * P + part], (uint32_t)subs, &s_flag)) return;
-      add(slot0, subs, kGradFold);
-    }
-  }
-  if (rg != 0) return;
-  float g[4];
-#pragma unroll
-  for (int c = 0; c < 4; ++c) g[c] = (float)(acc[c] + reg_grad(ld.lambda, (double)xq[c]));
-  buf_store4(make_buf(grads + (size_t)node * (size_t)d + c0, 4 * len), off, 0, g);
+  if (rg == 0 || nchunks > 1) finish(ld, grads, d, node, rc, nchunks, slot0, P, part, len, off, rg == 0, xq, acc, &s_flag);
 }
 
 hipError_t launch_grad(const LogisticData& ld, const float* x, float* grads, int64_t d, hipStream_t st) {
@@ -249,10 +316,10 @@ hipError_t launch_grad(const LogisticData& ld, const float* x, float* grads, int
   };
   const int rg = ld.row_groups;
   switch (grad_col_waves(ld.part_cols)) {
-    case 1: return rg == 1 ? go(k_grad<1, 1>, 1) : rg == 2 ? go(k_grad<1, 2>, 2) : rg == 4 ? go(k_grad<1, 4>, 4) : go(k_grad<1, 8>, 8);
-    case 2: return rg == 1 ? go(k_grad<2, 1>, 2) : rg == 2 ? go(k_grad<2, 2>, 4) : go(k_grad<2, 4>, 8);
-    case 4: return rg == 1 ? go(k_grad<4, 1>, 4) : go(k_grad<4, 2>, 8);
-    default: return go(k_grad<8, 1>, 8);
+    case 1: return rg == 1 ? go(k_grad<1, 1, false>, 1) : rg == 2 ? go(k_grad<1, 2, false>, 2) : rg == 4 ? go(k_grad<1, 4, false>, 4) : go(k_grad<1, 8, false>, 8);
+    case 2: return rg == 1 ? go(k_grad<2, 1, false>, 2) : rg == 2 ? go(k_grad<2, 2, false>, 4) : go(k_grad<2, 4, false>, 8);
+    case 4: return rg == 1 ? go(k_grad<4, 1, false>, 4) : go(k_grad<4, 2, false>, 8);
+    default: return ld.col_parts > 1 ? go(k_grad<8, 1, true>, 8) : go(k_grad<8, 1, false>, 8);
   }
 }
 

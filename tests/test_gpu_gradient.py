@@ -32,7 +32,16 @@ def test_gradient_of_a_long_shard_among_short_ones(n, d, rows, short):
     check_gradient(n, d, rows, cnt, rng)
 
 
-def check_gradient(n, d, rows, cnt, rng):
+@pytest.mark.parametrize("n,d,rows,short", [(3, 2049, 40, 40), (5, 5003, 203, 150), (3, 65536, 300, 1), (1, 131072, 20, 0), (90, 4099, 5, 5),
+                                            (1, 16384, 900, 0)])
+def test_gradient_where_blocks_do_not_wait_for_each_other(n, d, rows, short):
+    """A chunk whose blocks were not all running at once is formed by one of them."""
+    cnt = np.full(n, short)
+    cnt[n // 2] = rows
+    check_gradient(n, d, rows, cnt, np.random.default_rng(d * 13 + rows), _eng().FLAG_NO_WAIT)
+
+
+def check_gradient(n, d, rows, cnt, rng, flags=0):
     E = _eng()
     off = np.concatenate([[0], np.cumsum(cnt)]).astype(np.int64)
     A = rng.standard_normal((int(off[-1]), d), dtype=np.float32)
@@ -40,7 +49,7 @@ def check_gradient(n, d, rows, cnt, rng):
     x0 = (rng.standard_normal(d) / np.sqrt(d)).astype(np.float32)
     eng = E.AdaCGD(n=n, d=d, gamma=0.3, lam=0.1, worker_levels=[(E.TOPK, max(1, d // 10)), (E.TOPK, d)], zeta_worker=0.0,
                    master_levels=[], grad_mode=E.GRAD_LOGISTIC, A=_cuda(A), labels=_cuda(y), shard_offsets=off, x0=_cuda(x0),
-                   flags=E.FLAG_ANY_LEVEL_ORDER)
+                   flags=E.FLAG_ANY_LEVEL_ORDER | flags)
     for step in range(4):        # (both sets of what blocks meet at are used twice)
         if step:
             eng.step()
