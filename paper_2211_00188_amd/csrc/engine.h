@@ -63,10 +63,11 @@ struct LevelTable {
 };
 
 // Partial results a block leaves for the node's other blocks (norms, largest key, zeros; energies, counts), and words of
-// one set of what the blocks of a node meet at: the partial results and three histograms.
+// one set of what the blocks of a node meet at: the count of those that have begun, the partial results and three histograms.
 __host__ __device__ inline size_t node_part_quantities(int pk, int nq) { return 4 + 1 + 3 * (size_t)pk + nq; }
 __host__ __device__ inline size_t node_meet_words(int pk, int nq, int NB) {
-  return 2 * node_part_quantities(pk, nq) * NB + (pk > 0 ? kBins0 : 0) + (size_t)pk * (kBins1 + kBins2);
+  const size_t words = kCounterStride + 2 * node_part_quantities(pk, nq) * NB + (pk > 0 ? kBins0 : 0) + (size_t)pk * (kBins1 + kBins2);
+  return (words + kCounterStride - 1) / kCounterStride * kCounterStride;      // (the count of every node in a line of its own)
 }
 
 // Device arrays of one side.  nn nodes, each with a length-d vector.
@@ -138,6 +139,8 @@ struct NodeSet {
   float* qscale;        // [nn]
   uint32_t* meet;       // [2][nn][node_meet_words] partial results and histograms of a node's blocks (NB > 1); zero at init
   uint32_t* ticket;     // [2][kCounterStride] next (node, chunk) to be taken by a block; zero at init; null up to kNodeParts blocks
+  uint32_t* alone;      // [nn] blocks that have left a node that was given up (NB > 1); zero between launches
+  uint32_t polls;       // polls before a node is given up
   float* dense;         // [nn][d] C(v) of every node that sent a message, for the aggregation inside the one-block kernel
                         //         (null: the aggregation is a kernel of its own)
   double* accbuf;       // [d] fp64 sums of the sparse messages (only with quantiser levels)

@@ -165,6 +165,7 @@ void carve_nodeset(Carver& c, NodeSet& ns) {
   const bool chunks = ns.small && ns.NB > 1;
   ns.meet = chunks ? c.take<uint32_t>(2 * nn * node_meet_words(ns.lv.pk, (int)nq, ns.NB)) : nullptr;
   ns.ticket = chunks && nn * ns.NB > kNodeParts ? c.take<uint32_t>(2 * kCounterStride) : nullptr;
+  ns.alone = chunks ? c.take<uint32_t>(nn) : nullptr;
   ns.level_hist = c.take<unsigned long long>(m + 2);
   ns.repairs = ns.level_hist ? ns.level_hist + m + 1 : nullptr;   // (null when only measuring)
   // everything up to here must start at zero
@@ -564,6 +565,7 @@ size_t shape_all(const adacgd_config* cfg, const LevelTable& wl, const LevelTabl
     M.lv = ml;
     shape_nodeset(W, (int)cfg->n, cfg->d, two_pass, chunks);
     shape_nodeset(M, 1, cfg->d, two_pass, chunks);
+    W.polls = M.polls = cfg->flags & ADACGD_FLAG_NO_WAIT ? 0u : kPolls;
     shape_logistic(cfg, ld);
     Layout L{};
     return carve_all(nullptr, cfg, W, M, ld, L);

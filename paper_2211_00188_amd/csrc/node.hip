@@ -13,12 +13,13 @@
 // third digit) is complete when its counts add up to the number of keys that go into it, which every block knows,
 // and a partial result (never negative) is stored negated, so that it differs from the zero that was there before.
 // A meeting is then one atomic or store on its way to memory and one load coming back.
-// Waiting.  A block only waits for blocks of its own node.  Blocks take their (node, chunk) by an atomic ticket, so the
-// waiting blocks of the lowest unfinished node need at most NB <= kNodeParts resident blocks in all to finish,
-// whatever the order of dispatch; a launch of no more than kNodeParts blocks needs that many anyway and goes without.
-// A compute unit holds two blocks, the device 512, so eight such launches running side by side (of other contexts on
-// other streams) leave one of them enough, however they are mixed on the device.
-// Other kernels never wait, so they end and free their units.
+// Waiting.  A block only waits for blocks of its own node.  Blocks take their (node, chunk) by an atomic ticket, so that the
+// blocks of a node begin together whatever the order of dispatch (a launch of no more than kNodeParts blocks goes without).
+// That they are running all at once cannot be relied on: other launches, of other contexts on other streams or of other
+// processes, may have filled the device with blocks that wait themselves.  So a block counts itself in its node's word as
+// it begins, and the first meeting also waits for that word: where it is not complete after some time the node is given
+// up, its blocks leave, and the last of them to come does the node alone, from memory.  After the first meeting all blocks
+// of the node are running, and what they wait for comes.
 // What is polled exists twice: a launch uses one set and clears the other, which the previous launch of the node
 // set has left behind (launches of a node set are ordered on a stream).
 // Measured, per launch, against the general sequence of select.hip (sum of its kernels): Top-K sets, 8 nodes of 20000
@@ -114,10 +115,11 @@ constexpr int kErrBatch = 3;         // quantiser levels evaluated in one pass o
 // never matter: they add nothing to a sum, zeros are not counted in a histogram, and they are not sent.
 // CAP: candidates (values that can belong to the largest Top-K set below the identity) that fit the list in LDS;
 // with more of them the passes over the candidates run over the registers instead.
-template <int NT, int VPT, int CAP, bool QUANT>
+// MULTI: several blocks per node.
+template <int NT, int VPT, int CAP, bool QUANT, bool MULTI>
 __global__ __launch_bounds__(NT, NT >= 512 ? 4 : 1) void k_node(NodeSet ns, PassArgs a) {
   constexpr int NQ4 = VPT / 4, NW = NT / 64;
-  constexpr bool MULTI = CAP >= 2 * kMaxLevels * kNodeParts && NT >= 512;      // may run with several blocks per node
+  static_assert(!MULTI || CAP >= 2 * kMaxLevels * kNodeParts, "the counts of the node's blocks fit the list");
   extern __shared__ __align__(16) uint32_t dyn[];
   uint32_t* const hist = dyn;              // 4096 words: first digit; then kBatch histograms of 1024 or 512 bins
   uint32_t* const list = dyn + kBins0;     // CAP words: block scales of quantisers; keys of the candidates; counts of the node's blocks
@@ -136,7 +138,7 @@ __global__ __launch_bounds__(NT, NT >= 512 ? 4 : 1) void k_node(NodeSet ns, Pass
   __shared__ double s_tz[kMaxLevels + 1], s_te[kMaxLevels + 1];
   __shared__ uint32_t s_blk;
   __shared__ uint32_t s_fill[kBatch];
-  __shared__ int s_flag;
+  __shared__ int s_flag, s_quit;
 
   const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const uint32_t lane = tid & 63;
@@ -163,11 +165,16 @@ __global__ __launch_bounds__(NT, NT >= 512 ? 4 : 1) void k_node(NodeSet ns, Pass
   const uint32_t off0 = (uint32_t)tid * 16u;                                // byte offset of quad 0; quad q: + 16 q NT
 
   // where the node's blocks meet: histograms of the three digits, partial results [quantity][block]
-  uint32_t *gh1 = nullptr, *gh2 = nullptr, *gh3 = nullptr;
+  uint32_t *begun = nullptr, *gh1 = nullptr, *gh2 = nullptr, *gh3 = nullptr;
   double *part1 = nullptr, *part2 = nullptr;
-  if (MULTI && NB > 1) {
+  if (MULTI) {
     const size_t words = node_meet_words(pk, nq, NB);
-    part1 = reinterpret_cast<double*>(ns.meet + ((size_t)a.parity * ns.nn + node) * words);
+    begun = ns.meet + ((size_t)a.parity * ns.nn + node) * words;
+    part1 = reinterpret_cast<double*>(begun + kCounterStride);
+    if (tid == 0) {
+      atomicAdd(begun, 1u);
+      s_quit = 0;
+    }
     part2 = part1 + 4 * NB;
     gh1 = reinterpret_cast<uint32_t*>(part1 + node_part_quantities(pk, nq) * NB);
     gh2 = gh1 + kBins0;
@@ -198,11 +205,28 @@ __global__ __launch_bounds__(NT, NT >= 512 ? 4 : 1) void k_node(NodeSet ns, Pass
       if (waves_sum<NW>(redc[0][0], lane) == total) break;
     }
   };
+  auto none = [](double t) { return t == 0.0 && !(__double2hiint(t) < 0); };
   // One partial result of every block of the node, lane by lane (zero beyond them), once it is there.
   auto meet_value = [&](const double* p) {
     double t = -0.0;
     if ((int)lane < NB) {
-      do t = ld_coherent(p + lane); while (t == 0.0 && !(__double2hiint(t) < 0));
+      do t = ld_coherent(p + lane); while (none(t));
+    }
+    return -t;
+  };
+  // The same at the first meeting (wavefronts leave the loop as one; wavefront 0 finds out whether the node is complete).
+  auto meet_first = [&](const double* p) {
+    double t = (int)lane < NB ? 0.0 : -0.0;
+    uint32_t there = w == 0 ? 0u : (uint32_t)NB;
+    for (uint32_t polls = 0;; ++polls) {
+      if (none(t)) t = ld_coherent(p + lane);
+      if (there != (uint32_t)NB) there = poll_begun(begun, (uint32_t)NB, polls >= ns.polls);
+      if (there & kGivenUp) {
+        if (lane == 0) __hip_atomic_store(&s_quit, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        break;
+      }
+      if (there == (uint32_t)NB && !ballot(none(t))) break;
+      if (w != 0 && __hip_atomic_load(&s_quit, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)) break;
     }
     return -t;
   };
@@ -215,6 +239,266 @@ __global__ __launch_bounds__(NT, NT >= 512 ? 4 : 1) void k_node(NodeSet ns, Pass
     s_tz[tid] = lv.tz[tid];
     s_te[tid] = lv.te[tid];
   }
+
+  // ---- the cascade (every wavefront for itself, lane j the level j + 1); the node's results by one wavefront of `writer` ----
+  auto choose = [&](double S, double Dn, bool skip, bool writer, int* slot_out, int* q_out) {
+    double my_err = __longlong_as_double(0x7FF8000000000000ll);      // not evaluated on a skip
+    bool hit = false;
+    if (!skip && (int)lane < lv.m) {
+      const int ref = s_ref[lane];
+      if (s_kind[lane] != kTopK) {
+        my_err = s_fin[1 + kMaxLevels + ref];
+      } else if (ref >= pk) {                // the identity
+        my_err = 0.0;
+      } else {
+        const double tv = (double)__uint_as_float(s_T[ref]);
+        my_err = s_fin[0] + s_fin[1 + ref] + (double)(s_eq[ref] - s_r[ref]) * (tv * tv);    // (ties not taken)
+      }
+      hit = (int)lane + 1 < lv.m && my_err <= __dadd_rn(__dmul_rn(s_tz[lane + 1], Dn), __dmul_rn(s_te[lane + 1], S));
+    }
+    const uint64_t good = ballot(hit);
+    const int jstar = skip ? 0 : good ? __ffsll((unsigned long long)good) : lv.m;
+    int slot = -1, q_sel = -1;
+    if (jstar > 0) {
+      const int ref = __builtin_amdgcn_readfirstlane(s_ref[jstar - 1]);
+      if (__builtin_amdgcn_readfirstlane(s_kind[jstar - 1]) == kTopK) slot = ref;
+      else q_sel = ref;
+    }
+    if (w == 0 && writer) {
+      if ((int)lane < lv.m) ns.err[node * lv.m + lane] = my_err;
+      if (lane == 0) {
+        ns.S[node] = S;
+        ns.D[node] = Dn;
+        ns.level[node] = jstar;
+        atomicAdd(&ns.level_hist[jstar], 1ull);
+        if (serve) st_coherent(&ns.sel_slot[node], slot);
+        else ns.sel_slot[node] = slot;
+        ns.sel_q[node] = q_sel;
+        ns.msg_count[node] = slot >= 0 ? s_K[slot] : 0u;
+        if (nq > 0) ns.qscale[node] = 0.f;
+      }
+    }
+    *slot_out = slot;
+    *q_out = q_sel;
+  };
+
+  // ---- a whole node by one block, for one that was given up (NB > 1): the vector is read again for every digit and level ----
+  const uint32_t k0 = (uint32_t)a.seed, k1 = (uint32_t)(a.seed >> 32);
+  const uint32_t ctr1 = (uint32_t)node | a.node_flag;
+  auto alone = [&] {
+    constexpr uint32_t STEP = NT * 4;        // coordinates a pass of the block: four a thread, in order
+    static_assert(!MULTI || STEP == kWaveTile, "message offsets are kept for every kWaveTile coordinates");
+    const size_t start = (size_t)node * d;
+    const Buf xn = make_buf(a.x + start, 4 * d), hn = make_buf(a.h + start, 4 * d), yn = make_buf(diff ? nullptr : a.y + start, diff ? 0u : 4 * d);
+    auto load = [&](uint32_t l0, float (&vq)[4], float (&hq)[4]) {       // (zero beyond the end)
+      float xq[4];
+      buf_load4(xn, 4 * l0, 0, xq);
+      buf_load4(hn, 4 * l0, 0, hq);
+#pragma unroll
+      for (int c = 0; c < 4; ++c) vq[c] = diff ? xq[c] : xq[c] - hq[c];
+    };
+    auto total = [&](double e) {
+      e = wave_total(e);
+      __syncthreads();
+      if (lane == 0) red[0][w] = e;
+      __syncthreads();
+      return waves_sum<NW>(red[0], lane);
+    };
+    auto scan = [&](uint32_t n, uint32_t* sum) {       // exclusive, in thread order
+      const uint32_t inc = wave_scan(n);
+      __syncthreads();
+      if (lane == 63) redu[0][w] = inc;
+      __syncthreads();
+      uint32_t before;
+      *sum = waves_sum<NW>(redu[0], lane, w, &before);
+      return before + inc - n;
+    };
+    auto block_scale = [&](const float (&vq)[4], int B) {       // largest magnitude of the quantiser block of these coordinates
+      uint32_t m = 0;
+#pragma unroll
+      for (int c = 0; c < 4; ++c) m = max(m, magkey(vq[c]));
+#pragma unroll
+      for (int o = 1; o < 16; o <<= 1) m = max(m, (uint32_t)__shfl_xor(m, o, 64));
+      __syncthreads();
+      if ((lane & 15) == 0) segk[tid / 16] = m;
+      __syncthreads();
+      const int per = B / kSeg, first = tid / 16 / per * per;
+      m = 0;
+      for (int j = 0; j < per; ++j) m = max(m, segk[first + j]);
+      return __uint_as_float(m);
+    };
+    double S = 0.0, D = 0.0;
+    uint32_t kmax = 0, nonzero = 0;
+#pragma unroll 1
+    for (uint32_t l0 = tid * 4; l0 < d; l0 += STEP) {
+      float vq[4], hq[4], xq[4], yq[4];
+      load(l0, vq, hq);
+      buf_load4(xn, 4 * l0, 0, xq);
+      buf_load4(yn, 4 * l0, 0, yq);
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        S = fma((double)vq[c], (double)vq[c], S);
+        const double dw = (double)(xq[c] - yq[c]);
+        D = fma(dw, dw, D);
+        kmax = max(kmax, magkey(vq[c]));
+        nonzero += magkey(vq[c]) ? 1u : 0u;
+      }
+    }
+    S = total(S);
+    D = total(D);
+    scan(nonzero, &nonzero);
+    kmax = wave_top(kmax);
+    if (lane == 0) redu[1][w] = kmax;
+    __syncthreads();
+    kmax = wave_top(redu[1][lane & (NW - 1)]);
+    const double Dn = diff ? a.extD[node] : D;
+    const bool skip = !a.assign && S <= trigger_bound(lv, 0, S, Dn);
+    const float qa = __uint_as_float(kmax);
+    if (!skip) {
+      if (tid == 0) s_fin[0] = 0.0;
+#pragma unroll 1
+      for (int s = 0; s < pk; ++s) {
+        const uint32_t K = lane_value(s_K[s], 0);
+        uint32_t T = 0, r = K - nonzero, eq = d - nonzero;       // a size that the non-zero keys do not reach: threshold zero
+        if (K <= nonzero) {
+          r = K;
+#pragma unroll 1
+          for (int digit = 0; digit < 3; ++digit) {
+            const int above = digit == 0 ? 31 : digit == 1 ? kShift0 : kShift1, at = digit == 0 ? kShift0 : digit == 1 ? kShift1 : 0;
+            const int bins = digit == 0 ? kBins0 : digit == 1 ? kBins1 : kBins2;
+            __syncthreads();
+            for (int b = tid; b < kBins0; b += NT) hist[b] = 0;
+            __syncthreads();
+#pragma unroll 1
+            for (uint32_t l0 = tid * 4; l0 < d; l0 += STEP) {
+              float vq[4], hq[4];
+              load(l0, vq, hq);
+#pragma unroll
+              for (int c = 0; c < 4; ++c) {
+                const uint32_t key = magkey(vq[c]);
+                if (key && (key >> above) == T) atomicAdd(&hist[(key >> at) & (bins - 1)], 1u);
+              }
+            }
+            __syncthreads();
+            if (w == 0) wave_walk<kBins0>(hist, r, s_walk[0]);
+            __syncthreads();
+            T = T * bins + lane_value(s_walk[0][0], 0);
+            r = lane_value(s_walk[0][1], 0);
+            eq = lane_value(s_walk[0][2], 0);
+          }
+        }
+        double e = 0.0;
+#pragma unroll 1
+        for (uint32_t l0 = tid * 4; l0 < d; l0 += STEP) {
+          float vq[4], hq[4];
+          load(l0, vq, hq);
+#pragma unroll
+          for (int c = 0; c < 4; ++c) e += magkey(vq[c]) < T ? (double)vq[c] * (double)vq[c] : 0.0;
+        }
+        e = total(e);
+        if (tid == 0) { s_T[s] = T; s_r[s] = r; s_eq[s] = eq; s_fin[1 + s] = e; }
+      }
+      if (QUANT) {
+#pragma unroll 1
+        for (int q = 0; q < nq; ++q) {
+          const int B = lv.qblock[q];
+          double e = 0.0;
+#pragma unroll 1
+          for (uint32_t t0 = 0; t0 < d; t0 += STEP) {
+            float vq[4], hq[4];
+            load(t0 + tid * 4, vq, hq);
+            const float aq = B ? block_scale(vq, B) : qa;
+            const float cq = aq > 0.f ? (float)((double)aq / lv.qdenom[q]) : 0.f;
+            uint32_t rnd[4];
+            philox4x32_10((t0 >> 2) + tid, ctr1, a.step, 0u, k0, k1, rnd);
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+              float xi;
+              const double er = (double)fabsf(vq[c]) - (double)quant_mag(aq > 0.f ? fabsf(vq[c]) / aq : 0.f, lv.qs[q], cq, dither_of(rnd[c]), &xi);
+              e = fma(er, er, e);
+            }
+          }
+          e = total(e);
+          if (tid == 0) s_fin[1 + kMaxLevels + q] = e;
+        }
+      }
+    }
+    __syncthreads();
+    int slot, q_sel;
+    choose(S, Dn, skip, true, &slot, &q_sel);
+    if (slot >= 0) {
+      const bool ident = slot >= pk;
+      const uint32_t T = ident ? 0u : lane_value(s_T[slot], 0), r = ident ? d : lane_value(s_r[slot], 0);
+      uint32_t out = 0, ties = 0;          // entries, and keys equal to T, of the coordinates before these
+      uint32_t* __restrict__ go = ns.grp_off + (size_t)node * (ns.groups + 1);
+#pragma unroll 1
+      for (uint32_t t0 = 0; t0 < d; t0 += STEP) {
+        const uint32_t l0 = t0 + tid * 4;
+        float vq[4], hq[4];
+        load(l0, vq, hq);
+        uint32_t n = 0, sum;
+#pragma unroll
+        for (int c = 0; c < 4; ++c) n += magkey(vq[c]) == T && l0 + c < d ? 1u : 0u;
+        uint32_t rank = ties + scan(n, &sum), f = 0;
+        ties += sum;
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+          const uint32_t key = magkey(vq[c]);
+          if (l0 + c < d && (key > T || (key == T && rank < r))) f |= 1u << c;
+          rank += key == T ? 1u : 0u;
+        }
+        if (tid == 0) go[t0 / STEP] = out;
+        uint32_t pos = out + scan((uint32_t)__popc(f), &sum);
+        out += sum;
+        if (f) {
+#pragma unroll
+          for (int c = 0; c < 4; ++c) {
+            if ((f >> c) & 1u) {
+              ns.msg_idx[(size_t)node * ns.Kcap + pos] = (int32_t)(l0 + c);
+              ns.msg_val[(size_t)node * ns.Kcap + pos] = vq[c];
+              ++pos;
+              hq[c] = a.assign ? vq[c] : hq[c] + vq[c];
+            }
+          }
+          buf_store4(hn, 4 * l0, 0, hq);
+        }
+      }
+      if (tid == 0) go[ns.groups] = out;
+    } else if (QUANT && q_sel >= 0) {
+      const int B = lv.qblock[q_sel];
+      const float qc = !B && qa > 0.f ? (float)((double)qa / lv.qdenom[q_sel]) : 0.f;
+      if (tid == 0) ns.qscale[node] = qc;
+#pragma unroll 1
+      for (uint32_t t0 = 0; t0 < d; t0 += STEP) {
+        const uint32_t l0 = t0 + tid * 4;
+        float vq[4], hq[4];
+        load(l0, vq, hq);
+        const float aq = B ? block_scale(vq, B) : qa;
+        const float cq = B ? (aq > 0.f ? (float)((double)aq / lv.qdenom[q_sel]) : 0.f) : qc;
+        if (B && l0 < d && l0 % (uint32_t)B == 0) ns.qbscale[(size_t)node * ns.nseg + l0 / (uint32_t)B] = cq;
+        uint32_t rnd[4];
+        philox4x32_10(l0 >> 2, ctr1, a.step, 0u, k0, k1, rnd);
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+          int code = 0;
+          hq[c] += aq > 0.f ? quant_one(vq[c], aq, lv.qs[q_sel], cq, dither_of(rnd[c]), &code) : 0.f;
+          if (l0 + c < d) ns.qcodes[start + l0 + c] = (int16_t)code;
+        }
+        buf_store4(hn, 4 * l0, 0, hq);
+      }
+    }
+    if (a.xu_out && node == 0) {
+#pragma unroll 1
+      for (uint32_t l0 = tid * 4; l0 < d; l0 += STEP) {        // (of what is read again, this thread's own stores)
+        float hq[4], xq[4];
+        buf_load4(hn, 4 * l0, 0, hq);
+        buf_load4(make_buf(a.xu_x, 4 * d), 4 * l0, 0, xq);
+#pragma unroll
+        for (int c = 0; c < 4; ++c) xq[c] = (float)((double)xq[c] - a.xu_gamma * (double)hq[c]);
+        buf_store4(make_buf(a.xu_out, 4 * d), 4 * l0, 0, xq);
+      }
+    }
+  };
 
   // ---- read: v, ||v||^2, ||x - y||^2, largest key ----
   // (the estimator's first KH quads stay in registers, the rest is read again when it is updated)
@@ -302,7 +586,7 @@ __global__ __launch_bounds__(NT, NT >= 512 ? 4 : 1) void k_node(NodeSet ns, Pass
     }
     __syncthreads();
   };
-  if (MULTI && NB > 1) {
+  if (MULTI) {
     uint32_t zeros = 0;
     if (pk > 0) {
       first_digit();
@@ -327,11 +611,15 @@ __global__ __launch_bounds__(NT, NT >= 512 ? 4 : 1) void k_node(NodeSet ns, Pass
       if (pk > 0) st_coherent(&part1[3 * NB + part], -(double)zeros);
     }
     if (w < 4 && (w < 2 || (w == 2 ? QUANT : pk > 0))) {
-      const double t = meet_value(part1 + w * NB);
+      const double t = meet_first(part1 + w * NB);
       const double s = w == 2 ? (double)wave_top((uint32_t)t) : wave_total(t);
       if (lane == 0) s_first[w] = s;
     }
     __syncthreads();
+    if (__builtin_expect(s_quit, 0)) {
+      if (arrive_last_few(&ns.alone[node], (uint32_t)NB, &s_flag)) alone();
+      return;
+    }
     if (pk > 0) {
       for (uint32_t i = tid * 2; i < (uint32_t)kBins0; i += NT * 2) {
         const uint64_t two = ld_coherent(reinterpret_cast<const uint64_t*>(gh1 + i));
@@ -349,8 +637,6 @@ __global__ __launch_bounds__(NT, NT >= 512 ? 4 : 1) void k_node(NodeSet ns, Pass
   const bool skip = !a.assign && S <= trigger_bound(lv, 0, S, Dn);
 
   // ---- realised error of every quantiser level: those that share a scale together, kErrBatch at a time ----
-  const uint32_t k0 = (uint32_t)a.seed, k1 = (uint32_t)(a.seed >> 32);
-  const uint32_t ctr1 = (uint32_t)node | a.node_flag;
   const float qa = __uint_as_float(kmax);
   // block-wise levels: per block of B coordinates its scale a (the maximum over its segments) and c of up to
   // kErrBatch levels
@@ -445,7 +731,7 @@ __global__ __launch_bounds__(NT, NT >= 512 ? 4 : 1) void k_node(NodeSet ns, Pass
   }
 
   if (!skip && pk > 0) {
-    if (!(MULTI && NB > 1)) first_digit();
+    if (!(MULTI)) first_digit();
     uint32_t nonzero;                  // keys counted, of the whole node
     {
       constexpr int PER = kBins0 / NT;
@@ -519,7 +805,7 @@ __global__ __launch_bounds__(NT, NT >= 512 ? 4 : 1) void k_node(NodeSet ns, Pass
         inbin += c;
         most = max(most, c);
       }
-      if (NB == 1 && most <= 64) {
+      if (!MULTI && most <= 64) {
         // ---- few keys in every threshold's bin: one wavefront per size ranks them directly ----
         if (tid < kBatch) s_fill[tid] = 0;
         __syncthreads();
@@ -557,7 +843,7 @@ __global__ __launch_bounds__(NT, NT >= 512 ? 4 : 1) void k_node(NodeSet ns, Pass
             if (cand && (key >> kShift0) == pre[s]) atomicAdd(&hist[s * kBins1 + ((key >> kShift1) & (kBins1 - 1))], 1u);
         });
         __syncthreads();
-        if (MULTI && NB > 1) meet_hist(gh2 + (size_t)s0 * kBins1, nb * kBins1, inbin);
+        if (MULTI) meet_hist(gh2 + (size_t)s0 * kBins1, nb * kBins1, inbin);
         if (w < nb) wave_walk<kBins1>(hist + w * kBins1, s_walk[s0 + w][1], s_walk[s0 + w]);
         __syncthreads();
         // ---- third digit ----
@@ -577,7 +863,7 @@ __global__ __launch_bounds__(NT, NT >= 512 ? 4 : 1) void k_node(NodeSet ns, Pass
             if (cand && (key >> kShift1) == pre[s]) atomicAdd(&hist[s * kBins2 + (key & (kBins2 - 1))], 1u);
         });
         __syncthreads();
-        if (MULTI && NB > 1) meet_hist(gh3 + (size_t)s0 * kBins2, nb * kBins2, inbin);
+        if (MULTI) meet_hist(gh3 + (size_t)s0 * kBins2, nb * kBins2, inbin);
         if (w < nb) wave_walk<kBins2>(hist + w * kBins2, s_walk[s0 + w][1], s_walk[s0 + w]);
         __syncthreads();
 #pragma unroll
@@ -638,7 +924,7 @@ __global__ __launch_bounds__(NT, NT >= 512 ? 4 : 1) void k_node(NodeSet ns, Pass
   }
 
   // ---- totals over the node's blocks ----
-  if (MULTI && NB > 1 && !skip && (pk > 0 || nq > 0)) {
+  if (MULTI && !skip && (pk > 0 || nq > 0)) {
     const int ne = 1 + pk + nq;            // energies: below the candidates, below every threshold, quantiser errors
     __syncthreads();
     if (tid < ne + 2 * pk) {
@@ -661,44 +947,9 @@ __global__ __launch_bounds__(NT, NT >= 512 ? 4 : 1) void k_node(NodeSet ns, Pass
   }
   __syncthreads();
 
-  // ---- the cascade (every wavefront for itself, lane j the level j + 1) ----
-  double my_err = __longlong_as_double(0x7FF8000000000000ll);      // not evaluated on a skip
-  bool hit = false;
-  if (!skip && (int)lane < lv.m) {
-    const int ref = s_ref[lane];
-    if (s_kind[lane] != kTopK) {
-      my_err = s_fin[1 + kMaxLevels + ref];
-    } else if (ref >= pk) {                // the identity
-      my_err = 0.0;
-    } else {
-      const double tv = (double)__uint_as_float(s_T[ref]);
-      my_err = s_fin[0] + s_fin[1 + ref] + (double)(s_eq[ref] - s_r[ref]) * (tv * tv);    // (ties not taken)
-    }
-    hit = (int)lane + 1 < lv.m && my_err <= __dadd_rn(__dmul_rn(s_tz[lane + 1], Dn), __dmul_rn(s_te[lane + 1], S));
-  }
-  const uint64_t good = ballot(hit);
-  const int jstar = skip ? 0 : good ? __ffsll((unsigned long long)good) : lv.m;
-  int slot = -1, q_sel = -1;
-  if (jstar > 0) {
-    const int ref = __builtin_amdgcn_readfirstlane(s_ref[jstar - 1]);
-    if (__builtin_amdgcn_readfirstlane(s_kind[jstar - 1]) == kTopK) slot = ref;
-    else q_sel = ref;
-  }
+  int slot, q_sel;
+  choose(S, Dn, skip, part == 0, &slot, &q_sel);
   const uint32_t K_sel = slot >= 0 ? __builtin_amdgcn_readfirstlane(s_K[slot]) : 0u;
-  if (w == 0 && part == 0) {
-    if ((int)lane < lv.m) ns.err[node * lv.m + lane] = my_err;
-    if (lane == 0) {
-      ns.S[node] = S;
-      ns.D[node] = Dn;
-      ns.level[node] = jstar;
-      atomicAdd(&ns.level_hist[jstar], 1ull);
-      if (serve) st_coherent(&ns.sel_slot[node], slot);
-      else ns.sel_slot[node] = slot;
-      ns.sel_q[node] = q_sel;
-      ns.msg_count[node] = K_sel;
-      if (nq > 0) ns.qscale[node] = 0.f;
-    }
-  }
 
   if (slot >= 0) {
     // ---- message of the chosen Top-K size in ascending coordinate, h <- h + C(v) ----
@@ -707,7 +958,7 @@ __global__ __launch_bounds__(NT, NT >= 512 ? 4 : 1) void k_node(NodeSet ns, Pass
     uint32_t r = ident ? 0u : lane_value(s_r[slot], 0);         // ties this block takes, below
     const bool all = ident || lane_value(s_eq[slot], 0) == r;   // every key equal to T is taken
     uint32_t first = ident ? c0 : 0u;            // message offset of the chunk's first entry
-    if (MULTI && NB > 1 && !ident) {
+    if (MULTI && !ident) {
       const uint32_t g = list[slot * 64 + lane], e = list[(pk + slot) * 64 + lane];     // (zero beyond the node's blocks)
       const uint32_t before = wave_scan(e) - e;
       const uint32_t take = before >= r ? 0u : min(e, r - before);
@@ -883,7 +1134,7 @@ __global__ __launch_bounds__(NT, NT >= 512 ? 4 : 1) void k_node(NodeSet ns, Pass
 // ---------------------------------------------------------------------------
 // launcher
 // ---------------------------------------------------------------------------
-template <int NT, int VPT, int CAP>
+template <int NT, int VPT, int CAP, bool MULTI>
 static hipError_t launch_node_as(const NodeSet& ns, const PassArgs& a, hipStream_t st) {
   const size_t lds = sizeof(uint32_t) * (kBins0 + CAP);
   auto go = [&](auto kern) -> hipError_t {
@@ -894,15 +1145,20 @@ static hipError_t launch_node_as(const NodeSet& ns, const PassArgs& a, hipStream
     hipLaunchKernelGGL(kern, dim3((unsigned)ns.nn * ns.NB), dim3(NT), lds, st, ns, a);
     return hipGetLastError();
   };
-  return ns.lv.nq > 0 ? go(k_node<NT, VPT, CAP, true>) : go(k_node<NT, VPT, CAP, false>);
+  return ns.lv.nq > 0 ? go(k_node<NT, VPT, CAP, true, MULTI>) : go(k_node<NT, VPT, CAP, false, MULTI>);
 }
 
 hipError_t launch_node(const NodeSet& ns, const PassArgs& a, hipStream_t st) {
   (void)hipGetLastError();   // drop a stale error left by earlier runtime calls of this thread
-  if (ns.chunk <= 1024) return launch_node_as<256, 4, 1024>(ns, a, st);
-  if (ns.chunk <= 4096) return launch_node_as<512, 8, 4096>(ns, a, st);
-  if (ns.chunk <= 8192) return launch_node_as<512, 16, 8192>(ns, a, st);
-  return launch_node_as<512, 32, 12288>(ns, a, st);
+  if (ns.NB > 1) {
+    if (ns.chunk <= 4096) return launch_node_as<512, 8, 4096, true>(ns, a, st);
+    if (ns.chunk <= 8192) return launch_node_as<512, 16, 8192, true>(ns, a, st);
+    return launch_node_as<512, 32, 12288, true>(ns, a, st);
+  }
+  if (ns.chunk <= 1024) return launch_node_as<256, 4, 1024, false>(ns, a, st);
+  if (ns.chunk <= 4096) return launch_node_as<512, 8, 4096, false>(ns, a, st);
+  if (ns.chunk <= 8192) return launch_node_as<512, 16, 8192, false>(ns, a, st);
+  return launch_node_as<512, 32, 12288, false>(ns, a, st);
 }
 
 }  // namespace adacgd

@@ -15,6 +15,42 @@ DIMS = [(3, 1024), (3, 1025), (2, 4097), (2, 8193), (2, 16384), (2, 16385), (2, 
 @pytest.mark.parametrize("n,d,kind", [(n, d, k) for n, d in DIMS for k in ("normal", "ties", "const", "denormal")]
                          + [(130, 18435, "normal")])
 def test_one_launch_step_at_the_edges_of_its_layout(n, d, kind):
+    check_steps(n, d, kind)
+
+
+@pytest.mark.parametrize("n,d,kind", [(n, d, k) for n, d in [(2, 16385), (2, 20481), (3, 65535), (1, 65537), (1, 1 << 20)]
+                                      for k in ("normal", "ties", "const", "sparse")] + [(130, 18435, "normal")])
+def test_one_launch_step_where_blocks_do_not_wait_for_each_other(n, d, kind):
+    """A node whose blocks were not all running at once is done by one of them; between other launches both ways may occur."""
+    check_steps(n, d, kind, _eng().FLAG_NO_WAIT)
+
+
+@pytest.mark.parametrize("n,d", [(3, 20000), (2, 16385)])
+def test_compressed_start_and_differences_where_blocks_do_not_wait_for_each_other(n, d):
+    E = _eng()
+    rng = np.random.default_rng(d)
+    v = [rng.standard_normal((n, d)).astype(np.float32) for _ in range(3)]
+    x0 = _cuda(rng.standard_normal(d).astype(np.float32))
+    base = dict(n=n, d=d, gamma=0.05, x0=x0, worker_levels=[(E.TOPK, d // 50), (E.QUANT, 4), (E.QUANT_BLOCK, (5, 128)), (E.TOPK, d // 10)],
+                master_levels=[(E.QUANT_BLOCK, (4, 256))], zeta_worker=0.3, zeta_master=0.0, seed=9)
+    for diff in (False, True):
+        runs = []
+        for flags in (0, E.FLAG_NO_WAIT):
+            kw = dict(base, flags=flags | E.FLAG_ANY_LEVEL_ORDER)
+            kw.update(dict(grad_mode=E.DIFF_EXTERNAL, init_mode=E.INIT_ZERO) if diff else
+                      dict(grad_mode=E.GRAD_EXTERNAL, grad0=_cuda(v[2]), init_mode=E.INIT_COMPRESSED))
+            eng = E.AdaCGD(**kw)
+            for t in range(4):
+                S = (v[t % 2].astype(np.float64) ** 2).sum(axis=1)
+                eng.step(_cuda(v[t % 2]), *([_cuda(S * 0.9 * 4.0 ** -np.arange(n))] if diff else []))
+            runs.append([eng.state(f) for f in (E.F_X, E.F_GI, E.F_GTILDE, E.F_G, E.F_LEVEL, E.F_MSG_IDX, E.F_MSG_VAL, E.F_QCODES, E.F_QSCALE,
+                                                E.F_LEVEL_HIST)])
+            eng.close()
+        for a, b in zip(*runs):
+            np.testing.assert_array_equal(a, b)
+
+
+def check_steps(n, d, kind, flags=0):
     E = _eng()
     rng = np.random.default_rng(d)
     topk = sorted({1, max(1, d // 1000), max(1, d // 300), max(1, d // 50), max(1, d // 9), max(1, d // 2)})   # more than four sizes
@@ -31,7 +67,7 @@ def test_one_launch_step_at_the_edges_of_its_layout(n, d, kind):
     x0 = rng.standard_normal(d).astype(np.float32)
     orc = O.AdaCGDOracle(**kw)
     orc.init(x0, grads[0], O.INIT_FULLGRAD)
-    eng = E.AdaCGD(grad_mode=E.GRAD_EXTERNAL, x0=_cuda(x0), grad0=_cuda(grads[0]), **kw)
+    eng = E.AdaCGD(grad_mode=E.GRAD_EXTERNAL, x0=_cuda(x0), grad0=_cuda(grads[0]), flags=flags, **kw)
     with until_near_tie(("node", n, d, kind)):
         for t in (1, 2):
             g = (grads[t - 1] + grads[t] * np.float32(0.3)).astype(np.float32)
