@@ -1138,10 +1138,6 @@ template <int NT, int VPT, int CAP, bool MULTI>
 static hipError_t launch_node_as(const NodeSet& ns, const PassArgs& a, hipStream_t st) {
   const size_t lds = sizeof(uint32_t) * (kBins0 + CAP);
   auto go = [&](auto kern) -> hipError_t {
-    if (lds > 64 * 1024) {       // announced to the runtime (for the current device: a host-side setting)
-      const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-      if (e != hipSuccess) return e;
-    }
     hipLaunchKernelGGL(kern, dim3((unsigned)ns.nn * ns.NB), dim3(NT), lds, st, ns, a);
     return hipGetLastError();
   };
