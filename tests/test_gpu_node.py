@@ -50,14 +50,19 @@ def test_compressed_start_and_differences_where_blocks_do_not_wait_for_each_othe
             np.testing.assert_array_equal(a, b)
 
 
-def check_steps(n, d, kind, flags=0):
+@pytest.mark.parametrize("n,d", [(64, 512), (65, 512), (64, 513), (1, 512), (12, 1024)])
+def test_aggregation_inside_and_outside_the_workers_launch(n, d):
+    check_steps(n, d, "sparse", quant=False)
+
+
+def check_steps(n, d, kind, flags=0, quant=True):
     E = _eng()
     rng = np.random.default_rng(d)
     topk = sorted({1, max(1, d // 1000), max(1, d // 300), max(1, d // 50), max(1, d // 9), max(1, d // 2)})   # more than four sizes
     if d > 100000:
         topk = topk[1:4]
     levels = [(O.TOPK, k) for k in topk] + [(O.TOPK, d)]
-    quant = n < 100 and d < 100000
+    quant = quant and n < 100 and d < 100000
     if quant:
         levels += [(O.QUANT, 3), (O.QUANT, 5), (O.QUANT_BLOCK, (4, 512)), (O.QUANT_BLOCK, (2, 64))]
     levels = sorted(levels, key=lambda l: (O.level_alpha(l, d), l[0], str(l[1])))
