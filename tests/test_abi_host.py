@@ -213,8 +213,9 @@ def test_what_blocks_meet_at_is_clear_whatever_launches_failed_before(tmp_path):
 def test_workspace_of_the_gradient_grows_with_the_rows_and_not_with_the_longest_shard(n, d, rows, short):
     """What the gradient needs on top of vectors and level sets (those of a run with one row a shard): tables of the rows,
     two sets of their partial products, and partial sums of at most two rounds of blocks."""
-    need = lambda cnt: E.adacgd_workspace_bytes(_cfg(n=n, d=d, grad_mode=E.GRAD_LOGISTIC,
-                                                     shard_offsets=np.concatenate([[0], np.cumsum(cnt)]).astype(np.int64))[0])
+    def need(cnt):
+        offsets = np.concatenate([[0], np.cumsum(cnt)]).astype(np.int64)          # (the configuration points to it)
+        return E.adacgd_workspace_bytes(_cfg(n=n, d=d, grad_mode=E.GRAD_LOGISTIC, shard_offsets=offsets)[0])
     cnt = np.full(n, short)
     cnt[n // 2] = rows
     parts = (d + 2047) // 2048
