@@ -555,7 +555,9 @@ void shape_logistic(const adacgd_config* cfg, LogisticData& ld) {
 
 // Layout of both sides and of the objective; returns the bytes of workspace.  Several blocks per node that meet need
 // some memory that the general kernels do without (the next iterate's buffer, what they meet at): a configuration that
-// fits the static workspace only without them does without them, whichever workspace it gets.
+// fits the static workspace only without them does without them, whichever of the two workspaces it gets (the caller is told
+// one size for both).  Not where adacgd_init_static refuses it anyway; kernel timing, which it refuses too, must time what
+// runs without it.
 size_t shape_all(const adacgd_config* cfg, const LevelTable& wl, const LevelTable& ml, NodeSet& W, NodeSet& M, LogisticData& ld) {
   const bool two_pass = (cfg->flags & ADACGD_FLAG_TWO_PASS) != 0;
   auto shape = [&](bool chunks) {
@@ -571,7 +573,7 @@ size_t shape_all(const adacgd_config* cfg, const LevelTable& wl, const LevelTabl
     return carve_all(nullptr, cfg, W, M, ld, L);
   };
   const size_t need = shape(true);
-  if (need <= (size_t)ADACGD_STATIC_WORKSPACE_BYTES) return need;
+  if (need <= (size_t)ADACGD_STATIC_WORKSPACE_BYTES || logistic_mode(cfg->grad_mode) || (cfg->flags & ADACGD_FLAG_OVERLAP)) return need;
   const size_t less = shape(false);
   return less <= (size_t)ADACGD_STATIC_WORKSPACE_BYTES ? less : shape(true);
 }

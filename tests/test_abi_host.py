@@ -169,6 +169,16 @@ def test_a_configuration_near_the_static_workspace_keeps_fitting_it():
         _cfg(n=8, d=560000, **dict(levels, flags=E.FLAG_RETAIN_EXT | E.FLAG_TWO_PASS))[0])
 
 
+@pytest.mark.parametrize("kw", [dict(flags=E.FLAG_OVERLAP | E.FLAG_RETAIN_EXT),
+                                dict(grad_mode=E.GRAD_LOGISTIC, d=455000, shard_offsets=np.arange(9, dtype=np.int64))])
+def test_the_static_workspace_does_not_decide_where_it_cannot_be_used(kw):
+    """The kernels that need a little more memory are taken between its size and theirs (65.8 and 68.0 MB, 66.6 and 68.4 MB)."""
+    near = dict(dict(n=8, d=575000, worker_levels=[(E.QUANT, 4)], master_levels=[(E.QUANT, 4)]), **kw)
+    fast = E.adacgd_workspace_bytes(_cfg(**near)[0])
+    slow = E.adacgd_workspace_bytes(_cfg(**dict(near, flags=near.get("flags", 0) | E.FLAG_TWO_PASS))[0])
+    assert slow <= E.STATIC_WORKSPACE_BYTES < fast, (slow, fast)
+
+
 def test_what_blocks_meet_at_is_clear_whatever_launches_failed_before(tmp_path):
     """The two sets of polled memory in a model of the device: a launch needs its set clear, leaves it used and clears the
     other; a launch may fail (before it ran, or after), be captured, and captured launches be replayed."""
