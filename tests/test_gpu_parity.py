@@ -145,7 +145,7 @@ def make_vectors(rng, n, d, kind):
     raise ValueError(kind)
 
 
-SHAPES = [
+SHAPES = [                   # (what the general kernels make of them; the first two are several blocks in the one-launch step)
     (3, 3 * 8192 + 516),     # several tiles + ragged tail, 16-byte vector path
     (2, 2 * 8192 + 517),     # d % 4 != 0: scalar path
     (5, 1000),               # one partial tile
@@ -156,9 +156,10 @@ SHAPES = [
 
 @pytest.mark.parametrize("kind", ["normal", "ties", "heavy", "sparse", "denormal", "const"])
 @pytest.mark.parametrize("n,d,general", [(n, d, False) for n, d in SHAPES] +
-                         [(5, 1000, True), (1, 1, True), (3, 4096, False), (2, 4095, True)])
+                         [(5, 1000, True), (1, 1, True), (3, 4096, False), (2, 4095, True)] +
+                         [(3, 3 * 8192 + 516, True), (2, 2 * 8192 + 517, True), (2, 8192, True)])
 def test_compression_step_bit_exact_external_gradients(n, d, kind, general):
-    """`general`: short vectors through the general two-pass kernels instead of the one-block kernel."""
+    """`general`: through the general two-pass kernels instead of the one-launch step (which all of these lengths take)."""
     E = _eng()
     rng = np.random.default_rng(1000 + d + len(kind))
     Ks = sorted({max(1, min(d, k)) for k in (1, 7, d // 50, d // 8, d // 2, d)})
@@ -208,10 +209,12 @@ def test_retained_external_gradient_pointer_matches_copy():
         assert np.array_equal(bits(a), bits(b))
 
 
+@pytest.mark.parametrize("general", [False, True])
 @pytest.mark.parametrize("n,d", [(4, 3 * 8192 + 40), (3, 5003), (6, 3001)])
-def test_difference_mode_with_quantiser_levels_bit_exact(n, d):
+def test_difference_mode_with_quantiser_levels_bit_exact(n, d, general):
     """Caller-supplied difference vectors and trigger right-hand sides; mixed Top-K and
-    b-bit levels ordered by contraction parameter; every branch of the cascade occurs."""
+    b-bit levels ordered by contraction parameter; every branch of the cascade occurs; in the
+    one-launch step and in the general kernels."""
     E = _eng()
     wk = W.kernel_stress(seed=3, n=n, d=d)
     wk.worker_levels = by_alpha(wk.worker_levels, d)
@@ -222,7 +225,7 @@ def test_difference_mode_with_quantiser_levels_bit_exact(n, d):
     orc.init(x0, None, O.INIT_ZERO)
     eng = E.AdaCGD(n=n, d=d, gamma=0.1, worker_levels=wk.worker_levels, zeta_worker=1.0,
                    master_levels=wk.master_levels, zeta_master=0.0, grad_mode=E.DIFF_EXTERNAL,
-                   init_mode=E.INIT_ZERO, x0=_cuda(x0), seed=seed)
+                   init_mode=E.INIT_ZERO, x0=_cuda(x0), seed=seed, flags=E.FLAG_TWO_PASS if general else 0)
     seen = set()
     with until_near_tie(("diff", n, d)):
         for t in range(8):
@@ -670,12 +673,12 @@ def test_many_workers_small_dimension():
     assert (orc.level_hist_w > 0).sum() >= 3
 
 
-@pytest.mark.parametrize("n,d,quant", [(4, 900, True), (3, 20000 + 13, True), (2, 140 * 8192 + 36, False),
-                                       (3, 2 * 8192 + 517, False)])
-def test_general_triggers_bit_exact(n, d, quant):
+@pytest.mark.parametrize("n,d,quant,general", [(4, 900, True, False), (3, 20000 + 13, True, False), (2, 140 * 8192 + 36, False, False),
+                                               (3, 2 * 8192 + 517, False, False), (3, 20000 + 13, True, True), (3, 2 * 8192 + 517, False, True)])
+def test_general_triggers_bit_exact(n, d, quant, general):
     """Conditions of the cascade from the wider family err_j <= zeta_j D + eta_j S (Section 4.2,
-    Lemma 2 allow any), different at every position, on both sides; short vectors (one-block
-    kernel), the two-pass sequence with a quantiser level, and the one-pass sequence."""
+    Lemma 2 allow any), different at every position, on both sides; the one-launch step, the
+    two-pass sequence (`general`; with a quantiser level), and the one-pass sequence."""
     E = _eng()
     rng = np.random.default_rng(31 * d + n)
     Ks = sorted({max(1, min(d, k)) for k in (2, d // 100, d // 16, d // 3)})
@@ -699,7 +702,7 @@ def test_general_triggers_bit_exact(n, d, quant):
         orc = O.AdaCGDOracle(**kw)
         orc.init(x0, grads[0], O.INIT_ZERO)
         eng = E.AdaCGD(grad_mode=E.GRAD_EXTERNAL, init_mode=E.INIT_ZERO, x0=_cuda(x0), grad0=_cuda(grads[0]),
-                       flags=E.FLAG_ANY_LEVEL_ORDER, **kw)
+                       flags=E.FLAG_ANY_LEVEL_ORDER | (E.FLAG_TWO_PASS if general else 0), **kw)
         with until_near_tie((n, d, trial)):
             for t in range(1, steps + 1):
                 res, rm = orc.step(grads=grads[t])
@@ -799,8 +802,8 @@ def test_trajectory_sparse_features_reduced():
     eng.close()
 
 
-@pytest.mark.parametrize("n,d", [(4, 700), (3, 2 * 8192 + 516), (2, 130 * 8192)])
-def test_compressed_initial_estimators_bit_exact(n, d):
+@pytest.mark.parametrize("n,d,general", [(4, 700, False), (3, 2 * 8192 + 516, False), (2, 130 * 8192, False), (3, 2 * 8192 + 516, True)])
+def test_compressed_initial_estimators_bit_exact(n, d, general):
     """g~_i^0 = Top-K(grad f_i(x^0)) with the last level's K (the CLAG / EF21 start), then a few steps."""
     E = _eng()
     rng = np.random.default_rng(d + n)
@@ -819,7 +822,7 @@ def test_compressed_initial_estimators_bit_exact(n, d):
     orc = O.AdaCGDOracle(n=n, d=d, gamma=0.05, worker_levels=wl, zeta_worker=1.0)
     orc.init(x0, grads[0], O.INIT_COMPRESSED)
     eng = E.AdaCGD(n=n, d=d, gamma=0.05, worker_levels=wl, zeta_worker=1.0, grad_mode=E.GRAD_EXTERNAL,
-                   init_mode=E.INIT_COMPRESSED, x0=_cuda(x0), grad0=_cuda(grads[0]))
+                   init_mode=E.INIT_COMPRESSED, x0=_cuda(x0), grad0=_cuda(grads[0]), flags=E.FLAG_TWO_PASS if general else 0)
     assert np.array_equal(bits(eng.state(E.F_GI)), bits(orc.gi))
     assert np.array_equal(bits(eng.state(E.F_GTILDE)), bits(orc.gt))
     assert np.array_equal(bits(eng.state(E.F_G)), bits(orc.g))
@@ -859,14 +862,13 @@ def test_sparse_rows_degenerate_shapes():
 
 
 @pytest.mark.parametrize("master", [True, False])
-@pytest.mark.parametrize("n", [5, 70])
-def test_overlap_mode_short_vectors(n, master):
-    """Overlap mode on the one-block path (with and without the aggregation done by the workers' launch,
-    with and without a master compressor): same results as the oracle, step by step."""
+@pytest.mark.parametrize("n,d", [(5, 700), (70, 700), (5, 20000), (12, 65537)])
+def test_overlap_mode_short_vectors(n, d, master):
+    """Overlap mode on the one-launch step (one block a node, and several that meet on both streams at once; both
+    aggregations of Top-K messages; with and without a master compressor): same results as the oracle, step by step."""
     E = _eng()
-    d = 700
     rng = np.random.default_rng(n)
-    wl = [(O.TOPK, 3), (O.TOPK, 40), (O.TOPK, 300)]
+    wl = [(O.TOPK, 3), (O.TOPK, 40), (O.TOPK, 300)] + ([(O.QUANT, 4), (O.TOPK, d // 3)] if d == 20000 else [])
     ml = [(O.TOPK, 50)] if master else []
     grads = [rng.standard_normal((n, d)).astype(np.float32)]
     for t in range(8):
@@ -876,8 +878,8 @@ def test_overlap_mode_short_vectors(n, master):
     orc.init(x0, grads[0], O.INIT_FULLGRAD)
     arrs = [_cuda(g) for g in grads]
     eng = E.AdaCGD(n=n, d=d, gamma=0.05, worker_levels=wl, zeta_worker=1.0, master_levels=ml, zeta_master=0.5,
-                   grad_mode=E.GRAD_EXTERNAL, x0=_cuda(x0), grad0=arrs[0], flags=E.FLAG_OVERLAP | E.FLAG_RETAIN_EXT)
-    with until_near_tie(("overlap, short", n, master)):
+                   grad_mode=E.GRAD_EXTERNAL, x0=_cuda(x0), grad0=arrs[0], flags=E.FLAG_OVERLAP | E.FLAG_RETAIN_EXT | E.FLAG_ANY_LEVEL_ORDER)
+    with until_near_tie(("overlap, short", n, d, master)):
         for t in range(1, 9):
             res, rm = orc.step(grads=grads[t])
             eng.step(arrs[t])
@@ -890,7 +892,7 @@ def test_overlap_mode_short_vectors(n, master):
 
 
 @pytest.mark.parametrize("n,d,flags", [(4, 900, 0), (3, 3 * 8192 + 516, 0), (2, 130 * 8192, 0), (3, 20000, "retain"),
-                                       (3, 64 * 320, "block_rank")])
+                                       (3, 64 * 320, "block_rank"), (3, 3 * 8192 + 516, "two_pass")])
 def test_checkpoint_and_restore_continue_bit_for_bit(n, d, flags):
     """State copied out after three steps and restored into a context that was initialised from other
     data continues exactly like the uninterrupted run (mixed level set: the Philox counter is part of it)."""
@@ -907,7 +909,7 @@ def test_checkpoint_and_restore_continue_bit_for_bit(n, d, flags):
         grads[t] = (grads[t - 1] + grads[t] * np.float32(0.3)).astype(np.float32)
     arrs = [_cuda(g) for g in grads]
     x0 = rng.standard_normal(d).astype(np.float32)
-    fl = E.FLAG_RETAIN_EXT if flags == "retain" else E.FLAG_ANY_LEVEL_ORDER if flags == "block_rank" else 0
+    fl = {"retain": E.FLAG_RETAIN_EXT, "block_rank": E.FLAG_ANY_LEVEL_ORDER, "two_pass": E.FLAG_TWO_PASS}.get(flags, 0)
     kw = dict(n=n, d=d, gamma=0.05, worker_levels=wl, zeta_worker=1.0, master_levels=ml, zeta_master=0.3,
               grad_mode=E.GRAD_EXTERNAL, seed=9, flags=fl)
     a = E.AdaCGD(x0=_cuda(x0), grad0=arrs[0], **kw)
@@ -960,10 +962,11 @@ def test_stored_trajectory_from_the_engine():
     eng.close()
 
 
+@pytest.mark.parametrize("general", [False, True])
 @pytest.mark.parametrize("bits_", [(4,), (2, 8), (2, 4, 8), (2, 3, 4, 6, 8)])
-def test_one_to_five_quantiser_levels_bit_exact(bits_):
-    """Level sets with one, two, three (kernels specialised on the count) and five (general kernel)
-    quantiser levels next to two Top-K sizes, on the 16-byte vector path."""
+def test_one_to_five_quantiser_levels_bit_exact(bits_, general):
+    """Level sets with one, two, three and five quantiser levels next to two Top-K sizes: in the one-launch step (three at a
+    time) and in the general kernels (one, two and three have kernels of their own), on their 16-byte vector path."""
     E = _eng()
     n, d = 4, 3 * 8192 + 516
     rng = np.random.default_rng(len(bits_))
@@ -976,8 +979,9 @@ def test_one_to_five_quantiser_levels_bit_exact(bits_):
               seed=77)
     orc = O.AdaCGDOracle(**kw)
     orc.init(x0, grads[0], O.INIT_ZERO)
-    eng = E.AdaCGD(grad_mode=E.GRAD_EXTERNAL, init_mode=E.INIT_ZERO, x0=_cuda(x0), grad0=_cuda(grads[0]), **kw)
-    with until_near_tie(("quantiser levels", bits_)):
+    eng = E.AdaCGD(grad_mode=E.GRAD_EXTERNAL, init_mode=E.INIT_ZERO, x0=_cuda(x0), grad0=_cuda(grads[0]),
+                   flags=E.FLAG_TWO_PASS if general else 0, **kw)
+    with until_near_tie(("quantiser levels", bits_, general)):
         for t in range(1, 5):
             res, rm = orc.step(grads=grads[t])
             eng.step(_cuda(grads[t]))
@@ -1073,12 +1077,13 @@ def test_aggregation_with_wide_exponent_spread(dense):
 
 
 @pytest.mark.parametrize("n,d,flags", [(4, 3 * 8192 + 516, 0), (3, 2 * 8192 + 517, 0), (5, 1000, 0), (2, 4095, 0),
-                                       (3, 1000, "two_pass"), (2, 130, 0), (2, 5 * 8192, 0)])
+                                       (3, 1000, "two_pass"), (2, 130, 0), (2, 5 * 8192, 0),
+                                       (4, 3 * 8192 + 516, "two_pass"), (3, 2 * 8192 + 517, "two_pass"), (2, 5 * 8192, "two_pass")])
 @pytest.mark.parametrize("blocks", [((4, 256),), ((8, 64), (2, 2048)), ((4, 128), (4, 1024), (3, 512))])
 def test_block_wise_quantiser_levels_bit_exact(n, d, flags, blocks):
     """Level sets with block-wise b-bit quantisers (one max-norm scale per block of B coordinates) next to
-    Top-K levels and a plain quantiser, on the 16-byte and the scalar path, the one-block kernel and the
-    general kernels, worker and master side: levels, errors, estimators, codes and per-block scales."""
+    Top-K levels and a plain quantiser, in the one-launch step (one block a node and several) and on the 16-byte and the
+    scalar path of the general kernels, worker and master side: levels, errors, estimators, codes and per-block scales."""
     E = _eng()
     rng = np.random.default_rng(d + 7 * len(blocks))
     wl = [(O.TOPK, max(1, d // 300)), (O.TOPK, max(2, d // 20))] + [(O.QUANT_BLOCK, bb) for bb in blocks]
