@@ -55,14 +55,52 @@ def test_aggregation_inside_and_outside_the_workers_launch(n, d):
     check_steps(n, d, "sparse", quant=False)
 
 
-def check_steps(n, d, kind, flags=0, quant=True):
+@pytest.mark.parametrize("n,d", [(1, 300001), (2, 262147)])
+def test_quantisers_over_many_blocks(n, d):
+    check_steps(n, d, "normal", quant=True)
+
+
+@pytest.mark.parametrize("no_wait", [False, True])
+@pytest.mark.parametrize("what", [["inf"], ["nan"], ["inf", "nan", "-nan"], ["zeros"]])
+def test_infinities_and_nan_between_blocks_that_meet(what, no_wait):
+    """What the blocks of a node leave for each other may be infinite, not a number or zero: results are those of the general
+    kernels, bit for bit (NaN where they are NaN)."""
+    E = _eng()
+    n, d = 3, 20483
+    rng = np.random.default_rng(len(what))
+    v = [rng.standard_normal((n, d)).astype(np.float32) for _ in range(2)]
+    for a in v:
+        for w in what:
+            if w == "zeros":
+                a[:2] = 0.0
+            else:
+                a[0, rng.integers(0, d, 5)] = {"inf": np.inf, "nan": np.nan, "-nan": -np.float32(np.nan)}[w]
+                a[1, 4095] = -np.inf if w == "inf" else np.nan
+    out = []
+    for flags in (E.FLAG_TWO_PASS, E.FLAG_NO_WAIT if no_wait else 0):
+        eng = E.AdaCGD(n=n, d=d, gamma=0.05, worker_levels=[(E.TOPK, 3), (E.QUANT, 4), (E.QUANT_BLOCK, (4, 256)), (E.TOPK, 900), (E.TOPK, d)],
+                       zeta_worker=1.0, master_levels=[(E.TOPK, 100)], zeta_master=0.0, grad_mode=E.DIFF_EXTERNAL, init_mode=E.INIT_ZERO,
+                       x0=_cuda(np.zeros(d, np.float32)), seed=3, flags=flags | E.FLAG_ANY_LEVEL_ORDER)
+        for a, D in zip(v, (1e-3, 1e9)):
+            eng.step(_cuda(a), _cuda(np.full(n, D)))
+            out.append([eng.state(f) for f in (E.F_LEVEL, E.F_SQNORM, E.F_ERR, E.F_MSG_COUNT, E.F_MSG_IDX, E.F_MSG_VAL, E.F_GI, E.F_GTILDE, E.F_G, E.F_X)])
+        eng.close()
+    for a, b in zip(out[:2], out[2:]):
+        for f, (x, y) in enumerate(zip(a, b)):
+            if x.dtype == np.float64:
+                np.testing.assert_allclose(x, y, rtol=1e-12, err_msg=str(f))
+            else:
+                np.testing.assert_array_equal(x, y, err_msg=str(f))
+
+
+def check_steps(n, d, kind, flags=0, quant=None):
     E = _eng()
     rng = np.random.default_rng(d)
     topk = sorted({1, max(1, d // 1000), max(1, d // 300), max(1, d // 50), max(1, d // 9), max(1, d // 2)})   # more than four sizes
     if d > 100000:
         topk = topk[1:4]
     levels = [(O.TOPK, k) for k in topk] + [(O.TOPK, d)]
-    quant = quant and n < 100 and d < 100000
+    quant = n < 100 and d < 100000 if quant is None else quant
     if quant:
         levels += [(O.QUANT, 3), (O.QUANT, 5), (O.QUANT_BLOCK, (4, 512)), (O.QUANT_BLOCK, (2, 64))]
     levels = sorted(levels, key=lambda l: (O.level_alpha(l, d), l[0], str(l[1])))
