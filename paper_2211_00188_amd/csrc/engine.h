@@ -31,11 +31,8 @@ constexpr int kGradCols = 2048;
 constexpr int kGradRows = 16;           // rows a group of wavefronts holds at a time
 constexpr int kGradFold = 16;           // partial sums that one block adds up
 __host__ __device__ constexpr int grad_col_waves(int64_t cols) { return cols <= 256 ? 1 : cols <= 512 ? 2 : cols <= 1024 ? 4 : 8; }
-// The workers' launch also aggregates where they are at most kServeWorkers with at most kServeDim coordinates: one block adds up
-// what it reads back, instead of one more launch.  Per step, with and without: 10 x 300 11 us (12), 64 x 300 14.8 (16.5);
-// 10 x 1000 13.5 (12.1), 50 x 1000 20 (16), 10 x 4096 19.7 (13.3).
-constexpr int kServeWorkers = 64;
-constexpr int kServeDim = 512;
+constexpr int kServeWorkers = 64;       // it also aggregates when there are at most this many workers of one chunk each
+constexpr int64_t kServeMax = 65536;    // ... and at most this many worker-coordinates (one block adds them up)
 constexpr int kSeg = 64;                // block-wise quantiser scales are built from maxima over segments of 64 coordinates
 constexpr int kSegPerGroup = kWaveTile / kSeg;   // 32
 

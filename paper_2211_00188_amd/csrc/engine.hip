@@ -212,7 +212,7 @@ void carve_nodeset(Carver& c, NodeSet& ns) {
   ns.nseg = (int)((ns.d + kSeg - 1) / kSeg);
   ns.segmax = ns.lv.nqb && multi ? c.take<uint32_t>(nn * (size_t)ns.nseg) : nullptr;
   ns.qbscale = ns.lv.nqb ? c.take<float>(nn * (size_t)ns.nseg) : nullptr;
-  ns.dense = ns.small && nq == 0 && ns.lv.nr == 0 && nn <= kServeWorkers && ns.d <= kServeDim ? c.take<float>(nn * (size_t)ns.d) : nullptr;
+  ns.dense = ns.small && nq == 0 && ns.NB == 1 && nn <= kServeWorkers && (int64_t)nn * ns.d <= kServeMax ? c.take<float>(nn * (size_t)ns.d) : nullptr;
   ns.accbuf = (nq || ns.lv.nr) ? c.take<double>((size_t)ns.d) : nullptr;
   if (ns.lv.nr) {
     const size_t cc = (size_t)ns.lv.rcols * ns.lv.rcols, nr = ns.lv.nr;
@@ -713,8 +713,8 @@ int one_step(adacgd_ctx* c, const float* ext, const double* extD) {
   } else if ((rc = timed(c, ADACGD_K_XUPDATE, [&] { return launch_xupdate(c->x, c->x, c->g(), c->gamma, c->d, c->cs); }))) {
     return rc;
   }
-  // Short vectors, few workers, Top-K messages only: the workers' launch also does the aggregation (its last block), and
-  // the kernel that finishes g the next iterate update.
+  // Short vectors, few workers, Top-K messages only: the one-block kernel of the workers also does the
+  // aggregation (its last block), and the kernel that finishes g the next iterate update.
   const bool serve = c->W.dense != nullptr && !ov;
   PassArgs a{};
   a.h = c->gi;
