@@ -231,3 +231,15 @@ def test_workspace_of_the_gradient_grows_with_the_rows_and_not_with_the_longest_
     parts = (d + 2047) // 2048
     bound = int(cnt.sum()) * (4 + 16 * parts) + 2 * 4096 * 2048 * 8 // 8 + 16 * (n + 1024) + (1 << 16)
     assert need(cnt) - need(np.ones(n)) <= bound, (need(cnt), need(np.ones(n)), bound)
+
+
+def test_wide_buffer_stores_take_no_scalar_offset():
+    """A 16-byte buffer store with its offset in a scalar register may write what the next instruction puts into its data
+    registers: the compiler takes such a store for safe and leaves no wait states behind it."""
+    csrc = os.path.join(ROOT, "paper_2211_00188_amd", "csrc")
+    calls = []
+    for name in os.listdir(csrc):
+        calls += re.findall(r"raw_buffer_store_b(?:96|128)\(([^;]*)\);", open(os.path.join(csrc, name)).read())
+    assert calls
+    for args in calls:
+        assert args.split(",")[-2].strip() == "0", args
