@@ -31,8 +31,12 @@ constexpr int kGradCols = 2048;
 constexpr int kGradRows = 16;           // rows a group of wavefronts holds at a time
 constexpr int kGradFold = 16;           // partial sums that one block adds up
 __host__ __device__ constexpr int grad_col_waves(int64_t cols) { return cols <= 256 ? 1 : cols <= 512 ? 2 : cols <= 1024 ? 4 : 8; }
-constexpr int kServeWorkers = 64;       // it also aggregates when there are at most this many workers of one chunk each
-constexpr int64_t kServeMax = 65536;    // ... and at most this many worker-coordinates (one block adds them up)
+// Top-K messages of at most kServeWorkers workers of one chunk each are also written out as whole vectors, which the
+// aggregation reads coordinate by coordinate (k_aggregate_short): up to kServeDim coordinates the workers' launch does that
+// itself (its last block), which saves a launch.  A step inside the launch and with a launch of its own: 10 x 300 11 us and
+// 12, 64 x 300 14.8 and 16.5; 10 x 1000 13.5 and 12, 50 x 1000 20 and 13.
+constexpr int kServeWorkers = 64;
+constexpr int kServeDim = 512;
 constexpr int kSeg = 64;                // block-wise quantiser scales are built from maxima over segments of 64 coordinates
 constexpr int kSegPerGroup = kWaveTile / kSeg;   // 32
 
@@ -141,8 +145,8 @@ struct NodeSet {
   uint32_t* ticket;     // [2][kCounterStride] next (node, chunk) to be taken by a block; zero at init; null up to kNodeParts blocks
   uint32_t* alone;      // [nn] blocks that have left a node that was given up (NB > 1); zero between launches
   uint32_t polls;       // polls before a node is given up
-  float* dense;         // [nn][d] C(v) of every node that sent a message, for the aggregation inside the one-block kernel
-                        //         (null: the aggregation is a kernel of its own)
+  float* dense;         // [nn][d] C(v) of every node that sent a message, for k_aggregate_short and the aggregation inside
+                        //         the workers' launch (null: the messages themselves are added)
   double* accbuf;       // [d] fp64 sums of the sparse messages (only with quantiser levels)
   // Rank-K levels (allocated only when the level set has any; c = lv.rcols, nr = lv.nr)
   int GR;               // blocks per node of the Rank-K kernels
@@ -172,10 +176,11 @@ struct PassArgs {
   uint32_t parity;     // which of the two sets of NodeSet::meet this launch uses (alternates)
   int assign;          // 1 = the compressed start g~_i^0 = C_m(grad f_i(x^0)) (Section 2.3): h holds zeros and receives
                        // the selected values themselves, h[l] = C(v)[l], instead of fl(h[l] + C(v)[l]) (Top-K only)
-  // Server work that the one-block kernel for short vectors can take over (each part optional):
-  // the block that finishes last adds every node's message to the server vector, g~_new =
-  // fl(g~_old + sum / nn); and the iterate update that opens the next step, x_next = fl(x - gamma g),
-  // with g = g~_new when it follows the aggregation, else g = the updated estimator of node 0 (the master).
+  int to_dense;        // one-launch step: C(v) is written to NodeSet::dense as well
+  // Server work that the one-launch step can take over (each part optional): the block that finishes last adds every node's
+  // message to the server vector, g~_new = fl(g~_old + sum / nn); and the iterate update that opens the next step,
+  // x_next = fl(x - gamma g), with g = g~_new when it follows the aggregation, else g = the updated estimator of
+  // node 0 (the master).
   const float* agg_old;
   float* agg_new;
   const float* xu_x;
@@ -265,7 +270,7 @@ struct IterateUpdate {
   double gamma = 0.0;
 };
 hipError_t launch_aggregate(const NodeSet& ws, const float* gt_old, float* gt_new, const IterateUpdate& xu,
-                            hipStream_t st);
+                            bool from_dense, hipStream_t st);
 hipError_t launch_fill_u32(uint32_t* p, uint32_t v, size_t count, hipStream_t st);
 hipError_t launch_copy_f32(float* dst, const float* src, size_t count, hipStream_t st);
 hipError_t launch_grad(const LogisticData& ld, const float* x, float* grads, int64_t d, hipStream_t st);

@@ -212,7 +212,7 @@ void carve_nodeset(Carver& c, NodeSet& ns) {
   ns.nseg = (int)((ns.d + kSeg - 1) / kSeg);
   ns.segmax = ns.lv.nqb && multi ? c.take<uint32_t>(nn * (size_t)ns.nseg) : nullptr;
   ns.qbscale = ns.lv.nqb ? c.take<float>(nn * (size_t)ns.nseg) : nullptr;
-  ns.dense = ns.small && nq == 0 && ns.NB == 1 && nn <= kServeWorkers && (int64_t)nn * ns.d <= kServeMax ? c.take<float>(nn * (size_t)ns.d) : nullptr;
+  ns.dense = ns.small && nq == 0 && ns.lv.nr == 0 && ns.NB == 1 && nn <= kServeWorkers ? c.take<float>(nn * (size_t)ns.d) : nullptr;
   ns.accbuf = (nq || ns.lv.nr) ? c.take<double>((size_t)ns.d) : nullptr;
   if (ns.lv.nr) {
     const size_t cc = (size_t)ns.lv.rcols * ns.lv.rcols, nr = ns.lv.nr;
@@ -713,9 +713,9 @@ int one_step(adacgd_ctx* c, const float* ext, const double* extD) {
   } else if ((rc = timed(c, ADACGD_K_XUPDATE, [&] { return launch_xupdate(c->x, c->x, c->g(), c->gamma, c->d, c->cs); }))) {
     return rc;
   }
-  // Short vectors, few workers, Top-K messages only: the one-block kernel of the workers also does the
-  // aggregation (its last block), and the kernel that finishes g the next iterate update.
-  const bool serve = c->W.dense != nullptr && !ov;
+  // Short vectors, few workers, Top-K messages only: the aggregation reads C(v) as whole vectors, and where these are very
+  // short the workers' launch also does it (its last block); the kernel that finishes g does the next iterate update.
+  const bool dense = c->W.dense != nullptr && !ov, serve = dense && c->d <= kServeDim;
   PassArgs a{};
   a.h = c->gi;
   a.seed = c->seed;
@@ -737,6 +737,7 @@ int one_step(adacgd_ctx* c, const float* ext, const double* extD) {
   }
   float* gt_old = c->gt[c->cur];
   float* gt_new = c->gt[c->cur ^ 1];
+  a.to_dense = dense;
   if (serve) {
     a.agg_old = gt_old;
     a.agg_new = gt_new;
@@ -768,7 +769,7 @@ int one_step(adacgd_ctx* c, const float* ext, const double* extD) {
       xu.out = c->x_next;
       xu.gamma = c->gamma;
     }
-    if ((rc = timed(c, ADACGD_K_AGGREGATE, [&] { return launch_aggregate(c->W, gt_old, gt_new, xu, c->cs); }))) return rc;
+    if ((rc = timed(c, ADACGD_K_AGGREGATE, [&] { return launch_aggregate(c->W, gt_old, gt_new, xu, dense, c->cs); }))) return rc;
   }
   if (ov) {
     HIPCHK(c, hipEventRecord(c->ev_agg, c->st));

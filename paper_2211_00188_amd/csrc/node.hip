@@ -106,7 +106,6 @@ __device__ __forceinline__ void wave_scan_table(uint32_t* t, int n, uint32_t lan
 __device__ __forceinline__ uint32_t hist_slot(uint32_t bin) { return ((bin & 31u) << 7) | (bin >> 5); }
 __device__ __forceinline__ uint32_t hist_bin(uint32_t slot) { return ((slot & 127u) << 5) | (slot >> 7); }
 
-constexpr int kServeVpt = 32;        // the launch can aggregate up to this many values per thread
 constexpr int kBatch = 4;            // Top-K sizes whose second and third digits are resolved side by side
 constexpr int kErrBatch = 3;         // quantiser levels evaluated in one pass over the values
 
@@ -157,7 +156,7 @@ __global__ __launch_bounds__(NT, NT >= 512 ? 4 : 1) void k_node(NodeSet ns, Pass
   const int node = (int)(blk / (uint32_t)NB), part = (int)(blk % (uint32_t)NB);
   const uint32_t c0 = (uint32_t)part * (uint32_t)ns.chunk;           // first coordinate of the chunk
   const uint32_t len = min((uint32_t)ns.chunk, d - c0);
-  const bool serve = VPT <= kServeVpt && a.agg_new != nullptr;     // this launch also aggregates: C(v) goes to ns.dense, coherently
+  const bool serve = NT * VPT <= 2 * kServeDim && a.agg_new != nullptr;     // this launch also aggregates: ns.dense is written coherently
   const size_t row = (size_t)node * d + c0;
   const bool diff = a.diff != 0;
   const Buf xb = make_buf(a.x + row, 4 * len), hb = make_buf(a.h + row, 4 * len);
@@ -1041,11 +1040,17 @@ __global__ __launch_bounds__(NT, NT >= 512 ? 4 : 1) void k_node(NodeSet ns, Pass
         }
         buf_store4(hb, off0, q * NT * 16, hq);
       }
-      if (serve) {
-        float* __restrict__ dense = ns.dense + row;
+      if (!MULTI && a.to_dense) {
+        float cv[4];
 #pragma unroll
-        for (int c = 0; c < 4; ++c)
-          if (l0 + c < len) st_coherent(&dense[l0 + c], ((f >> c) & 1u) ? v[q * 4 + c] : 0.f);
+        for (int c = 0; c < 4; ++c) cv[c] = ((f >> c) & 1u) ? v[q * 4 + c] : 0.f;
+        if (serve) {
+#pragma unroll
+          for (int c = 0; c < 4; ++c)
+            if (l0 + c < len) st_coherent(&ns.dense[row + l0 + c], cv[c]);
+        } else {
+          buf_store4(make_buf(ns.dense + row, 4 * len), off0, q * NT * 16, cv);
+        }
       }
     }
   } else if (QUANT && q_sel >= 0) {
@@ -1111,7 +1116,7 @@ __global__ __launch_bounds__(NT, NT >= 512 ? 4 : 1) void k_node(NodeSet ns, Pass
   }
   if (!serve) return;
 
-  // ---- server aggregation by the block that finishes last (Top-K messages of at most 64 workers, NB = 1): every
+  // ---- server aggregation by the block that finishes last (Top-K messages of few workers, NB = 1): every
   // coordinate's sum in ascending worker index; what a worker does not send adds +0, which changes no sum ----
   if (!arrive_last(ns.done, (uint32_t)ns.nn, (uint32_t)node, &s_flag)) return;
   const uint64_t senders = ballot(lane < (uint32_t)ns.nn && ld_coherent(&ns.sel_slot[lane < (uint32_t)ns.nn ? lane : 0]) >= 0);

@@ -50,7 +50,7 @@ def test_compressed_start_and_differences_where_blocks_do_not_wait_for_each_othe
             np.testing.assert_array_equal(a, b)
 
 
-@pytest.mark.parametrize("n,d", [(64, 512), (65, 512), (64, 513), (1, 512), (12, 1024)])
+@pytest.mark.parametrize("n,d", [(64, 512), (65, 512), (64, 513), (1, 512), (12, 1024), (9, 16384), (5, 16001), (33, 3001)])
 def test_aggregation_inside_and_outside_the_workers_launch(n, d):
     check_steps(n, d, "sparse", quant=False)
 
