@@ -396,7 +396,7 @@ def extra_small_logistic(E, W, torch, wl, steps, sparse_rows=False):
             "steps": steps, "ms_per_step": dt / steps * 1e3, "steps_per_sec": steps / dt,
             "zeta_worker": wl.zeta_worker, "kernel_launches_per_step": launches,
             "level_histogram_skip_then_levels_since_init": [int(v) for v in hist],
-            "note": "a step is four short dependent kernels: latency-bound, no roofline applies"}
+            "note": "a step is a few short dependent kernels (kernel_launches_per_step): latency-bound, no roofline applies"}
 
 
 def main():

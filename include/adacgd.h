@@ -276,8 +276,8 @@ enum adacgd_field {
  * then holds the second scan that repairs a failed estimate (idle otherwise).  Other vectors run
  * scan + filter as two passes.  Without Rank-K levels, vectors of at most 65536 coordinates -- and
  * longer ones, up to 2^20, if there are few nodes -- are handled by one kernel that does the whole
- * compression step of all nodes, timed in the scan slot; with few, short messages that launch also
- * aggregates (the aggregate slot stays empty), and the launch that finishes g also writes the next
+ * compression step of all nodes, timed in the scan slot; up to 512 coordinates, with at most 64
+ * workers and Top-K levels only, that launch also aggregates (the aggregate slot stays empty), and the launch that finishes g also writes the next
  * iterate (the xupdate slot stays empty); so does the aggregation of any vector length when there
  * is no master compressor (g is g~ then). */
 enum adacgd_kernel {

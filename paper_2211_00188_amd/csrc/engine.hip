@@ -244,11 +244,14 @@ void shape_nodeset(NodeSet& ns, int nn, int64_t d, bool force_two_pass, bool chu
   // 1/32 sample to be informative, and a candidate set that is a minor part of the vector.
   ns.onepass = (!force_two_pass && ns.lv.nq == 0 && ns.lv.p > 0 && d % 4 == 0 && ns.tiles >= 128 &&
                 4 * (int64_t)ns.Kcap <= d) ? 1 : 0;
-  // One launch for the whole step: one block per node where the vector fits its registers; else several blocks that
-  // meet, in the smallest chunks with which all blocks of the launch are resident together (more blocks read faster
-  // and meet as often).  Launches that need more than one round of blocks stay with it up to d = 65536, where the
-  // general sequence is a dozen short kernels; longer vectors then stream better through the general kernels (16 nodes
-  // of 2^20: 109 us here, 105 us there; 32 nodes with quantisers 310 us here, 270 us there).
+  // One launch for the whole step: one block per node where the vector fits its registers (in chunks of 4096 that meet, a
+  // whole step of one node of 5003 coordinates takes 21 us instead of 14, of 50 nodes 28.5 instead of 20.6; one of 16384 22
+  // instead of 20, 300 of 16384 47 either way); else several blocks that meet, in the smallest chunks with which all
+  // blocks of the launch are resident together (more blocks read faster and meet as often).
+  // Launches that need more than one round of blocks stay with it up to d = 65536 only.  That line is a careful one: beyond it
+  // the general kernels win where quantisers are many (32 nodes of 2^20 with three: 270 us there, 310 here; 200 of 262144
+  // 177 and 185) and not elsewhere (Top-K levels: 100 of 131072 90 there, 74 here; 200 of 262144 174 and 172; 20 of 2^20
+  // 130 and 99).
   ns.small = 0;
   ns.NB = 1;
   ns.chunk = (int)d;

@@ -23,8 +23,8 @@
 // What is polled exists twice: a launch uses one set and clears the other, which the previous launch of the node
 // set has left behind (launches of a node set are ordered on a stream).
 // Measured, per launch, against the general sequence of select.hip (sum of its kernels): Top-K sets, 8 nodes of 20000
-// coordinates 20 us (55), 10 of 5003 22 us (95), one node of 2^20 (a master) 37 us (75), 8 of 1000003 45 us (100);
-// 200 nodes of 65536 107 us (170); 1000 of 65536 with quantisers 444 us (595).
+// coordinates 20 us (55), 10 of 5003 14 us (95), one node of 2^20 (a master) 36 us (75), 8 of 1000003 45 us (100);
+// 200 nodes of 65536 109 us (170); 1000 of 65536 with quantisers 439 us (595).
 #include "devutil.h"
 #include "engine.h"
 #include "quant.h"

@@ -252,9 +252,9 @@ __global__ __launch_bounds__(64) void k_aggregate_short(NodeSet ws, const float*
 // Dense (quantised, Rank-K) messages: a block owns 256 coordinates, each lane four of them; its eight wavefronts take
 // one eighth of the workers each, in ascending order, and their partial sums are combined in wavefront order:
 // g~_new = fl(g~_old + (sparse sums + dense sums) / n).  What the workers chose is read for 64 of them at a time, so
-// that only the messages themselves are waited for, four workers' at a time (eight would halve the wavefronts in flight): with two coordinates a lane and the
-// chain choice -> scale -> codes for every eight workers it took 53 us for 32 workers of 2^20 coordinates (now 20) and
-// 135 us for 1000 of 65536 (now 45).
+// that only the messages themselves are waited for, four workers' at a time (eight would halve the wavefronts in flight):
+// with two coordinates a lane and the chain choice -> scale -> codes for every eight workers it took 53 us for 32 workers
+// of 2^20 coordinates (now 20) and 135 us for 1000 of 65536 (now 45).
 constexpr int kDenseCols = 256;
 constexpr int kDenseWaves = 8;
 __global__ __launch_bounds__(64 * kDenseWaves, 8) void k_aggregate_dense(NodeSet ws, const float* __restrict__ gt_old,
@@ -552,8 +552,9 @@ __global__ __launch_bounds__(kBlock) void k_csr_cols4(LogisticData ld, const flo
   uint32_t longest = 0;
 #pragma unroll
   for (int c = 0; c < 4; ++c) longest = max(longest, e[c] - b[c]);
-  // (62 us instead of 92 for 200 workers x 64000 entries x 65536 columns.  kDeep entries of every column at a time: entry after entry, the longest of the wavefront's 256 columns -- five entries
-  // where the mean is one -- makes it wait for as many pairs of dependent gathers)
+  // (62 us instead of 92 for 200 workers x 64000 entries x 65536 columns.  kDeep entries of every column at a time: entry
+  // after entry, the longest of the wavefront's 256 columns -- five entries where the mean is one -- makes it wait for as
+  // many pairs of dependent gathers)
   constexpr int kDeep = 4;
   for (uint32_t t = 0; t < longest; t += kDeep) {
     int32_t r[kDeep][4];
