@@ -50,6 +50,35 @@ def test_compressed_start_and_differences_where_blocks_do_not_wait_for_each_othe
             np.testing.assert_array_equal(a, b)
 
 
+def test_many_contexts_side_by_side():
+    """Ten contexts on streams of their own, each with launches whose blocks meet: more blocks that wait than the device holds
+    at once.  Same results as one after the other."""
+    import torch
+    E = _eng()
+    n, d, count = 8, 200001, 10
+    rng = np.random.default_rng(3)
+    g = [_cuda(rng.standard_normal((n, d)).astype(np.float32)) for _ in range(3)]
+    x0 = _cuda(np.zeros(d, np.float32))
+    torch.cuda.synchronize()
+    out = []
+    for side_by_side in (False, True):
+        engs = [E.AdaCGD(n=n, d=d, gamma=0.05, worker_levels=[(E.TOPK, 50 + i), (E.QUANT, 4), (E.TOPK, d // 9)], zeta_worker=0.3,
+                         master_levels=[(E.TOPK, d // 30)], zeta_master=0.0, grad_mode=E.GRAD_EXTERNAL, grad0=g[2], x0=x0, seed=i,
+                         stream=torch.cuda.Stream().cuda_stream, flags=E.FLAG_ANY_LEVEL_ORDER | E.FLAG_RETAIN_EXT) for i in range(count)]
+        torch.cuda.synchronize()
+        for group in ([engs] if side_by_side else [[e] for e in engs]):
+            for t in range(4):
+                for e in group:
+                    e.step(g[t % 2])
+            torch.cuda.synchronize()
+        out.append([[e.state(f) for f in (E.F_X, E.F_GI, E.F_G, E.F_LEVEL, E.F_LEVEL_HIST)] for e in engs])
+        for e in engs:
+            e.close()
+    for a, b in zip(*out):
+        for x, y in zip(a, b):
+            np.testing.assert_array_equal(x, y)
+
+
 @pytest.mark.parametrize("n,d", [(64, 512), (65, 512), (64, 513), (1, 512), (12, 1024), (9, 16384), (5, 16001), (33, 3001)])
 def test_aggregation_inside_and_outside_the_workers_launch(n, d):
     check_steps(n, d, "sparse", quant=False)
