@@ -29,6 +29,9 @@
  *  - All work is enqueued on the caller's stream; adacgd_step does not
  *    synchronise.  adacgd_state synchronises the stream before copying.
  *  - One context must not be used from two threads at once.
+ *  - Any number of contexts, on streams of their own and in several processes, may run side by side: launches whose
+ *    blocks share a vector do not rely on these blocks being on the device all at once (a vector whose blocks find no
+ *    room for some 30 ms is worked on by one of them, with the same results).
  *  - Steps may be captured into a graph on the caller's stream, an even number of them (two steps lead back to
  *    the buffers they began with) by one or several adacgd_step calls, at any time after init, and replayed any
  *    number of times between other calls.  With ADACGD_FLAG_RETAIN_EXT the first captured step compares with the
