@@ -280,7 +280,8 @@ enum adacgd_field {
  * scan + filter as two passes.  Without Rank-K levels, vectors of at most 65536 coordinates -- and
  * longer ones, up to 2^20, if there are few nodes -- are handled by one kernel that does the whole
  * compression step of all nodes, timed in the scan slot; up to 512 coordinates, with at most 64
- * workers and Top-K levels only, that launch also aggregates (the aggregate slot stays empty), and
+ * workers and Top-K levels only, that launch also aggregates (the aggregate slot stays empty) and
+ * compresses on the master's side if its levels are of that kind too (the M slots stay empty), and
  * the launch that finishes g also writes the next iterate (the xupdate slot stays empty); so does
  * the aggregation of any vector length when there is no master compressor (g is g~ then). */
 enum adacgd_kernel {

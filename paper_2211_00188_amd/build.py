@@ -9,7 +9,7 @@ from concurrent.futures import ThreadPoolExecutor
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libadacgd.so")
-SOURCES = ["select.hip", "node.hip", "rank.hip", "grad.hip", "server.hip", "engine.hip"]
+SOURCES = ["select.hip", "node.hip", "short.hip", "rank.hip", "grad.hip", "server.hip", "engine.hip"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-ffp-contract=off",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
 

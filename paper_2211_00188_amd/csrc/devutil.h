@@ -78,6 +78,38 @@ __device__ __forceinline__ uint32_t wave_top(uint32_t v) {      // maximum
   return lane_value(v, 63);
 }
 
+// Lane by lane: a + (a of the partner lane) where the lane's bit O is clear, b + (b of the partner lane) where it is
+// set; partners are O = 32 or 16 lanes apart.  One swap a word (of the upper half -- or odd rows -- of a with the lower
+// half -- or even rows -- of b) and one addition.
+template <int O>
+__device__ __forceinline__ double halves_sum(double a, double b) {
+  const uint32_t al = (uint32_t)__double2loint(a), ah = (uint32_t)__double2hiint(a), bl = (uint32_t)__double2loint(b), bh = (uint32_t)__double2hiint(b);
+  if constexpr (O == 32) {
+    const auto lo = __builtin_amdgcn_permlane32_swap(al, bl, false, false), hi = __builtin_amdgcn_permlane32_swap(ah, bh, false, false);
+    return __hiloint2double((int)hi[0], (int)lo[0]) + __hiloint2double((int)hi[1], (int)lo[1]);
+  } else {
+    const auto lo = __builtin_amdgcn_permlane16_swap(al, bl, false, false), hi = __builtin_amdgcn_permlane16_swap(ah, bh, false, false);
+    return __hiloint2double((int)hi[0], (int)lo[0]) + __hiloint2double((int)hi[1], (int)lo[1]);
+  }
+}
+
+// Sums of eight values over the wavefront: lane l gets that of p[l / 8].  Every exchange halves the values that a lane
+// carries: ten additions instead of the 48 of eight wave_total.
+__device__ __forceinline__ double wave_total8(double (&p)[8]) {
+#pragma unroll
+  for (int i = 0; i < 4; ++i) p[i] = halves_sum<32>(p[i], p[i + 4]);
+#pragma unroll
+  for (int i = 0; i < 2; ++i) p[i] = halves_sum<16>(p[i], p[i + 2]);
+  const bool up = (lane_id() & 8u) != 0;
+  double a0 = p[0], a1 = p[1];
+  asm volatile("" : "+v"(a0), "+v"(a1));      // (else: a select of addresses, and from that one of every element)
+  p[0] = (up ? a1 : a0) + dpp_or0<0x128, 0xf>(up ? a0 : a1);      // row_ror:8
+  p[0] += dpp_or0<0x141, 0xf>(p[0]);       // row_half_mirror
+  p[0] += dpp_or0<0x4e, 0xf>(p[0]);        // quad_perm 2 3 0 1
+  p[0] += dpp_or0<0xb1, 0xf>(p[0]);        // quad_perm 1 0 3 2
+  return p[0];
+}
+
 // Sum over a 256-thread block in a fixed order; result valid in every thread.
 __device__ __forceinline__ double block_sum(double v, double* lds4) {
   v = wave_sum(v);

@@ -32,11 +32,10 @@ constexpr int kGradRows = 16;           // rows a group of wavefronts holds at a
 constexpr int kGradFold = 16;           // partial sums that one block adds up
 __host__ __device__ constexpr int grad_col_waves(int64_t cols) { return cols <= 256 ? 1 : cols <= 512 ? 2 : cols <= 1024 ? 4 : 8; }
 // Top-K messages of at most kServeWorkers workers of one chunk each are also written out as whole vectors, which the
-// aggregation reads coordinate by coordinate (k_aggregate_short): up to kServeDim coordinates the workers' launch does that
-// itself (its last block), which saves a launch.  A step inside the launch and with a launch of its own: 10 x 300 11 us and
-// 12, 64 x 300 14.8 and 16.5; 10 x 1000 13.5 and 12, 50 x 1000 20 and 13.
+// aggregation reads coordinate by coordinate (k_aggregate_short).
 constexpr int kServeWorkers = 64;
-constexpr int kServeDim = 512;
+// Vectors of at most kShortDim coordinates and Top-K levels only: short.hip (which aggregates such messages itself).
+constexpr int kShortDim = 512;
 constexpr int kSeg = 64;                // block-wise quantiser scales are built from maxima over segments of 64 coordinates
 constexpr int kSegPerGroup = kWaveTile / kSeg;   // 32
 
@@ -146,7 +145,7 @@ struct NodeSet {
   uint32_t* alone;      // [nn] blocks that have left a node that was given up (NB > 1); zero between launches
   uint32_t polls;       // polls before a node is given up
   float* dense;         // [nn][d] C(v) of every node that sent a message, for k_aggregate_short and the aggregation inside
-                        //         the workers' launch (null: the messages themselves are added)
+                        //         the workers' launch of short.hip (null: the messages themselves are added)
   double* accbuf;       // [d] fp64 sums of the sparse messages (only with quantiser levels)
   // Rank-K levels (allocated only when the level set has any; c = lv.rcols, nr = lv.nr)
   int GR;               // blocks per node of the Rank-K kernels
@@ -178,9 +177,9 @@ struct PassArgs {
                        // the selected values themselves, h[l] = C(v)[l], instead of fl(h[l] + C(v)[l]) (Top-K only)
   int to_dense;        // one-launch step: C(v) is written to NodeSet::dense as well
   // Server work that the one-launch step can take over (each part optional): the block that finishes last adds every node's
-  // message to the server vector, g~_new = fl(g~_old + sum / nn); and the iterate update that opens the next step,
-  // x_next = fl(x - gamma g), with g = g~_new when it follows the aggregation, else g = the updated estimator of
-  // node 0 (the master).
+  // message to the server vector, g~_new = fl(g~_old + sum / nn) (short.hip only); and the iterate update that opens the
+  // next step, x_next = fl(x - gamma g), with g = g~_new when it follows the aggregation, else g = the updated estimator
+  // of node 0 (the master).
   const float* agg_old;
   float* agg_new;
   const float* xu_x;
@@ -251,6 +250,8 @@ hipError_t launch_filter(const NodeSet& ns, const PassArgs& a, hipStream_t st);
 hipError_t launch_gather(const NodeSet& ns, hipStream_t st);
 hipError_t launch_select(const NodeSet& ns, hipStream_t st);
 hipError_t launch_node(const NodeSet& ns, const PassArgs& a, hipStream_t st);
+// ms, m: the master and its arguments, where the launch that aggregates also compresses the server's vector (else null)
+hipError_t launch_short(const NodeSet& ns, const PassArgs& a, const NodeSet* ms, const PassArgs* m, hipStream_t st);
 hipError_t launch_sample(const NodeSet& ns, const PassArgs& a, hipStream_t st);
 hipError_t launch_scanx(const NodeSet& ns, const PassArgs& a, bool repair, hipStream_t st);
 hipError_t launch_tally(const NodeSet& ns, hipStream_t st);

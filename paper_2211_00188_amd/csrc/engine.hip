@@ -645,6 +645,9 @@ hipError_t launch_meeting(hipStream_t st, MeetingSets& sets, void* meet, size_t 
   return adacgd::launch_meeting(sets, capturing(st), clear, launch);
 }
 
+// Whether a node set's step is that of short.hip.
+bool is_short(const NodeSet& ns) { return ns.small && ns.d <= kShortDim && ns.lv.nq == 0; }
+
 // One application of the AdaCGD compressor to every node of a set, on the stream c->cs.
 // `before_tally`, if set, is an event the stream waits for before the kernels that overwrite the
 // message tables (tally, compact, qapply): in overlap mode the previous step's aggregation, which
@@ -653,6 +656,7 @@ int compress(adacgd_ctx* c, NodeSet& ns, PassArgs a, int slot0, hipEvent_t befor
   int rc;
   if (ns.small) {      // the whole step in one launch (timed in the scan's slot)
     if (before_tally) HIPCHK(c, hipStreamWaitEvent(c->cs, before_tally, 0));
+    if (is_short(ns)) return timed(c, slot0 + 1, [&] { return launch_short(ns, a, nullptr, nullptr, c->cs); });
     const size_t words = 2 * (size_t)ns.nn * node_meet_words(ns.lv.pk, ns.lv.nq, ns.NB);
     return timed(c, slot0 + 1, [&] {
       return launch_meeting(c->cs, slot0 == ADACGD_K_W_SAMPLE ? c->w_meet : c->m_meet, ns.meet, words, ns.ticket, [&](uint32_t p) {
@@ -717,8 +721,9 @@ int one_step(adacgd_ctx* c, const float* ext, const double* extD) {
     return rc;
   }
   // Short vectors, few workers, Top-K messages only: the aggregation reads C(v) as whole vectors, and where these are very
-  // short the workers' launch also does it (its last block); the kernel that finishes g does the next iterate update.
-  const bool dense = c->W.dense != nullptr && !ov, serve = dense && c->d <= kServeDim;
+  // short the workers' launch also does it (its last block), and the master's compression after it; the kernel that finishes
+  // g does the next iterate update.
+  const bool dense = c->W.dense != nullptr && !ov, serve = dense && is_short(c->W), whole = serve && c->has_master && is_short(c->M);
   PassArgs a{};
   a.h = c->gi;
   a.seed = c->seed;
@@ -750,9 +755,25 @@ int one_step(adacgd_ctx* c, const float* ext, const double* extD) {
       a.xu_gamma = c->gamma;
     }
   }
+  PassArgs m{};
+  m.x = gt_new;
+  m.h = c->g_own;
+  m.y = gt_old;
+  m.seed = c->seed;
+  m.step = (uint32_t)c->step;
+  m.node_flag = 0x80000000u;
+  if (c->x_next) {
+    m.xu_x = c->x;
+    m.xu_out = c->x_next;
+    m.xu_gamma = c->gamma;
+  }
   // g~_i^{t+1} = C^AC_{g~_i^t, grad f_i(x^t)}(grad f_i(x^{t+1}))
   if (ov) c->cs = c->wst;
-  if ((rc = compress(c, c->W, a, ADACGD_K_W_SAMPLE, ov && c->agg_recorded ? c->ev_agg : nullptr))) return rc;
+  if (whole) {
+    if ((rc = timed(c, ADACGD_K_W_SCAN, [&] { return launch_short(c->W, a, &c->M, &m, c->cs); }))) return rc;
+  } else if ((rc = compress(c, c->W, a, ADACGD_K_W_SAMPLE, ov && c->agg_recorded ? c->ev_agg : nullptr))) {
+    return rc;
+  }
   if (ov) {
     HIPCHK(c, hipEventRecord(c->ev_worker, c->wst));
     c->cs = c->st;
@@ -780,21 +801,7 @@ int one_step(adacgd_ctx* c, const float* ext, const double* extD) {
   }
   c->cur ^= 1;
   // g^{t+1} = C^AC_{g^t, g~^t}(g~^{t+1})
-  if (c->has_master) {
-    PassArgs m{};
-    m.x = gt_new;
-    m.h = c->g_own;
-    m.y = gt_old;
-    m.seed = c->seed;
-    m.step = (uint32_t)c->step;
-    m.node_flag = 0x80000000u;
-    if (c->x_next) {
-      m.xu_x = c->x;
-      m.xu_out = c->x_next;
-      m.xu_gamma = c->gamma;
-    }
-    if ((rc = compress(c, c->M, m, ADACGD_K_M_SAMPLE, nullptr))) return rc;
-  }
+  if (c->has_master && !whole && (rc = compress(c, c->M, m, ADACGD_K_M_SAMPLE, nullptr))) return rc;
   c->step += 1;
   return ADACGD_OK;
 }

@@ -24,21 +24,6 @@ namespace adacgd {
 // 2000 x 8 x 300 took 24 us (18 with two kernels), now 10 us.
 // ---------------------------------------------------------------------------
 
-// Lane by lane: a + (a of the partner lane) where the lane's bit O is clear, b + (b of the partner lane) where it is
-// set; partners are O = 32 or 16 lanes apart.  One swap a word (of the upper half -- or odd rows -- of a with the lower
-// half -- or even rows -- of b) and one addition.
-template <int O>
-__device__ __forceinline__ double halves_sum(double a, double b) {
-  const uint32_t al = (uint32_t)__double2loint(a), ah = (uint32_t)__double2hiint(a), bl = (uint32_t)__double2loint(b), bh = (uint32_t)__double2hiint(b);
-  if constexpr (O == 32) {
-    const auto lo = __builtin_amdgcn_permlane32_swap(al, bl, false, false), hi = __builtin_amdgcn_permlane32_swap(ah, bh, false, false);
-    return __hiloint2double((int)hi[0], (int)lo[0]) + __hiloint2double((int)hi[1], (int)lo[1]);
-  } else {
-    const auto lo = __builtin_amdgcn_permlane16_swap(al, bl, false, false), hi = __builtin_amdgcn_permlane16_swap(ah, bh, false, false);
-    return __hiloint2double((int)hi[0], (int)lo[0]) + __hiloint2double((int)hi[1], (int)lo[1]);
-  }
-}
-
 __device__ __forceinline__ double grad_weight(double yl, double z, double N) { return -yl / (1.0 + exp(yl * z)) / N; }
 
 // What a block does with its column sums (four a lane, in the wavefronts that `hold` them): the gradient, or with several
@@ -199,8 +184,7 @@ __global__ __launch_bounds__(64 * CW * RG, 4) void k_grad(LogisticData ld, const
       const bool live = base + r * RG + rg < rows;
       buf_load4(make_buf(live ? ap + (size_t)(r * RG) * (size_t)d : ld.A, live ? 4 * len : 0u), off, 0, a[r]);
     }
-    // products with x, eight rows at a time: of their sums over the wavefront every exchange halves the rows that a
-    // lane carries; lane l ends with row l / 8
+    // products with x, eight rows at a time (lane l gets the sum of row l / 8)
 #pragma unroll
     for (int r0 = 0; r0 < R; r0 += 8) {
       double p[8];
@@ -213,20 +197,8 @@ __global__ __launch_bounds__(64 * CW * RG, 4) void k_grad(LogisticData ld, const
 #pragma unroll
         for (int c = 1; c < 4; ++c) p[r] = fma((double)a[r0 + r][c], (double)xq[c], p[r]);
       }
-#pragma unroll
-      for (int i = 0; i < 4; ++i) p[i] = halves_sum<32>(p[i], p[i + 4]);
-#pragma unroll
-      for (int i = 0; i < 2; ++i) p[i] = halves_sum<16>(p[i], p[i + 2]);
-      {
-        const bool up = (lane & 8u) != 0;
-        double a0 = p[0], a1 = p[1];
-        asm volatile("" : "+v"(a0), "+v"(a1));      // (else: a select of addresses, and from that one of every element)
-        p[0] = (up ? a1 : a0) + dpp_or0<0x128, 0xf>(up ? a0 : a1);      // row_ror:8
-      }
-      p[0] += dpp_or0<0x141, 0xf>(p[0]);       // row_half_mirror
-      p[0] += dpp_or0<0x4e, 0xf>(p[0]);        // quad_perm 2 3 0 1
-      p[0] += dpp_or0<0xb1, 0xf>(p[0]);        // quad_perm 1 0 3 2
-      if ((lane & 7u) == 0) red[w][r0 + (lane >> 3)] = p[0];
+      const double all = wave_total8(p);
+      if ((lane & 7u) == 0) red[w][r0 + (lane >> 3)] = all;
     }
     // (the values widened to fp64 are formed anew below: carrying them along would not fit the registers)
 #pragma unroll

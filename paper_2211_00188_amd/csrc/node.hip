@@ -156,7 +156,6 @@ __global__ __launch_bounds__(NT, NT >= 512 ? 4 : 1) void k_node(NodeSet ns, Pass
   const int node = (int)(blk / (uint32_t)NB), part = (int)(blk % (uint32_t)NB);
   const uint32_t c0 = (uint32_t)part * (uint32_t)ns.chunk;           // first coordinate of the chunk
   const uint32_t len = min((uint32_t)ns.chunk, d - c0);
-  const bool serve = NT * VPT <= 2 * kServeDim && a.agg_new != nullptr;     // this launch also aggregates: ns.dense is written coherently
   const size_t row = (size_t)node * d + c0;
   const bool diff = a.diff != 0;
   const Buf xb = make_buf(a.x + row, 4 * len), hb = make_buf(a.h + row, 4 * len);
@@ -270,8 +269,7 @@ __global__ __launch_bounds__(NT, NT >= 512 ? 4 : 1) void k_node(NodeSet ns, Pass
         ns.D[node] = Dn;
         ns.level[node] = jstar;
         atomicAdd(&ns.level_hist[jstar], 1ull);
-        if (serve) st_coherent(&ns.sel_slot[node], slot);
-        else ns.sel_slot[node] = slot;
+        ns.sel_slot[node] = slot;
         ns.sel_q[node] = q_sel;
         ns.msg_count[node] = slot >= 0 ? s_K[slot] : 0u;
         if (nq > 0) ns.qscale[node] = 0.f;
@@ -1044,13 +1042,7 @@ __global__ __launch_bounds__(NT, NT >= 512 ? 4 : 1) void k_node(NodeSet ns, Pass
         float cv[4];
 #pragma unroll
         for (int c = 0; c < 4; ++c) cv[c] = ((f >> c) & 1u) ? v[q * 4 + c] : 0.f;
-        if (serve) {
-#pragma unroll
-          for (int c = 0; c < 4; ++c)
-            if (l0 + c < len) st_coherent(&ns.dense[row + l0 + c], cv[c]);
-        } else {
-          buf_store4(make_buf(ns.dense + row, 4 * len), off0, q * NT * 16, cv);
-        }
+        buf_store4(make_buf(ns.dense + row, 4 * len), off0, q * NT * 16, cv);
       }
     }
   } else if (QUANT && q_sel >= 0) {
@@ -1102,7 +1094,7 @@ __global__ __launch_bounds__(NT, NT >= 512 ? 4 : 1) void k_node(NodeSet ns, Pass
   }
 
   // ---- iterate update that opens the next step, from this node's new estimator (the master) ----
-  if (a.xu_out && !serve && node == 0) {
+  if (a.xu_out && node == 0) {
     const Buf xub = make_buf(a.xu_x + c0, 4 * len), xuo = make_buf(a.xu_out + c0, 4 * len);
 #pragma unroll
     for (int q = 0; q < NQ4; ++q) {
@@ -1113,26 +1105,6 @@ __global__ __launch_bounds__(NT, NT >= 512 ? 4 : 1) void k_node(NodeSet ns, Pass
       for (int c = 0; c < 4; ++c) xq[c] = (float)((double)xq[c] - a.xu_gamma * (double)hq[c]);
       buf_store4(xuo, off0, q * NT * 16, xq);
     }
-  }
-  if (!serve) return;
-
-  // ---- server aggregation by the block that finishes last (Top-K messages of few workers, NB = 1): every
-  // coordinate's sum in ascending worker index; what a worker does not send adds +0, which changes no sum ----
-  if (!arrive_last(ns.done, (uint32_t)ns.nn, (uint32_t)node, &s_flag)) return;
-  const uint64_t senders = ballot(lane < (uint32_t)ns.nn && ld_coherent(&ns.sel_slot[lane < (uint32_t)ns.nn ? lane : 0]) >= 0);
-  const double nn = (double)ns.nn;
-  for (uint32_t l = tid; l < d; l += NT) {
-    double acc = 0.0;
-    for (int i0 = 0; i0 < ns.nn; i0 += 8) {
-      float t[8];
-#pragma unroll
-      for (int u = 0; u < 8; ++u) t[u] = (i0 + u < 64 && ((senders >> (i0 + u)) & 1u)) ? ld_coherent(&ns.dense[(size_t)(i0 + u) * d + l]) : 0.f;
-#pragma unroll
-      for (int u = 0; u < 8; ++u) acc += (double)t[u];
-    }
-    const float gn = (float)((double)a.agg_old[l] + acc / nn);
-    a.agg_new[l] = gn;
-    if (a.xu_out) a.xu_out[l] = (float)((double)a.xu_x[l] - a.xu_gamma * (double)gn);
   }
 }
 

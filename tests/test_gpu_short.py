@@ -1,0 +1,71 @@
+"""The compression step of short vectors (short.hip) at the edges of its range: block sizes, remainders, as many and more workers
+than its launch aggregates, ties and zeros that leave its histogram, levels and triggers on both sides; against the oracle bit
+for bit, and against the general kernels where values are infinite or not numbers."""
+import numpy as np
+import pytest
+
+from oracle import adacgd_oracle as O
+from test_gpu_parity import _cuda, _eng, compare_step, make_vectors, until_near_tie
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("n,d,kind", [(n, d, k) for n, d in [(1, 1), (2, 2), (3, 63), (2, 64), (4, 65), (5, 127), (2, 128), (3, 129), (2, 255),
+                                                             (64, 256), (65, 257), (20, 300), (3, 511), (33, 512), (70, 512)]
+                                      for k in ("normal", "ties", "const", "denormal", "sparse")])
+@pytest.mark.parametrize("master", ["none", "one", "many", "quant"])
+def test_short_vectors(n, d, kind, master):
+    E = _eng()
+    rng = np.random.default_rng(d * 100 + n)
+    sizes = sorted({1, max(1, d // 50), max(1, d // 9), max(1, d // 3), max(1, d // 2), d})
+    some = sorted({max(1, d // 20), max(1, d // 4), d})
+    ml = {"none": [], "one": [(O.TOPK, max(1, d // 20))], "many": [(O.TOPK, k) for k in some], "quant": [(O.QUANT, 4)]}[master]
+    kw = dict(n=n, d=d, gamma=0.05, worker_levels=[(O.TOPK, k) for k in sizes], zeta_worker=0.3, master_levels=ml,
+              zeta_master=0.4 if master == "many" else 0.0, seed=77)
+    grads = [make_vectors(rng, n, d, kind) for _ in range(3)]
+    x0 = rng.standard_normal(d).astype(np.float32)
+    orc = O.AdaCGDOracle(**kw)
+    orc.init(x0, grads[0], O.INIT_FULLGRAD)
+    eng = E.AdaCGD(grad_mode=E.GRAD_EXTERNAL, x0=_cuda(x0), grad0=_cuda(grads[0]), **kw)
+    with until_near_tie(("short", n, d, kind, master)):
+        for t in (1, 2, 3):
+            g = (grads[t - 1] + grads[t % 3] * np.float32(0.3)).astype(np.float32)
+            res, rm = orc.step(grads=g)
+            eng.step(_cuda(g))
+            compare_step(eng, orc, res, rm, ("short", n, d, kind, master, t), check_master=bool(ml))
+    eng.close()
+
+
+@pytest.mark.parametrize("mode", ["overlap", "compressed", "diff"])
+@pytest.mark.parametrize("n,d", [(3, 100), (20, 300), (65, 512)])
+@pytest.mark.parametrize("what", ["normal", "inf", "nan", "wide"])
+def test_short_vectors_against_the_general_kernels(n, d, what, mode):
+    """The same results as the general kernels give, bit for bit, also where the largest key is infinite or not a number, where keys
+    lie further below it than the histogram reaches, and in the other modes of a context."""
+    E = _eng()
+    rng = np.random.default_rng(n + d)
+    v = [rng.standard_normal((n, d)).astype(np.float32) for _ in range(3)]
+    for a in v:
+        if what == "wide":
+            a *= np.float32(2.0) ** rng.integers(-120, 20, (n, d)).astype(np.float32)
+        elif what != "normal":
+            a[0, rng.integers(0, d, 3)] = np.float32(what)
+    out = []
+    for flags in (E.FLAG_TWO_PASS, 0):
+        kw = dict(grad_mode=E.DIFF_EXTERNAL, init_mode=E.INIT_ZERO) if mode == "diff" else dict(grad_mode=E.GRAD_EXTERNAL, grad0=_cuda(v[2]))
+        if mode == "compressed":
+            kw.update(init_mode=E.INIT_COMPRESSED)
+        flags |= E.FLAG_ANY_LEVEL_ORDER | (E.FLAG_OVERLAP if mode == "overlap" else 0)
+        eng = E.AdaCGD(n=n, d=d, gamma=0.05, worker_levels=[(E.TOPK, d // 9), (E.TOPK, 3), (E.TOPK, d // 2)], zeta_worker=0.5,
+                       master_levels=[(E.TOPK, d // 4)], zeta_master=0.0, x0=_cuda(np.zeros(d, np.float32)), seed=3, flags=flags, **kw)
+        for t, D in enumerate((1e-3, 1e9, 1e-3)):
+            eng.step(_cuda(v[t]), *([_cuda(np.full(n, D))] if mode == "diff" else []))
+            out.append([eng.state(f) for f in (E.F_LEVEL, E.F_SQNORM, E.F_ERR, E.F_MSG_COUNT, E.F_MSG_IDX, E.F_MSG_VAL, E.F_GI, E.F_GTILDE,
+                                               E.F_G, E.F_X, E.F_LEVEL_HIST, E.F_M_MSG_IDX)])
+        eng.close()
+    for a, b in zip(out[:3], out[3:]):
+        for f, (x, y) in enumerate(zip(a, b)):
+            if x.dtype == np.float64:
+                np.testing.assert_allclose(x, y, rtol=1e-12, err_msg=str(f))
+            else:
+                np.testing.assert_array_equal(x, y, err_msg=str(f))
