@@ -27,6 +27,7 @@ constexpr int kNodeParts = 64;
 constexpr int kNodeResident = 512;      // its blocks resident at once: two per compute unit (layouts follow it, nothing depends on it)
 constexpr uint32_t kPolls = 1u << 15;   // a block waits that many polls (of about 1 us) for others to begin, then does without them
 // One-launch gradient (k_grad): up to kGradCols columns a block, up to kNodeParts such parts of a row.
+constexpr int64_t kCacheBytes = int64_t(256) << 20;      // memory-side cache
 constexpr int kGradCols = 2048;
 constexpr int kGradRows = 16;           // rows a group of wavefronts holds at a time
 constexpr int kGradFold = 16;           // partial sums that one block adds up
@@ -211,7 +212,8 @@ struct LogisticData {
   // One-launch gradient of dense features (k_grad): every shard's rows in chunks of chunk_rows, its columns in
   // col_parts parts of part_cols, one block each; col_parts = 0: the two-kernel form.
   int col_parts;
-  int part_cols;
+  int part_cols;           // ... in turns of 256 columns (col_parts > 1)
+  int stream;              // the features do not fit the memory-side cache: they are read past it
   int row_groups;          // groups of wavefronts of a block that hold different rows
   int chunk_rows;          // a multiple of the rows a block holds at a time
   int groups;              // row chunks of all shards together

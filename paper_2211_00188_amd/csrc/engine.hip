@@ -511,8 +511,8 @@ void shape_logistic(const adacgd_config* cfg, LogisticData& ld) {
     // spread over the device.
     const int64_t n = cfg->n, d = cfg->d;
     int64_t parts = (d + kGradCols - 1) / kGradCols;
-    ld.part_cols = (int)(parts == 1 ? d : ((d + parts - 1) / parts + 15) / 16 * 16);
-    parts = (d + ld.part_cols - 1) / ld.part_cols;
+    ld.part_cols = (int)(parts == 1 ? d : ((d + 255) / 256 + parts - 1) / parts * 256);
+    ld.stream = ld.rows * d * 4 > kCacheBytes;
     const int waves = grad_col_waves(ld.part_cols);
     ld.row_groups = 1;
     while (ld.row_groups * waves < 8 && ld.row_groups * kGradRows < mx) ld.row_groups *= 2;

@@ -24,26 +24,30 @@ namespace adacgd {
 // 2000 x 8 x 300 took 24 us (18 with two kernels), now 10 us.
 // ---------------------------------------------------------------------------
 
+// First of a lane's four columns.  The P blocks of a row take turns of 256 columns, so that what a block reads is spread over the
+// memory's channels as the whole row is: with 2048 columns side by side some blocks had their rows after 4 us and waited 15 us
+// for others' (1000 x 32 rows x 65536 columns: 1.95 ms, in turns 1.87).
+__device__ __forceinline__ uint32_t grad_column(uint32_t wave, uint32_t P, uint32_t part, uint32_t lane) { return ((wave * P + part) * 64 + lane) * 4; }
+
 __device__ __forceinline__ double grad_weight(double yl, double z, double N) { return -yl / (1.0 + exp(yl * z)) / N; }
 
-// What a block does with its column sums (four a lane, in the wavefronts that `hold` them): the gradient, or with several
+// What a block does with its column sums (four a lane from column `col` on, the part's quad `at`, in the wavefronts that `hold` them): the gradient, or with several
 // chunks a shard -- each leaves its sums, and the last to arrive adds them in chunk order: kGradFold of them; of more
 // chunks, the last of every kGradFold leaves their sum, and the last of those adds these (one block adding all of them
 // took 140 us for 1 x 4000 rows x 2048 columns, 250 chunks).
 __device__ __forceinline__ void finish(const LogisticData& ld, float* __restrict__ grads, int64_t d, int node, int rc, int nchunks, int slot0,
-                                       uint32_t P, uint32_t part, uint32_t len, uint32_t off, bool hold, const float (&xq)[4], double (&acc)[4],
+                                       uint32_t P, uint32_t part, uint32_t at, uint32_t col, bool hold, const float (&xq)[4], double (&acc)[4],
                                        int* flag) {
-  const uint32_t l0 = off / 4;
   if (nchunks > 1) {
-    // (columns l, l + 4, l + 8, ... of a part lie side by side, so that a wavefront's accesses do)
+    // (a part's columns 0, 4, 8, ... lie side by side, so that a wavefront's accesses do)
     const uint32_t quads = ((uint32_t)ld.part_cols + 3) / 4;
     const size_t slot_len = (size_t)P * quads * 4;
-    double* __restrict__ sums = ld.part + (size_t)part * quads * 4 + off / 16;
+    double* __restrict__ sums = ld.part + (size_t)part * quads * 4 + at;
     auto leave = [&](int slot) {
       if (hold) {
 #pragma unroll
         for (int c = 0; c < 4; ++c)
-          if (l0 + c < len) st_coherent(&sums[(size_t)slot * slot_len + c * quads], acc[c]);
+          if (col + c < (uint32_t)d) st_coherent(&sums[(size_t)slot * slot_len + c * quads], acc[c]);
       }
     };
     auto add = [&](int slot, int count, int stride) {
@@ -56,7 +60,7 @@ __device__ __forceinline__ void finish(const LogisticData& ld, float* __restrict
           for (int u = 0; u < 8; ++u)
 #pragma unroll
             for (int c = 0; c < 4; ++c)
-              v[u][c] = r0 + u < count && l0 + c < len ? ld_coherent(&sums[(size_t)(slot + (r0 + u) * stride) * slot_len + c * quads]) : 0.0;
+              v[u][c] = r0 + u < count && col + c < (uint32_t)d ? ld_coherent(&sums[(size_t)(slot + (r0 + u) * stride) * slot_len + c * quads]) : 0.0;
 #pragma unroll
           for (int u = 0; u < 8; ++u)
 #pragma unroll
@@ -79,7 +83,7 @@ __device__ __forceinline__ void finish(const LogisticData& ld, float* __restrict
   float g[4];
 #pragma unroll
   for (int c = 0; c < 4; ++c) g[c] = (float)(acc[c] + reg_grad(ld.lambda, (double)xq[c]));
-  buf_store4(make_buf(grads + (size_t)node * (size_t)d + part * (uint32_t)ld.part_cols, 4 * len), off, 0, g);
+  buf_store4(make_buf(grads + (size_t)node * (size_t)d, 4 * (uint32_t)d), 4 * col, 0, g);
 }
 
 // A whole row chunk by one block of eight wavefronts: the weights of its rows, left where the products were (nobody polls
@@ -87,7 +91,6 @@ __device__ __forceinline__ void finish(const LogisticData& ld, float* __restrict
 __device__ __forceinline__ void grad_alone(const LogisticData& ld, const float* __restrict__ x, float* __restrict__ grads, int64_t d, int node, int rc,
                                         int nchunks, int slot0, uint32_t r_begin, int rows, double N, double* slots, int* flag) {
   const uint32_t P = (uint32_t)ld.col_parts, lane = threadIdx.x & 63;
-  const uint32_t off = threadIdx.x * 16u;
   for (int row = (int)(threadIdx.x >> 6); row < rows; row += 8) {
     const float* __restrict__ a = ld.A + (size_t)(r_begin + (uint32_t)row) * (size_t)d;
     double z = 0.0;
@@ -98,23 +101,24 @@ __device__ __forceinline__ void grad_alone(const LogisticData& ld, const float* 
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   __syncthreads();
   for (uint32_t p = 0; p < P; ++p) {
-    const uint32_t c0 = p * (uint32_t)ld.part_cols, len = min((uint32_t)ld.part_cols, (uint32_t)d - c0);
+    const uint32_t col = grad_column(threadIdx.x >> 6, P, p, lane);
     float xq[4];
-    buf_load4(make_buf(x + c0, 4 * len), off, 0, xq);
+    buf_load4(make_buf(x, 4 * (uint32_t)d), 4 * col, 0, xq);
     double acc[4] = {0.0, 0.0, 0.0, 0.0};
     for (int row = 0; row < rows; ++row) {
       float a[4];
-      buf_load4(make_buf(ld.A + (size_t)(r_begin + (uint32_t)row) * (size_t)d + c0, 4 * len), off, 0, a);
+      buf_load4(make_buf(ld.A + (size_t)(r_begin + (uint32_t)row) * (size_t)d, 4 * (uint32_t)d), 4 * col, 0, a);
       const double s = ld_coherent(&slots[(size_t)row * P]);
 #pragma unroll
       for (int c = 0; c < 4; ++c) acc[c] = fma(s, (double)a[c], acc[c]);
     }
-    finish(ld, grads, d, node, rc, nchunks, slot0, P, p, len, off, true, xq, acc, flag);
+    finish(ld, grads, d, node, rc, nchunks, slot0, P, p, threadIdx.x, col, true, xq, acc, flag);
   }
 }
 
-// PARTED: rows are longer than a block's columns (CW = 8, RG = 1)
-template <int CW, int RG, bool PARTED>
+// PARTED: rows are longer than a block's columns (CW = 8, RG = 1).  STREAM: the features do not fit the memory-side cache and are read
+// past it (1000 x 32 rows x 65536 columns: 1.87 ms, so 1.82).
+template <int CW, int RG, bool PARTED, bool STREAM = false>
 __global__ __launch_bounds__(64 * CW * RG, 4) void k_grad(LogisticData ld, const float* __restrict__ x, float* __restrict__ grads, int64_t d) {
   constexpr int R = kGradRows, NT = 64 * CW * RG;
   __shared__ double red[CW * RG][R], s_m[RG][R];
@@ -150,15 +154,13 @@ __global__ __launch_bounds__(64 * CW * RG, 4) void k_grad(LogisticData ld, const
     nchunks = (int)scalar((uint32_t)t.z);
     slot0 = (int)scalar((uint32_t)t.w);
   }
-  const uint32_t c0 = part * (uint32_t)ld.part_cols;
-  const uint32_t len = min((uint32_t)ld.part_cols, (uint32_t)d - c0);
   // (a row number fits 31 bits: the host's choice of this kernel)
   const uint32_t r_first = scalar((uint32_t)ld.offsets[node]);
   const int count = (int)(scalar((uint32_t)ld.offsets[node + 1]) - r_first);
   const int skip = rc * ld.chunk_rows, rows = max(0, min(count - skip, ld.chunk_rows));
   const uint32_t r_begin = r_first + (uint32_t)skip;
   const double N = (double)count;
-  const uint32_t off = (uint32_t)(cw * 64 + (int)lane) * 16u;       // byte offset of this lane's four columns
+  const uint32_t col = grad_column((uint32_t)cw, P, part, lane), bytes = 4 * (uint32_t)d;
   const size_t set = (size_t)ld.rows * P;
   double* __restrict__ slots = PARTED ? ld.meet + ld.parity * set + (size_t)r_begin * P : nullptr;
   if (PARTED) {       // the set the previous launch used, cleared for the next one
@@ -171,18 +173,18 @@ __global__ __launch_bounds__(64 * CW * RG, 4) void k_grad(LogisticData ld, const
   }
   if (tid == 0) s_quit = 0;
   float xq[4];
-  buf_load4(make_buf(x + c0, 4 * len), off, 0, xq);
+  buf_load4(make_buf(x, bytes), 4 * col, 0, xq);
   auto label = [&](int row) { return row < rows ? ld.labels[r_begin + (uint32_t)row] : 0.f; };      // (asked for before it is needed)
   auto weight = [&](double yl, double z) { return grad_weight(yl, z, N); };
   double acc[4] = {0.0, 0.0, 0.0, 0.0};
   for (int base = 0; base < rows; base += R * RG) {
     // rows base + r RG + rg of the chunk (rows beyond its end read as zero and get weight zero)
     float a[R][4];
-    const float* __restrict__ ap = ld.A + (size_t)(r_begin + (uint32_t)(base + rg)) * (size_t)d + c0;
+    const float* __restrict__ ap = ld.A + (size_t)(r_begin + (uint32_t)(base + rg)) * (size_t)d;
 #pragma unroll
     for (int r = 0; r < R; ++r) {
       const bool live = base + r * RG + rg < rows;
-      buf_load4(make_buf(live ? ap + (size_t)(r * RG) * (size_t)d : ld.A, live ? 4 * len : 0u), off, 0, a[r]);
+      buf_load4<STREAM ? kStream : 0>(make_buf(live ? ap + (size_t)(r * RG) * (size_t)d : ld.A, live ? bytes : 0u), 4 * col, 0, a[r]);
     }
     // products with x, eight rows at a time (lane l gets the sum of row l / 8)
 #pragma unroll
@@ -276,7 +278,7 @@ __global__ __launch_bounds__(64 * CW * RG, 4) void k_grad(LogisticData ld, const
         for (int c = 0; c < 4; ++c) acc[c] += s_acc[g][cw * 256 + (int)lane * 4 + c];
     }
   }
-  if (rg == 0 || nchunks > 1) finish(ld, grads, d, node, rc, nchunks, slot0, P, part, len, off, rg == 0, xq, acc, &s_flag);
+  if (rg == 0 || nchunks > 1) finish(ld, grads, d, node, rc, nchunks, slot0, P, part, (uint32_t)(cw * 64) + lane, col, rg == 0, xq, acc, &s_flag);
 }
 
 hipError_t launch_grad(const LogisticData& ld, const float* x, float* grads, int64_t d, hipStream_t st) {
@@ -291,7 +293,7 @@ hipError_t launch_grad(const LogisticData& ld, const float* x, float* grads, int
     case 1: return rg == 1 ? go(k_grad<1, 1, false>, 1) : rg == 2 ? go(k_grad<1, 2, false>, 2) : rg == 4 ? go(k_grad<1, 4, false>, 4) : go(k_grad<1, 8, false>, 8);
     case 2: return rg == 1 ? go(k_grad<2, 1, false>, 2) : rg == 2 ? go(k_grad<2, 2, false>, 4) : go(k_grad<2, 4, false>, 8);
     case 4: return rg == 1 ? go(k_grad<4, 1, false>, 4) : go(k_grad<4, 2, false>, 8);
-    default: return ld.col_parts > 1 ? go(k_grad<8, 1, true>, 8) : go(k_grad<8, 1, false>, 8);
+    default: return ld.col_parts == 1 ? go(k_grad<8, 1, false>, 8) : ld.stream ? go(k_grad<8, 1, true, true>, 8) : go(k_grad<8, 1, true>, 8);
   }
 }
 
