@@ -31,20 +31,40 @@ __device__ __forceinline__ uint32_t grad_column(uint32_t wave, uint32_t P, uint3
 
 __device__ __forceinline__ double grad_weight(double yl, double z, double N) { return -yl / (1.0 + exp(yl * z)) / N; }
 
-// What a block does with its column sums (four a lane from column `col` on, the part's quad `at`, in the wavefronts that `hold` them): the gradient, or with several
-// chunks a shard -- each leaves its sums, and the last to arrive adds them in chunk order: kGradFold of them; of more
-// chunks, the last of every kGradFold leaves their sum, and the last of those adds these (one block adding all of them
-// took 140 us for 1 x 4000 rows x 2048 columns, 250 chunks).
+// Sums of the RG groups of wavefronts, in group order, in group 0; share: four values of every thread, thread by thread (null if RG = 1).
+template <int RG>
+__device__ __forceinline__ void add_groups(double (&acc)[4], double* share, int rg) {
+  if (RG == 1) return;
+  const int lanes = (int)blockDim.x / RG, mine = (int)threadIdx.x - rg * lanes;
+  __syncthreads();
+#pragma unroll
+  for (int c = 0; c < 4; ++c) share[(rg * 4 + c) * lanes + mine] = acc[c];
+  __syncthreads();
+  if (rg == 0) {
+#pragma unroll
+    for (int g = 1; g < RG; ++g)
+#pragma unroll
+      for (int c = 0; c < 4; ++c) acc[c] += share[(g * 4 + c) * lanes + mine];
+  }
+}
+
+// What a block does with its column sums (four a lane from column `col` on, the part's quad `at`, in group 0 of its RG groups of
+// wavefronts): the gradient, or with several chunks a shard -- each leaves its sums, and the last to arrive adds them:
+// kGradFold RG of them, every group its share, the groups' sums in their order; of more chunks, the last of every kGradFold RG
+// leaves their sum, and the last of those adds these (one block adding all of them took 140 us for 1 x 4000 rows x 2048
+// columns, 250 chunks; 20 chunks added by the first group alone, 16 and then the two sums, 1.5 us more than by four groups).
+template <int RG>
 __device__ __forceinline__ void finish(const LogisticData& ld, float* __restrict__ grads, int64_t d, int node, int rc, int nchunks, int slot0,
-                                       uint32_t P, uint32_t part, uint32_t at, uint32_t col, bool hold, const float (&xq)[4], double (&acc)[4],
-                                       int* flag) {
+                                       uint32_t P, uint32_t part, uint32_t at, uint32_t col, int rg, const float (&xq)[4], double (&acc)[4],
+                                       double* share, int* flag) {
+  constexpr int FOLD = kGradFold * RG;
   if (nchunks > 1) {
     // (a part's columns 0, 4, 8, ... lie side by side, so that a wavefront's accesses do)
     const uint32_t quads = ((uint32_t)ld.part_cols + 3) / 4;
     const size_t slot_len = (size_t)P * quads * 4;
     double* __restrict__ sums = ld.part + (size_t)part * quads * 4 + at;
     auto leave = [&](int slot) {
-      if (hold) {
+      if (rg == 0) {
 #pragma unroll
         for (int c = 0; c < 4; ++c)
           if (col + c < (uint32_t)d) st_coherent(&sums[(size_t)slot * slot_len + c * quads], acc[c]);
@@ -53,33 +73,32 @@ __device__ __forceinline__ void finish(const LogisticData& ld, float* __restrict
     auto add = [&](int slot, int count, int stride) {
 #pragma unroll
       for (int c = 0; c < 4; ++c) acc[c] = 0.0;
-      if (hold) {
-        for (int r0 = 0; r0 < count; r0 += 8) {        // eight loads of a column in flight
-          double v[8][4];
+      for (int r0 = rg; r0 < count; r0 += 8 * RG) {        // eight loads of a column in flight
+        double v[8][4];
 #pragma unroll
-          for (int u = 0; u < 8; ++u)
+        for (int u = 0; u < 8; ++u)
 #pragma unroll
-            for (int c = 0; c < 4; ++c)
-              v[u][c] = r0 + u < count && col + c < (uint32_t)d ? ld_coherent(&sums[(size_t)(slot + (r0 + u) * stride) * slot_len + c * quads]) : 0.0;
+          for (int c = 0; c < 4; ++c)
+            v[u][c] = r0 + u * RG < count && col + c < (uint32_t)d ? ld_coherent(&sums[(size_t)(slot + (r0 + u * RG) * stride) * slot_len + c * quads]) : 0.0;
 #pragma unroll
-          for (int u = 0; u < 8; ++u)
+        for (int u = 0; u < 8; ++u)
 #pragma unroll
-            for (int c = 0; c < 4; ++c) acc[c] += v[u][c];
-        }
+          for (int c = 0; c < 4; ++c) acc[c] += v[u][c];
       }
+      add_groups<RG>(acc, share, rg);
     };
     leave(slot0 + rc);
-    const int sub = rc - rc % kGradFold, members = min(kGradFold, nchunks - sub);
+    const int sub = rc - rc % FOLD, members = min(FOLD, nchunks - sub);
     if (!arrive_last_few(&ld.col_done[(size_t)(slot0 + sub) * P + part], (uint32_t)members, flag)) return;
     add(slot0 + sub, members, 1);
-    if (nchunks > kGradFold) {
+    if (nchunks > FOLD) {
       leave(slot0 + sub);
-      const int subs = (nchunks + kGradFold - 1) / kGradFold;
+      const int subs = (nchunks + FOLD - 1) / FOLD;
       if (!arrive_last_few(&ld.col_done[(size_t)(ld.part_slots + slot0) * P + part], (uint32_t)subs, flag)) return;
-      add(slot0, subs, kGradFold);
+      add(slot0, subs, FOLD);
     }
   }
-  if (!hold) return;
+  if (rg != 0) return;
   float g[4];
 #pragma unroll
   for (int c = 0; c < 4; ++c) g[c] = (float)(acc[c] + reg_grad(ld.lambda, (double)xq[c]));
@@ -112,7 +131,7 @@ __device__ __forceinline__ void grad_alone(const LogisticData& ld, const float* 
 #pragma unroll
       for (int c = 0; c < 4; ++c) acc[c] = fma(s, (double)a[c], acc[c]);
     }
-    finish(ld, grads, d, node, rc, nchunks, slot0, P, p, threadIdx.x, col, true, xq, acc, flag);
+    finish<1>(ld, grads, d, node, rc, nchunks, slot0, P, p, threadIdx.x, col, 0, xq, acc, nullptr, flag);
   }
 }
 
@@ -122,7 +141,7 @@ template <int CW, int RG, bool PARTED, bool STREAM = false>
 __global__ __launch_bounds__(64 * CW * RG, 4) void k_grad(LogisticData ld, const float* __restrict__ x, float* __restrict__ grads, int64_t d) {
   constexpr int R = kGradRows, NT = 64 * CW * RG;
   __shared__ double red[CW * RG][R], s_m[RG][R];
-  __shared__ double s_acc[RG > 1 ? RG : 1][RG > 1 ? CW * 256 : 1];
+  __shared__ double s_acc[RG > 1 ? RG * CW * 256 : 1];
   __shared__ uint32_t s_blk;
   __shared__ int s_flag, s_quit;
   const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), cw = w % CW, rg = w / CW;
@@ -186,6 +205,7 @@ __global__ __launch_bounds__(64 * CW * RG, 4) void k_grad(LogisticData ld, const
       const bool live = base + r * RG + rg < rows;
       buf_load4<STREAM ? kStream : 0>(make_buf(live ? ap + (size_t)(r * RG) * (size_t)d : ld.A, live ? bytes : 0u), 4 * col, 0, a[r]);
     }
+    const float yl_row = !PARTED && tid < R * RG ? label(base + tid % R * RG + tid / R) : 0.f;      // (comes with the rows)
     // products with x, eight rows at a time (lane l gets the sum of row l / 8)
 #pragma unroll
     for (int r0 = 0; r0 < R; r0 += 8) {
@@ -252,7 +272,7 @@ __global__ __launch_bounds__(64 * CW * RG, 4) void k_grad(LogisticData ld, const
       double z = 0.0;
 #pragma unroll
       for (int j = 0; j < CW; ++j) z += red[g * CW + j][r];
-      s_m[g][r] = row < rows ? weight((double)label(row), z) : 0.0;
+      s_m[g][r] = row < rows ? weight((double)yl_row, z) : 0.0;
     }
     __syncthreads();
     if (PARTED && base == 0 && __builtin_expect(s_quit, 0)) {
@@ -267,18 +287,8 @@ __global__ __launch_bounds__(64 * CW * RG, 4) void k_grad(LogisticData ld, const
       for (int c = 0; c < 4; ++c) acc[c] = fma(s, (double)a[r][c], acc[c]);
     }
   }
-  if (RG > 1) {
-#pragma unroll
-    for (int c = 0; c < 4; ++c) s_acc[rg][cw * 256 + (int)lane * 4 + c] = acc[c];
-    __syncthreads();
-    if (rg == 0) {
-#pragma unroll
-      for (int g = 1; g < RG; ++g)
-#pragma unroll
-        for (int c = 0; c < 4; ++c) acc[c] += s_acc[g][cw * 256 + (int)lane * 4 + c];
-    }
-  }
-  if (rg == 0 || nchunks > 1) finish(ld, grads, d, node, rc, nchunks, slot0, P, part, (uint32_t)(cw * 64) + lane, col, rg == 0, xq, acc, &s_flag);
+  add_groups<RG>(acc, s_acc, rg);
+  if (rg == 0 || nchunks > 1) finish<RG>(ld, grads, d, node, rc, nchunks, slot0, P, part, (uint32_t)(cw * 64) + lane, col, rg, xq, acc, s_acc, &s_flag);
 }
 
 hipError_t launch_grad(const LogisticData& ld, const float* x, float* grads, int64_t d, hipStream_t st) {
