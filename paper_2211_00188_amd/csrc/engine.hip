@@ -672,7 +672,8 @@ int compress(adacgd_ctx* c, NodeSet& ns, PassArgs a, int slot0, hipEvent_t befor
     if ((rc = timed(c, slot0 + 2, [&] { return launch_scanx(ns, a, true, c->cs); }))) return rc;
   } else {
     if ((rc = timed(c, slot0 + 1, [&] { return launch_scan(ns, a, c->cs); }))) return rc;
-    if ((rc = timed(c, slot0 + 2, [&] { return launch_filter(ns, a, c->cs); }))) return rc;
+    // (without a Top-K size below d there are no candidates to look for: gather and select are left out too)
+    if ((ns.lv.pk > 0 || ns.lv.nq > 0) && (rc = timed(c, slot0 + 2, [&] { return launch_filter(ns, a, c->cs); }))) return rc;
   }
   if (ns.lv.nr > 0) {
     const int rank_slot = slot0 == ADACGD_K_W_SAMPLE ? ADACGD_K_W_RANK : ADACGD_K_M_RANK;
@@ -681,8 +682,8 @@ int compress(adacgd_ctx* c, NodeSet& ns, PassArgs a, int slot0, hipEvent_t befor
     if ((rc = timed(c, eig_slot, [&] { return launch_rank_eig(ns, a, c->cs); }))) return rc;
     if ((rc = timed(c, rank_slot, [&] { return launch_rank_errors(ns, a, c->cs); }))) return rc;
   }
-  if (ns.lv.p > 0 && (rc = timed(c, slot0 + 3, [&] { return launch_gather(ns, c->cs); }))) return rc;
-  if (ns.lv.p > 0 && (rc = timed(c, slot0 + 4, [&] { return launch_select(ns, c->cs); }))) return rc;
+  if (ns.lv.pk > 0 && (rc = timed(c, slot0 + 3, [&] { return launch_gather(ns, c->cs); }))) return rc;
+  if (ns.lv.pk > 0 && (rc = timed(c, slot0 + 4, [&] { return launch_select(ns, c->cs); }))) return rc;
   if (before_tally) HIPCHK(c, hipStreamWaitEvent(c->cs, before_tally, 0));
   if ((rc = timed(c, slot0 + 5, [&] { return launch_tally(ns, c->cs); }))) return rc;
   if (ns.lv.p > 0 && (rc = timed(c, slot0 + 6, [&] { return launch_compact(ns, a, c->cs); }))) return rc;

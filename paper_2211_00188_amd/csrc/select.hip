@@ -1111,8 +1111,8 @@ __global__ __launch_bounds__(kBlock) void k_tally(NodeSet ns) {
   }
   const uint32_t* __restrict__ counts = ns.grp_count + (size_t)node * groups;
   const bool skip = ns.skip[node] != 0;         // the node keeps h: no candidates were extracted
-  // (a level set without any Top-K level has no candidate arrays at all: nothing to read either)
-  for (int g = lo + w; g < ((skip || p == 0) ? lo : hi); g += 4) {
+  // (a level set with no Top-K size below d has no thresholds, and no candidates were looked for)
+  for (int g = lo + w; g < ((skip || ns.lv.pk == 0) ? lo : hi); g += 4) {
     const GroupHead cur = group_load<false>(cval, coff, counts, g, ns.d, lane);
     uint32_t cg[P], ce[P];
 #pragma unroll
@@ -1177,6 +1177,8 @@ __global__ __launch_bounds__(kBlock) void k_tally(NodeSet ns) {
     for (int j = 0; j < lv.m; ++j) {
       if (skip) {
         err[j] = __longlong_as_double(0x7FF8000000000000ll);    // not evaluated: the cascade stopped before
+      } else if (lv.kind[j] == kTopK && lv.ref[j] >= lv.pk) {   // the identity
+        err[j] = 0.0;
       } else if (lv.kind[j] == kTopK) {
         const int s = lv.ref[j];
         const double tv = (double)__uint_as_float(ns.prefix[node * p + s]);
@@ -1213,6 +1215,10 @@ __global__ __launch_bounds__(kBlock) void k_tally(NodeSet ns) {
     // (the message tables, this scale among them, are read by the previous step's aggregation: the first
     // kernel that may write them is this one, which in overlap mode is ordered behind that aggregation)
     if (lv.nq > 0) ns.qscale[node] = 0.f;       // the apply kernel sets it if the chosen level is a quantiser
+    if (slot >= lv.pk) {                        // the identity: no threshold, every coordinate is sent
+      ns.grp_off[(size_t)node * (groups + 1) + groups] = lv.K[slot];
+      slot = -1;
+    }
     if (slot >= 0) {
       ns.sel_T[node] = ns.prefix[node * p + slot];
       ns.sel_r[node] = ns.rank[node * p + slot];
@@ -1254,12 +1260,26 @@ __global__ __launch_bounds__(kBlock) void k_compact(NodeSet ns, PassArgs a) {
   const int node = blockIdx.y, tid = threadIdx.x, w = tid >> 6, lane = tid & 63;
   const int slot = ns.sel_slot[node];
   if (slot < 0) return;
-  const uint32_t T = ns.sel_T[node], r = ns.sel_r[node];
   const int groups = ns.groups, p = ns.lv.p;
   const int GB = (groups + ns.G2 - 1) / ns.G2;
   const int lo = blockIdx.x * GB, hi = min(groups, lo + GB);
   if (lo >= hi) return;
   const size_t row = (size_t)node * (size_t)ns.d;
+  if (slot >= ns.lv.pk) {          // the identity: the message is the difference itself
+    for (int g = lo + w; g < hi; g += 4) {
+      if (lane == 0) ns.grp_off[(size_t)node * (groups + 1) + g] = (uint32_t)g * kWaveTile;
+      const int64_t end = min(ns.d, ((int64_t)g + 1) * kWaveTile);
+#pragma unroll 4
+      for (int64_t l = (int64_t)g * kWaveTile + lane; l < end; l += 64) {
+        const float hv = a.h[row + l], v = a.diff ? a.x[row + l] : a.x[row + l] - hv;
+        ns.msg_idx[(size_t)node * ns.Kcap + l] = (int32_t)l;
+        ns.msg_val[(size_t)node * ns.Kcap + l] = v;
+        a.h[row + l] = a.assign ? v : hv + v;
+      }
+    }
+    return;
+  }
+  const uint32_t T = ns.sel_T[node], r = ns.sel_r[node];
   const uint32_t* __restrict__ cval = ns.cand_val + row;
   const uint16_t* __restrict__ coff = ns.cand_off + row;
   float* __restrict__ h = a.h + row;
@@ -1479,7 +1499,7 @@ hipError_t launch_select(const NodeSet& ns, hipStream_t st) {
 
 hipError_t launch_tally(const NodeSet& ns, hipStream_t st) {
   (void)hipGetLastError();   // drop a stale error left by earlier runtime calls of this thread
-  const dim3 grid(ns.G2, ns.nn), block(kBlock);
+  const dim3 grid(ns.lv.pk > 0 ? ns.G2 : 1, ns.nn), block(kBlock);      // (no thresholds: nothing to count)
   if (ns.lv.p <= 4) hipLaunchKernelGGL((k_tally<4>), grid, block, 0, st, ns);
   else if (ns.lv.p <= 8) hipLaunchKernelGGL((k_tally<8>), grid, block, 0, st, ns);
   else hipLaunchKernelGGL((k_tally<16>), grid, block, 0, st, ns);

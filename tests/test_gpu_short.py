@@ -69,3 +69,38 @@ def test_short_vectors_against_the_general_kernels(n, d, what, mode):
                 np.testing.assert_allclose(x, y, rtol=1e-12, err_msg=str(f))
             else:
                 np.testing.assert_array_equal(x, y, err_msg=str(f))
+
+
+@pytest.mark.parametrize("d", [1, 2047, 2048, 2049, 8192, 20483, 70001])
+@pytest.mark.parametrize("mode", ["gradients", "diff", "compressed"])
+@pytest.mark.parametrize("levels", ["identity", "quantiser", "rank"])
+def test_level_sets_whose_only_sparsifier_is_the_identity(d, mode, levels):
+    """No size below d: the general kernels look for no candidates, and the identity's message is the difference itself.  Against the
+    oracle's definition: every coordinate sent, in order."""
+    E = _eng()
+    n = 3
+    if levels == "rank":
+        d = max(256, d // 16 * 16)
+    rng = np.random.default_rng(d)
+    v = [make_vectors(rng, n, d, "normal") for _ in range(3)]
+    first = {"identity": [], "quantiser": [(E.QUANT, 4)], "rank": [(E.RANK, (1, 16))]}[levels]
+    kw = dict(grad_mode=E.DIFF_EXTERNAL, init_mode=E.INIT_ZERO) if mode == "diff" else dict(grad_mode=E.GRAD_EXTERNAL, grad0=_cuda(v[2]))
+    if mode == "compressed":
+        kw.update(init_mode=E.INIT_COMPRESSED)
+    eng = E.AdaCGD(n=n, d=d, gamma=0.05, worker_levels=first + [(E.TOPK, d)], zeta_worker=0.0, master_levels=[(E.TOPK, d)], zeta_master=0.0,
+                   x0=_cuda(np.zeros(d, np.float32)), seed=3, flags=E.FLAG_TWO_PASS | E.FLAG_ANY_LEVEL_ORDER, **kw)
+    h = np.zeros((n, d), np.float32) if mode == "diff" else v[2].copy()
+    gt = (h.astype(np.float64).sum(axis=0) / n).astype(np.float32)
+    for t in range(2):
+        eng.step(_cuda(v[t]), *([_cuda(np.ones(n))] if mode == "diff" else []))
+        msg = v[t] if mode == "diff" else v[t] - h
+        h = h + msg
+        gt = (gt.astype(np.float64) + msg.astype(np.float64).sum(axis=0) / n).astype(np.float32)
+        assert eng.state(E.F_LEVEL).tolist() == [len(first) + 1] * n
+        np.testing.assert_array_equal(eng.state(E.F_GI), h)
+        np.testing.assert_array_equal(eng.state(E.F_GTILDE), gt)
+        for idx, val in eng.messages():
+            np.testing.assert_array_equal(idx, np.arange(d))
+        np.testing.assert_array_equal(eng.state(E.F_MSG_VAL).reshape(n, d), msg)
+        assert (eng.state(E.F_ERR)[:, -1] == 0).all()
+    eng.close()
