@@ -168,6 +168,8 @@ void carve_nodeset(Carver& c, NodeSet& ns) {
   ns.alone = chunks ? c.take<uint32_t>(nn) : nullptr;
   ns.level_hist = c.take<unsigned long long>(m + 2);
   ns.repairs = ns.level_hist ? ns.level_hist + m + 1 : nullptr;   // (null when only measuring)
+  ns.level = c.take<int32_t>(nn);
+  ns.msg_count = c.take<uint32_t>(nn);
   // everything up to here must start at zero
   ns.prefix = c.take<uint32_t>(nn * p);
   ns.rank = c.take<uint32_t>(nn * p);
@@ -199,12 +201,10 @@ void carve_nodeset(Carver& c, NodeSet& ns) {
   ns.cand_val = p && multi ? c.take<uint32_t>(nn * (size_t)ns.d) : nullptr;
   ns.cand_off = p && multi ? c.take<uint16_t>(nn * (size_t)ns.d) : nullptr;
   ns.glist = p && multi ? c.take<uint32_t>(nn * (size_t)ns.d) : nullptr;
-  ns.level = c.take<int32_t>(nn);
-  ns.sel_slot = c.take<int32_t>(nn);
+  ns.sel_slot = c.take<int32_t>(nn);       // (these two start at -1, filled up to sel_T)
   ns.sel_q = c.take<int32_t>(nn);
   ns.sel_T = c.take<uint32_t>(nn);
   ns.sel_r = c.take<uint32_t>(nn);
-  ns.msg_count = c.take<uint32_t>(nn);
   ns.msg_idx = c.take<int32_t>(nn * (size_t)ns.Kcap);
   ns.msg_val = c.take<float>(nn * (size_t)ns.Kcap);
   ns.qcodes = nq ? c.take<int16_t>(nn * (size_t)ns.d) : nullptr;
@@ -1054,12 +1054,15 @@ static int init_impl(const adacgd_config* cfg, adacgd_ctx** out, int static_dev)
   }
   if (L.col_done) INITCHK(launch_fill_u32(L.col_done, 0u, col_counters(c->ld, c->n, c->d), c->st));
   if (logistic_mode(cfg->grad_mode)) {
-    std::vector<int32_t> rn((size_t)c->ld.rows);
-    for (int64_t i = 0; i < c->n; ++i)
-      for (int64_t l = cfg->shard_offsets[i]; l < cfg->shard_offsets[i + 1]; ++l) rn[(size_t)l] = (int32_t)i;
+    std::vector<int32_t> rn;
     INITCHK(hipMemcpyAsync(L.offsets, cfg->shard_offsets, (size_t)(c->n + 1) * sizeof(int64_t), hipMemcpyHostToDevice,
                            c->st));
-    INITCHK(hipMemcpyAsync(L.row_node, rn.data(), rn.size() * sizeof(int32_t), hipMemcpyHostToDevice, c->st));
+    if (c->ld.col_parts == 0) {       // (k_grad does not ask for a row's shard)
+      rn.resize((size_t)c->ld.rows);
+      for (int64_t i = 0; i < c->n; ++i)
+        for (int64_t l = cfg->shard_offsets[i]; l < cfg->shard_offsets[i + 1]; ++l) rn[(size_t)l] = (int32_t)i;
+      INITCHK(hipMemcpyAsync(L.row_node, rn.data(), rn.size() * sizeof(int32_t), hipMemcpyHostToDevice, c->st));
+    }
     std::vector<int4> chunks;
     if (L.chunks) {
       int slot = 0;
@@ -1113,18 +1116,15 @@ static int init_impl(const adacgd_config* cfg, adacgd_ctx** out, int static_dev)
   }
   INITCHK(launch_mean(c->gi, c->gt[0], c->gt[1], c->g_own, (int)c->n, c->d, c->st));
   if (c->x_next) INITCHK(launch_xupdate(c->x_next, c->x, c->g(), c->gamma, c->d, c->st));
-  // message tables start empty
-  INITCHK(launch_fill_u32((uint32_t*)c->W.sel_slot, 0xFFFFFFFFu, (size_t)c->n, c->st));
-  INITCHK(launch_fill_u32((uint32_t*)c->W.sel_q, 0xFFFFFFFFu, (size_t)c->n, c->st));
-  if (c->W.lv.nr) INITCHK(launch_fill_u32((uint32_t*)c->W.sel_rk, 0xFFFFFFFFu, (size_t)c->n, c->st));
-  if (c->has_master && c->M.lv.nr) INITCHK(launch_fill_u32((uint32_t*)c->M.sel_rk, 0xFFFFFFFFu, 1, c->st));
-  INITCHK(launch_fill_u32(c->W.msg_count, 0u, (size_t)c->n, c->st));
-  INITCHK(launch_fill_u32((uint32_t*)c->W.level, 0u, (size_t)c->n, c->st));
-  if (c->has_master) {
-    INITCHK(launch_fill_u32((uint32_t*)c->M.sel_slot, 0xFFFFFFFFu, 1, c->st));
-    INITCHK(launch_fill_u32((uint32_t*)c->M.sel_q, 0xFFFFFFFFu, 1, c->st));
-    INITCHK(launch_fill_u32(c->M.msg_count, 0u, 1, c->st));
-    INITCHK(launch_fill_u32((uint32_t*)c->M.level, 0u, 1, c->st));
+  // message tables start empty (levels and counts are among what started at zero, unless the compressed start has been there)
+  for (NodeSet* ns : {&c->W, &c->M}) {
+    if (ns == &c->M && !c->has_master) continue;
+    INITCHK(launch_fill_u32((uint32_t*)ns->sel_slot, 0xFFFFFFFFu, (size_t)((uint32_t*)ns->sel_T - (uint32_t*)ns->sel_slot), c->st));
+    if (ns->lv.nr) INITCHK(launch_fill_u32((uint32_t*)ns->sel_rk, 0xFFFFFFFFu, (size_t)ns->nn, c->st));
+  }
+  if (cfg->init_mode == ADACGD_INIT_COMPRESSED) {
+    INITCHK(launch_fill_u32(c->W.msg_count, 0u, (size_t)c->n, c->st));
+    INITCHK(launch_fill_u32((uint32_t*)c->W.level, 0u, (size_t)c->n, c->st));
   }
   if ((cfg->flags & ADACGD_FLAG_OVERLAP) && !logistic_mode(cfg->grad_mode)) {
     INITCHK(hipStreamSynchronize(c->st));     // the worker stream starts from a finished initial state
