@@ -277,8 +277,10 @@ enum adacgd_field {
 /* Kernel slots of ADACGD_F_KERNEL_MS.  W = worker side, M = master side.  Long vectors with
  * Top-K levels only run sample + scan (the scan also extracts the candidates); the filter slot
  * then holds the second scan that repairs a failed estimate (idle otherwise).  Other vectors run
- * scan + filter as two passes.  Without Rank-K levels, vectors of at most 65536 coordinates -- and
- * longer ones, up to 2^20, if there are few nodes -- are handled by one kernel that does the whole
+ * scan + filter as two passes; where no Top-K size is below d, gather and select have nothing to do and
+ * are left out, and so is the filter unless there are quantisers.  Without Rank-K levels, vectors of at
+ * most 65536 coordinates -- and longer ones, up to 2^20, if there are few nodes -- are handled by one
+ * kernel that does the whole
  * compression step of all nodes, timed in the scan slot; up to 512 coordinates, with at most 64
  * workers and Top-K levels only, that launch also aggregates (the aggregate slot stays empty) and
  * compresses on the master's side if its levels are of that kind too (the M slots stay empty), and
