@@ -212,8 +212,9 @@ struct LogisticData {
   // One-launch gradient of dense features (k_grad): every shard's rows in chunks of chunk_rows, its columns in
   // col_parts parts of part_cols, one block each; col_parts = 0: the two-kernel form.
   int col_parts;
-  int part_cols;           // ... in turns of 256 columns (col_parts > 1)
-  int stream;              // the features do not fit the memory-side cache: they are read past it
+  int part_cols;           // ... side by side, or
+  int turns;               // ... in turns of 256 columns (col_parts > 1)
+  int stream;              // the features are read past the memory-side cache (only with turns)
   int row_groups;          // groups of wavefronts of a block that hold different rows
   int chunk_rows;          // a multiple of the rows a block holds at a time
   int groups;              // row chunks of all shards together

@@ -511,8 +511,15 @@ void shape_logistic(const adacgd_config* cfg, LogisticData& ld) {
     // spread over the device.
     const int64_t n = cfg->n, d = cfg->d;
     int64_t parts = (d + kGradCols - 1) / kGradCols;
-    ld.part_cols = (int)(parts == 1 ? d : ((d + 255) / 256 + parts - 1) / parts * 256);
-    ld.stream = ld.rows * d * 4 > kCacheBytes;
+    // Turns of 256 columns (grad_columns) where rows begin on lines of 128 bytes: elsewhere two blocks share the line at every
+    // end of a turn, and 20 shards of 2000 MiB in all took 840 instead of 800 us with rows of 5003, 445 instead of 426 with
+    // 4097 (with 4096: 360 and 380, read past the cache).  Nor is anything gained there by reading past the cache.  That is done
+    // from 5/4 of the cache on: 4096 columns 59.7 us at 262 MiB, read past it 65.8; 67.5 and 68.6 at 300, 75.2 and 74.9 at
+    // 320, 93.2 and 87.8 at 400.
+    ld.turns = parts > 1 && d % 32 == 0;
+    ld.part_cols = (int)(parts == 1 ? d : ld.turns ? ((d + 255) / 256 + parts - 1) / parts * 256 : ((d + parts - 1) / parts + 15) / 16 * 16);
+    if (!ld.turns) parts = (d + ld.part_cols - 1) / ld.part_cols;
+    ld.stream = ld.turns && ld.rows * d * 4 > kCacheBytes + kCacheBytes / 4;
     const int waves = grad_col_waves(ld.part_cols);
     ld.row_groups = 1;
     while (ld.row_groups * waves < 8 && ld.row_groups * kGradRows < mx) ld.row_groups *= 2;

@@ -24,10 +24,19 @@ namespace adacgd {
 // 2000 x 8 x 300 took 24 us (18 with two kernels), now 10 us.
 // ---------------------------------------------------------------------------
 
-// First of a lane's four columns.  The P blocks of a row take turns of 256 columns, so that what a block reads is spread over the
-// memory's channels as the whole row is: with 2048 columns side by side some blocks had their rows after 4 us and waited 15 us
-// for others' (1000 x 32 rows x 65536 columns: 1.95 ms, in turns 1.87).
-__device__ __forceinline__ uint32_t grad_column(uint32_t wave, uint32_t P, uint32_t part, uint32_t lane) { return ((wave * P + part) * 64 + lane) * 4; }
+// Where a lane's four columns lie.  TURNS: the P blocks of a row take turns of 256 columns, so that what a block reads is spread
+// over the memory's channels as the whole row is: with 2048 columns side by side some blocks had their rows after 4 us and waited
+// 15 us for others' (1000 x 32 rows x 65536 columns: 1.95 ms, in turns 1.87).  Otherwise side by side.
+struct GradColumns {
+  uint32_t first, len;       // the row from `first` on, as far as the block may go
+  uint32_t off;              // byte offset of the lane's columns in it
+};
+template <bool TURNS>
+__device__ __forceinline__ GradColumns grad_columns(const LogisticData& ld, uint32_t d, uint32_t P, uint32_t part, uint32_t wave, uint32_t lane) {
+  if (TURNS) return {0, d, ((wave * P + part) * 64 + lane) * 16};
+  const uint32_t first = part * (uint32_t)ld.part_cols;
+  return {first, min((uint32_t)ld.part_cols, d - first), (wave * 64 + lane) * 16};
+}
 
 __device__ __forceinline__ double grad_weight(double yl, double z, double N) { return -yl / (1.0 + exp(yl * z)) / N; }
 
@@ -48,16 +57,17 @@ __device__ __forceinline__ void add_groups(double (&acc)[4], double* share, int 
   }
 }
 
-// What a block does with its column sums (four a lane from column `col` on, the part's quad `at`, in group 0 of its RG groups of
+// What a block does with its column sums (four a lane, the part's quad `at`, in group 0 of its RG groups of
 // wavefronts): the gradient, or with several chunks a shard -- each leaves its sums, and the last to arrive adds them:
 // kGradFold RG of them, every group its share, the groups' sums in their order; of more chunks, the last of every kGradFold RG
 // leaves their sum, and the last of those adds these (one block adding all of them took 140 us for 1 x 4000 rows x 2048
 // columns, 250 chunks; 20 chunks added by the first group alone, 16 and then the two sums, 1.5 us more than by four groups).
 template <int RG>
 __device__ __forceinline__ void finish(const LogisticData& ld, float* __restrict__ grads, int64_t d, int node, int rc, int nchunks, int slot0,
-                                       uint32_t P, uint32_t part, uint32_t at, uint32_t col, int rg, const float (&xq)[4], double (&acc)[4],
+                                       uint32_t P, uint32_t part, const GradColumns& gc, uint32_t at, int rg, const float (&xq)[4], double (&acc)[4],
                                        double* share, int* flag) {
   constexpr int FOLD = kGradFold * RG;
+  const uint32_t l0 = gc.off / 4;
   if (nchunks > 1) {
     // (a part's columns 0, 4, 8, ... lie side by side, so that a wavefront's accesses do)
     const uint32_t quads = ((uint32_t)ld.part_cols + 3) / 4;
@@ -67,7 +77,7 @@ __device__ __forceinline__ void finish(const LogisticData& ld, float* __restrict
       if (rg == 0) {
 #pragma unroll
         for (int c = 0; c < 4; ++c)
-          if (col + c < (uint32_t)d) st_coherent(&sums[(size_t)slot * slot_len + c * quads], acc[c]);
+          if (l0 + c < gc.len) st_coherent(&sums[(size_t)slot * slot_len + c * quads], acc[c]);
       }
     };
     auto add = [&](int slot, int count, int stride) {
@@ -79,7 +89,7 @@ __device__ __forceinline__ void finish(const LogisticData& ld, float* __restrict
         for (int u = 0; u < 8; ++u)
 #pragma unroll
           for (int c = 0; c < 4; ++c)
-            v[u][c] = r0 + u * RG < count && col + c < (uint32_t)d ? ld_coherent(&sums[(size_t)(slot + (r0 + u * RG) * stride) * slot_len + c * quads]) : 0.0;
+            v[u][c] = r0 + u * RG < count && l0 + c < gc.len ? ld_coherent(&sums[(size_t)(slot + (r0 + u * RG) * stride) * slot_len + c * quads]) : 0.0;
 #pragma unroll
         for (int u = 0; u < 8; ++u)
 #pragma unroll
@@ -102,11 +112,12 @@ __device__ __forceinline__ void finish(const LogisticData& ld, float* __restrict
   float g[4];
 #pragma unroll
   for (int c = 0; c < 4; ++c) g[c] = (float)(acc[c] + reg_grad(ld.lambda, (double)xq[c]));
-  buf_store4(make_buf(grads + (size_t)node * (size_t)d, 4 * (uint32_t)d), 4 * col, 0, g);
+  buf_store4(make_buf(grads + (size_t)node * (size_t)d + gc.first, 4 * gc.len), gc.off, 0, g);
 }
 
 // A whole row chunk by one block of eight wavefronts: the weights of its rows, left where the products were (nobody polls
 // them any more), then one part of the columns after the other.
+template <bool TURNS>
 __device__ __forceinline__ void grad_alone(const LogisticData& ld, const float* __restrict__ x, float* __restrict__ grads, int64_t d, int node, int rc,
                                         int nchunks, int slot0, uint32_t r_begin, int rows, double N, double* slots, int* flag) {
   const uint32_t P = (uint32_t)ld.col_parts, lane = threadIdx.x & 63;
@@ -120,24 +131,24 @@ __device__ __forceinline__ void grad_alone(const LogisticData& ld, const float* 
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   __syncthreads();
   for (uint32_t p = 0; p < P; ++p) {
-    const uint32_t col = grad_column(threadIdx.x >> 6, P, p, lane);
+    const GradColumns gc = grad_columns<TURNS>(ld, (uint32_t)d, P, p, threadIdx.x >> 6, lane);
     float xq[4];
-    buf_load4(make_buf(x, 4 * (uint32_t)d), 4 * col, 0, xq);
+    buf_load4(make_buf(x + gc.first, 4 * gc.len), gc.off, 0, xq);
     double acc[4] = {0.0, 0.0, 0.0, 0.0};
     for (int row = 0; row < rows; ++row) {
       float a[4];
-      buf_load4(make_buf(ld.A + (size_t)(r_begin + (uint32_t)row) * (size_t)d, 4 * (uint32_t)d), 4 * col, 0, a);
+      buf_load4(make_buf(ld.A + (size_t)(r_begin + (uint32_t)row) * (size_t)d + gc.first, 4 * gc.len), gc.off, 0, a);
       const double s = ld_coherent(&slots[(size_t)row * P]);
 #pragma unroll
       for (int c = 0; c < 4; ++c) acc[c] = fma(s, (double)a[c], acc[c]);
     }
-    finish<1>(ld, grads, d, node, rc, nchunks, slot0, P, p, threadIdx.x, col, 0, xq, acc, nullptr, flag);
+    finish<1>(ld, grads, d, node, rc, nchunks, slot0, P, p, gc, threadIdx.x, 0, xq, acc, nullptr, flag);
   }
 }
 
-// PARTED: rows are longer than a block's columns (CW = 8, RG = 1).  STREAM: the features do not fit the memory-side cache and are read
-// past it (1000 x 32 rows x 65536 columns: 1.87 ms, so 1.82).
-template <int CW, int RG, bool PARTED, bool STREAM = false>
+// PARTED: rows are longer than a block's columns (CW = 8, RG = 1).  STREAM: the features are read past the memory-side cache
+// (1000 x 32 rows x 65536 columns: 1.87 ms, so 1.82).
+template <int CW, int RG, bool PARTED, bool TURNS = false, bool STREAM = false>
 __global__ __launch_bounds__(64 * CW * RG, 4) void k_grad(LogisticData ld, const float* __restrict__ x, float* __restrict__ grads, int64_t d) {
   constexpr int R = kGradRows, NT = 64 * CW * RG;
   __shared__ double red[CW * RG][R], s_m[RG][R];
@@ -179,7 +190,7 @@ __global__ __launch_bounds__(64 * CW * RG, 4) void k_grad(LogisticData ld, const
   const int skip = rc * ld.chunk_rows, rows = max(0, min(count - skip, ld.chunk_rows));
   const uint32_t r_begin = r_first + (uint32_t)skip;
   const double N = (double)count;
-  const uint32_t col = grad_column((uint32_t)cw, P, part, lane), bytes = 4 * (uint32_t)d;
+  const GradColumns gc = grad_columns<TURNS>(ld, (uint32_t)d, P, part, (uint32_t)cw, lane);
   const size_t set = (size_t)ld.rows * P;
   double* __restrict__ slots = PARTED ? ld.meet + ld.parity * set + (size_t)r_begin * P : nullptr;
   if (PARTED) {       // the set the previous launch used, cleared for the next one
@@ -192,18 +203,18 @@ __global__ __launch_bounds__(64 * CW * RG, 4) void k_grad(LogisticData ld, const
   }
   if (tid == 0) s_quit = 0;
   float xq[4];
-  buf_load4(make_buf(x, bytes), 4 * col, 0, xq);
+  buf_load4(make_buf(x + gc.first, 4 * gc.len), gc.off, 0, xq);
   auto label = [&](int row) { return row < rows ? ld.labels[r_begin + (uint32_t)row] : 0.f; };      // (asked for before it is needed)
   auto weight = [&](double yl, double z) { return grad_weight(yl, z, N); };
   double acc[4] = {0.0, 0.0, 0.0, 0.0};
   for (int base = 0; base < rows; base += R * RG) {
     // rows base + r RG + rg of the chunk (rows beyond its end read as zero and get weight zero)
     float a[R][4];
-    const float* __restrict__ ap = ld.A + (size_t)(r_begin + (uint32_t)(base + rg)) * (size_t)d;
+    const float* __restrict__ ap = ld.A + (size_t)(r_begin + (uint32_t)(base + rg)) * (size_t)d + gc.first;
 #pragma unroll
     for (int r = 0; r < R; ++r) {
       const bool live = base + r * RG + rg < rows;
-      buf_load4<STREAM ? kStream : 0>(make_buf(live ? ap + (size_t)(r * RG) * (size_t)d : ld.A, live ? bytes : 0u), 4 * col, 0, a[r]);
+      buf_load4<STREAM ? kStream : 0>(make_buf(live ? ap + (size_t)(r * RG) * (size_t)d : ld.A, live ? 4 * gc.len : 0u), gc.off, 0, a[r]);
     }
     const float yl_row = !PARTED && tid < R * RG ? label(base + tid % R * RG + tid / R) : 0.f;      // (comes with the rows)
     // products with x, eight rows at a time (lane l gets the sum of row l / 8)
@@ -276,7 +287,7 @@ __global__ __launch_bounds__(64 * CW * RG, 4) void k_grad(LogisticData ld, const
     }
     __syncthreads();
     if (PARTED && base == 0 && __builtin_expect(s_quit, 0)) {
-      if (arrive_last_few(&ld.alone[group], P, &s_flag)) grad_alone(ld, x, grads, d, node, rc, nchunks, slot0, r_begin, rows, N, slots, &s_flag);
+      if (arrive_last_few(&ld.alone[group], P, &s_flag)) grad_alone<TURNS>(ld, x, grads, d, node, rc, nchunks, slot0, r_begin, rows, N, slots, &s_flag);
       return;
     }
 #pragma unroll
@@ -288,7 +299,7 @@ __global__ __launch_bounds__(64 * CW * RG, 4) void k_grad(LogisticData ld, const
     }
   }
   add_groups<RG>(acc, s_acc, rg);
-  if (rg == 0 || nchunks > 1) finish<RG>(ld, grads, d, node, rc, nchunks, slot0, P, part, (uint32_t)(cw * 64) + lane, col, rg, xq, acc, s_acc, &s_flag);
+  if (rg == 0 || nchunks > 1) finish<RG>(ld, grads, d, node, rc, nchunks, slot0, P, part, gc, (uint32_t)(cw * 64) + lane, rg, xq, acc, s_acc, &s_flag);
 }
 
 hipError_t launch_grad(const LogisticData& ld, const float* x, float* grads, int64_t d, hipStream_t st) {
@@ -303,7 +314,8 @@ hipError_t launch_grad(const LogisticData& ld, const float* x, float* grads, int
     case 1: return rg == 1 ? go(k_grad<1, 1, false>, 1) : rg == 2 ? go(k_grad<1, 2, false>, 2) : rg == 4 ? go(k_grad<1, 4, false>, 4) : go(k_grad<1, 8, false>, 8);
     case 2: return rg == 1 ? go(k_grad<2, 1, false>, 2) : rg == 2 ? go(k_grad<2, 2, false>, 4) : go(k_grad<2, 4, false>, 8);
     case 4: return rg == 1 ? go(k_grad<4, 1, false>, 4) : go(k_grad<4, 2, false>, 8);
-    default: return ld.col_parts == 1 ? go(k_grad<8, 1, false>, 8) : ld.stream ? go(k_grad<8, 1, true, true>, 8) : go(k_grad<8, 1, true>, 8);
+    default: return ld.col_parts == 1 ? go(k_grad<8, 1, false>, 8)
+                                  : ld.stream ? go(k_grad<8, 1, true, true, true>, 8) : ld.turns ? go(k_grad<8, 1, true, true>, 8) : go(k_grad<8, 1, true>, 8);
   }
 }
 

@@ -233,6 +233,17 @@ def test_workspace_of_the_gradient_grows_with_the_rows_and_not_with_the_longest_
     assert need(cnt) - need(np.ones(n)) <= bound, (need(cnt), need(np.ones(n)), bound)
 
 
+@pytest.mark.parametrize("d,columns", [(2048, 2048), (2049, 2 * 1040), (2080, 2 * 1280), (4100, 3 * 1376), (4096, 4096), (4128, 3 * 1536)])
+def test_columns_of_the_gradients_parts(d, columns):
+    """Partial sums are as long as the parts of a row together.  Parts are whole turns of 256 columns only where rows begin on lines
+    of 128 bytes; elsewhere they lie side by side, whole sixteens."""
+    def need(rows):
+        offsets = np.array([0, rows], np.int64)
+        return E.adacgd_workspace_bytes(_cfg(n=1, d=d, grad_mode=E.GRAD_LOGISTIC, shard_offsets=offsets)[0])
+    grown = need(32) - need(16)        # one chunk of 16 rows, and two, which leave partial sums
+    assert 0 <= grown - 2 * columns * 8 <= 4096, (grown, 2 * columns * 8)
+
+
 def test_wide_buffer_stores_take_no_scalar_offset():
     """A 16-byte buffer store with its offset in a scalar register may write what the next instruction puts into its data
     registers: the compiler takes such a store for safe and leaves no wait states behind it."""

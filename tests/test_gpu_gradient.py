@@ -41,6 +41,14 @@ def test_gradient_where_blocks_do_not_wait_for_each_other(n, d, rows, short):
     check_gradient(n, d, rows, cnt, np.random.default_rng(d * 13 + rows), _eng().FLAG_NO_WAIT)
 
 
+# lengths with rows that begin on lines (multiples of 32: blocks take turns of columns) and without, a few columns in the last turn
+# or part; the last three, of one length each, have more features than are kept in the cache, as many as are, and rows off the lines
+@pytest.mark.parametrize("n,d,rows", [(3, 2080, 40), (3, 2303, 40), (3, 2304, 17), (2, 4064, 33), (2, 4112, 33), (1, 131040, 20), (1, 131056, 20),
+                                      (100, 131072, 7), (80, 131072, 7), (100, 130000, 7)])
+def test_gradient_of_rows_on_and_off_the_lines(n, d, rows):
+    check_gradient(n, d, rows, np.full(n, rows), np.random.default_rng(d * 17 + rows))
+
+
 def check_gradient(n, d, rows, cnt, rng, flags=0):
     E = _eng()
     off = np.concatenate([[0], np.cumsum(cnt)]).astype(np.int64)
