@@ -30,7 +30,9 @@ constexpr uint32_t kPolls = 1u << 15;   // a block waits that many polls (of abo
 constexpr int64_t kCacheBytes = int64_t(256) << 20;      // memory-side cache
 constexpr int kGradCols = 2048;
 constexpr int kGradRows = 16;           // rows a group of wavefronts holds at a time
-constexpr int kGradFold = 16;           // partial sums that one block adds up
+constexpr int kGradFold = 16;           // partial sums that one block adds up,
+constexpr int kGradFoldAll = 32;        // or all of a shard's if that many at most and several groups of wavefronts to share them
+constexpr int kGradFoldShare = 8;       // ... which they do with more than that
 __host__ __device__ constexpr int grad_col_waves(int64_t cols) { return cols <= 256 ? 1 : cols <= 512 ? 2 : cols <= 1024 ? 4 : 8; }
 // Top-K messages of at most kServeWorkers workers of one chunk each are also written out as whole vectors, which the
 // aggregation reads coordinate by coordinate (k_aggregate_short).

@@ -40,12 +40,12 @@ __device__ __forceinline__ GradColumns grad_columns(const LogisticData& ld, uint
 
 __device__ __forceinline__ double grad_weight(double yl, double z, double N) { return -yl / (1.0 + exp(yl * z)) / N; }
 
-// Sums of the RG groups of wavefronts, in group order, in group 0; share: four values of every thread, thread by thread (null if RG = 1).
+// Sums of the RG groups of wavefronts, in group order, in group 0; share: four values of every thread, thread by thread (null if
+// RG = 1), of which nobody reads any more (a barrier lies behind the last call's reads: arrive_last_few).
 template <int RG>
 __device__ __forceinline__ void add_groups(double (&acc)[4], double* share, int rg) {
   if (RG == 1) return;
   const int lanes = (int)blockDim.x / RG, mine = (int)threadIdx.x - rg * lanes;
-  __syncthreads();
 #pragma unroll
   for (int c = 0; c < 4; ++c) share[(rg * 4 + c) * lanes + mine] = acc[c];
   __syncthreads();
@@ -59,14 +59,16 @@ __device__ __forceinline__ void add_groups(double (&acc)[4], double* share, int 
 
 // What a block does with its column sums (four a lane, the part's quad `at`, in group 0 of its RG groups of
 // wavefronts): the gradient, or with several chunks a shard -- each leaves its sums, and the last to arrive adds them:
-// kGradFold RG of them, every group its share, the groups' sums in their order; of more chunks, the last of every kGradFold RG
-// leaves their sum, and the last of those adds these (one block adding all of them took 140 us for 1 x 4000 rows x 2048
-// columns, 250 chunks; 20 chunks added by the first group alone, 16 and then the two sums, 1.5 us more than by four groups).
+// kGradFold of them; of more chunks, the last of every kGradFold leaves their sum, and the last of those adds these (one
+// block adding all of them took 140 us for 1 x 4000 rows x 2048 columns, 250 chunks).  Several groups share the work, the groups'
+// sums added in their order, where that takes rounds of loads off; up to kGradFoldAll chunks are then added at once (20 x 2500
+// rows x 300 columns, 20 chunks: 18.7 us instead of 20.4).  Not more at once, since they arrive at one counter and end up in
+// one block (128 at once: 1 x 20000 rows x 100 columns 16.2 us; 16 and then ten, 13.2, shared 12.7), and fewer are not shared
+// (50 x 700 x 100, six chunks: 12.2 us shared and 11.6 not).
 template <int RG>
 __device__ __forceinline__ void finish(const LogisticData& ld, float* __restrict__ grads, int64_t d, int node, int rc, int nchunks, int slot0,
                                        uint32_t P, uint32_t part, const GradColumns& gc, uint32_t at, int rg, const float (&xq)[4], double (&acc)[4],
                                        double* share, int* flag) {
-  constexpr int FOLD = kGradFold * RG;
   const uint32_t l0 = gc.off / 4;
   if (nchunks > 1) {
     // (a part's columns 0, 4, 8, ... lie side by side, so that a wavefront's accesses do)
@@ -83,29 +85,32 @@ __device__ __forceinline__ void finish(const LogisticData& ld, float* __restrict
     auto add = [&](int slot, int count, int stride) {
 #pragma unroll
       for (int c = 0; c < 4; ++c) acc[c] = 0.0;
-      for (int r0 = rg; r0 < count; r0 += 8 * RG) {        // eight loads of a column in flight
+      const bool shared = RG > 1 && count > kGradFoldShare;
+      const int step = shared ? RG : 1;
+      for (int r0 = shared ? rg : rg == 0 ? 0 : count; r0 < count; r0 += 8 * step) {        // eight loads of a column in flight
         double v[8][4];
 #pragma unroll
         for (int u = 0; u < 8; ++u)
 #pragma unroll
           for (int c = 0; c < 4; ++c)
-            v[u][c] = r0 + u * RG < count && l0 + c < gc.len ? ld_coherent(&sums[(size_t)(slot + (r0 + u * RG) * stride) * slot_len + c * quads]) : 0.0;
+            v[u][c] = r0 + u * step < count && l0 + c < gc.len ? ld_coherent(&sums[(size_t)(slot + (r0 + u * step) * stride) * slot_len + c * quads]) : 0.0;
 #pragma unroll
         for (int u = 0; u < 8; ++u)
 #pragma unroll
           for (int c = 0; c < 4; ++c) acc[c] += v[u][c];
       }
-      add_groups<RG>(acc, share, rg);
+      if (shared) add_groups<RG>(acc, share, rg);
     };
     leave(slot0 + rc);
-    const int sub = rc - rc % FOLD, members = min(FOLD, nchunks - sub);
+    const int fold = RG > 1 && nchunks <= kGradFoldAll ? nchunks : kGradFold;
+    const int sub = rc - rc % fold, members = min(fold, nchunks - sub);
     if (!arrive_last_few(&ld.col_done[(size_t)(slot0 + sub) * P + part], (uint32_t)members, flag)) return;
     add(slot0 + sub, members, 1);
-    if (nchunks > FOLD) {
+    if (nchunks > fold) {
       leave(slot0 + sub);
-      const int subs = (nchunks + FOLD - 1) / FOLD;
+      const int subs = (nchunks + fold - 1) / fold;
       if (!arrive_last_few(&ld.col_done[(size_t)(ld.part_slots + slot0) * P + part], (uint32_t)subs, flag)) return;
-      add(slot0, subs, FOLD);
+      add(slot0, subs, fold);
     }
   }
   if (rg != 0) return;
@@ -216,7 +221,6 @@ __global__ __launch_bounds__(64 * CW * RG, 4) void k_grad(LogisticData ld, const
       const bool live = base + r * RG + rg < rows;
       buf_load4<STREAM ? kStream : 0>(make_buf(live ? ap + (size_t)(r * RG) * (size_t)d : ld.A, live ? 4 * gc.len : 0u), gc.off, 0, a[r]);
     }
-    const float yl_row = !PARTED && tid < R * RG ? label(base + tid % R * RG + tid / R) : 0.f;      // (comes with the rows)
     // products with x, eight rows at a time (lane l gets the sum of row l / 8)
 #pragma unroll
     for (int r0 = 0; r0 < R; r0 += 8) {
@@ -283,7 +287,7 @@ __global__ __launch_bounds__(64 * CW * RG, 4) void k_grad(LogisticData ld, const
       double z = 0.0;
 #pragma unroll
       for (int j = 0; j < CW; ++j) z += red[g * CW + j][r];
-      s_m[g][r] = row < rows ? weight((double)yl_row, z) : 0.0;
+      s_m[g][r] = row < rows ? weight((double)label(row), z) : 0.0;
     }
     __syncthreads();
     if (PARTED && base == 0 && __builtin_expect(s_quit, 0)) {

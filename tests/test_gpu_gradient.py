@@ -41,6 +41,15 @@ def test_gradient_where_blocks_do_not_wait_for_each_other(n, d, rows, short):
     check_gradient(n, d, rows, cnt, np.random.default_rng(d * 13 + rows), _eng().FLAG_NO_WAIT)
 
 
+# chunk counts around those that one group of wavefronts adds, that several share, and that are added at once: 8, 9, 16, 17, 32, 33 chunks
+# and more than 32 sums of 16, in blocks of eight, four and two groups (128, 64 and 32 rows a chunk) and of one
+@pytest.mark.parametrize("n,d,rows", [(2, d, held * c + more) for d, held in ((100, 128), (300, 64), (1000, 32), (2048, 16))
+                                      for c, more in ((1, 0), (8, 0), (8, 1), (16, 0), (16, 1), (32, 0), (32, 1), (64, 1))]
+                         + [(1, 100, 16384), (1, 100, 16385), (1, 300, 4097), (1, 1024, 1024), (1, 1024, 1025), (1, 1024, 17000), (1, 700, 2000)])
+def test_gradient_around_the_counts_of_partial_sums(n, d, rows):
+    check_gradient(n, d, rows, np.full(n, rows), np.random.default_rng(d * 19 + rows))
+
+
 # lengths with rows that begin on lines (multiples of 32: blocks take turns of columns) and without, a few columns in the last turn
 # or part; the last three, of one length each, have more features than are kept in the cache, as many as are, and rows off the lines
 @pytest.mark.parametrize("n,d,rows", [(3, 2080, 40), (3, 2303, 40), (3, 2304, 17), (2, 4064, 33), (2, 4112, 33), (1, 131040, 20), (1, 131056, 20),
