@@ -202,11 +202,11 @@ struct LogisticData {
   const float* A;
   const float* labels;
   const int64_t* offsets;  // device [n+1]
-  const int32_t* row_node; // device [rows]
+  const int32_t* row_node; // device [rows] shard of each row (null for k_grad, which does not ask for it)
   int64_t rows;
   int64_t max_rows;        // largest shard
   double lambda;
-  double* margins;         // [rows]  s_l = -y_l / (1 + exp(y_l a_l^T x)) / N_i
+  double* margins;         // [rows]  s_l = -y_l / (1 + exp(y_l a_l^T x)) / N_i (null for k_grad)
   double* part;            // [n][row_chunks][d] when row_chunks > 1; k_grad: [part_slots][grad_slot_len]
   uint32_t* col_done;      // [n][column blocks] arrival counters when row_chunks > 1; k_grad: [2][part_slots][col_parts];
                            // zero between launches

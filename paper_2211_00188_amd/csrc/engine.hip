@@ -461,7 +461,7 @@ size_t carve_all(char* base, const adacgd_config* cfg, NodeSet& W, NodeSet& M, L
   if (logistic_mode(cfg->grad_mode)) {
     const size_t rows = cfg->shard_offsets[n];
     L.offsets = c.take<int64_t>(n + 1);
-    L.row_node = c.take<int32_t>(rows);
+    L.row_node = ld.col_parts ? nullptr : c.take<int32_t>(rows);
     L.margins = ld.col_parts ? nullptr : c.take<double>(rows);
     ld.meet = ld.col_parts > 1 ? c.take<double>((grad_meet_words(ld) + 1) / 2) : nullptr;
     ld.begun = ld.meet ? reinterpret_cast<uint32_t*>(ld.meet + 2 * rows * ld.col_parts) : nullptr;
@@ -1064,7 +1064,7 @@ static int init_impl(const adacgd_config* cfg, adacgd_ctx** out, int static_dev)
     std::vector<int32_t> rn;
     INITCHK(hipMemcpyAsync(L.offsets, cfg->shard_offsets, (size_t)(c->n + 1) * sizeof(int64_t), hipMemcpyHostToDevice,
                            c->st));
-    if (c->ld.col_parts == 0) {       // (k_grad does not ask for a row's shard)
+    if (L.row_node) {
       rn.resize((size_t)c->ld.rows);
       for (int64_t i = 0; i < c->n; ++i)
         for (int64_t l = cfg->shard_offsets[i]; l < cfg->shard_offsets[i + 1]; ++l) rn[(size_t)l] = (int32_t)i;

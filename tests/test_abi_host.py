@@ -244,6 +244,13 @@ def test_columns_of_the_gradients_parts(d, columns):
     assert 0 <= grown - 2 * columns * 8 <= 4096, (grown, 2 * columns * 8)
 
 
+def test_rows_that_need_no_tables_take_no_workspace():
+    """Rows of up to 2048 columns in shards of one chunk: the one-launch gradient keeps nothing for a row."""
+    def need(rows):
+        return E.adacgd_workspace_bytes(_cfg(n=1000, d=100, grad_mode=E.GRAD_LOGISTIC, shard_offsets=np.arange(1001, dtype=np.int64) * rows)[0])
+    assert need(16) == need(1)
+
+
 def test_wide_buffer_stores_take_no_scalar_offset():
     """A 16-byte buffer store with its offset in a scalar register may write what the next instruction puts into its data
     registers: the compiler takes such a store for safe and leaves no wait states behind it."""
