@@ -96,7 +96,7 @@ struct NodeSet {
   uint32_t* sel_hist;   // [nn][p][kBins1]        digit counts of long gathered lists; zero between launches
   uint32_t* sel_done;   // [nn][p][kArriveFan+1]  arrival counters of the select kernels
   uint32_t* gcur;       // [nn]                   keys gathered so far; zero between steps
-  uint32_t* glist;      // [nn][d]                keys of the candidates inside the slots' first-digit bins
+  uint32_t* glist;      // [nn][d]                keys of the candidates inside the slots' first-digit bins (null: as cand_val)
   uint32_t* prefix;     // [nn][p]                known high bits of slot threshold T_s (12, 22, 31 bits)
   uint32_t* rank;       // [nn][p]                rank of the K_s-th element inside the prefix
   uint32_t* eqcnt;      // [nn][p]                count of keys equal to T_s
@@ -129,7 +129,8 @@ struct NodeSet {
   uint32_t* blk_out;    // [nn][G2]     message offset of the block's first group, chosen level
   uint32_t* blk_eqb;    // [nn][G2]     ties before the block's first group, chosen level
   uint32_t* grp_off;    // [nn][groups+1] message offset of each group's first entry (last = total)
-  uint32_t* cand_val;   // [nn][d]  value bits of the candidates; group g starts at g * kWaveTile
+  uint32_t* cand_val;   // [nn][d]  value bits of the candidates; group g starts at g * kWaveTile (null: one launch a step, or no
+                        //          Top-K size below d)
   uint16_t* cand_off;   // [nn][d]  their coordinate offsets inside the group, same layout
   int32_t* level;       // [nn]   0 = skip
   int32_t* sel_slot;    // [nn]   slot of the chosen Top-K level, -1 otherwise

@@ -198,9 +198,10 @@ void carve_nodeset(Carver& c, NodeSet& ns) {
   ns.blk_out = c.take<uint32_t>(nn * ns.G2);
   ns.blk_eqb = c.take<uint32_t>(nn * ns.G2);
   ns.grp_off = c.take<uint32_t>(nn * (tiles + 1));
-  ns.cand_val = p && multi ? c.take<uint32_t>(nn * (size_t)ns.d) : nullptr;
-  ns.cand_off = p && multi ? c.take<uint16_t>(nn * (size_t)ns.d) : nullptr;
-  ns.glist = p && multi ? c.take<uint32_t>(nn * (size_t)ns.d) : nullptr;
+  const bool cands = ns.lv.pk > 0 && multi;
+  ns.cand_val = cands ? c.take<uint32_t>(nn * (size_t)ns.d) : nullptr;
+  ns.cand_off = cands ? c.take<uint16_t>(nn * (size_t)ns.d) : nullptr;
+  ns.glist = cands ? c.take<uint32_t>(nn * (size_t)ns.d) : nullptr;
   ns.sel_slot = c.take<int32_t>(nn);       // (these two start at -1, filled up to sel_T)
   ns.sel_q = c.take<int32_t>(nn);
   ns.sel_T = c.take<uint32_t>(nn);

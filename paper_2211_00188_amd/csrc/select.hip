@@ -30,13 +30,14 @@
 //             epilogue: bin and in-bin rank of each Top-K size, candidate cut-off bin, skip mark
 //   filter  : re-forms v, candidates = keys in bins >= cut-off, energy below, realised
 //             error of every quantiser level (Philox dither)
-// Then, both sequences:
+//             (left out where there are neither quantisers nor a Top-K size below d)
+// Then, both sequences, gather and select only with a Top-K size below d:
 //   gather  : keys of the candidates inside some Top-K size's bin -> one list per node
 //   select  : one block per (Top-K size, node) finishes the radix select on that list:
 //             exact threshold key T_s, ties to take r_s, count of keys equal to T_s
 //   tally   : per group counts of keys > T_s and == T_s, energy strictly below T_s
 //             epilogue: err of every level, the cascade, message layout per block
-//   compact : writes the chosen level's message in ascending coordinate and updates h
+//   compact : writes the chosen level's message in ascending coordinate and updates h (the identity's from x and h)
 //   qapply  : dense update and codes for nodes whose chosen level is a quantiser
 // Vectors of up to 65536 coordinates without Rank-K levels take none of this: node.hip does the whole step
 // of a node in one launch.
@@ -322,7 +323,8 @@ __global__ __launch_bounds__(kBlock) void k_scan(NodeSet ns, PassArgs a) {
     // to do for the node (the tally kernel takes the same decision from the same two numbers)
     // (the compressed start applies its one level unconditionally: a zero gradient still selects K zeros, signs kept)
     ns.skip[node] = (!a.assign && s <= trigger_bound(ns.lv, 0, s, dnode)) ? 1u : 0u;
-    ns.bmin[node] = p > 0 ? s_bin[p - 1] : (uint32_t)kBins0;   // largest K reaches lowest
+    // largest K reaches lowest; no candidates at all if the only one is the identity, whose message is the difference itself
+    ns.bmin[node] = ns.lv.pk > 0 ? s_bin[p - 1] : (uint32_t)kBins0;
     if (ns.lv.nq > 0) ns.amax[node] = s_kmax;
   }
 }

@@ -251,6 +251,16 @@ def test_rows_that_need_no_tables_take_no_workspace():
     assert need(16) == need(1)
 
 
+@pytest.mark.parametrize("levels", [[(E.RANK, (1, 64))], [(E.QUANT, 4)]])
+def test_the_identity_alone_needs_no_candidate_lists(levels):
+    """Next to levels of another kind the identity costs its message, 8 bytes a coordinate, and tables of a few bytes a group."""
+    n, d = 16, 1 << 20
+    def need(more):
+        return E.adacgd_workspace_bytes(_cfg(n=n, d=d, worker_levels=levels + more, flags=E.FLAG_TWO_PASS | E.FLAG_ANY_LEVEL_ORDER)[0])
+    grown = need([(E.TOPK, d)]) - need([])
+    assert 8 * n * d <= grown <= 9 * n * d, (grown, 8 * n * d)
+
+
 def test_wide_buffer_stores_take_no_scalar_offset():
     """A 16-byte buffer store with its offset in a scalar register may write what the next instruction puts into its data
     registers: the compiler takes such a store for safe and leaves no wait states behind it."""

@@ -104,3 +104,35 @@ def test_level_sets_whose_only_sparsifier_is_the_identity(d, mode, levels):
         np.testing.assert_array_equal(eng.state(E.F_MSG_VAL).reshape(n, d), msg)
         assert (eng.state(E.F_ERR)[:, -1] == 0).all()
     eng.close()
+
+
+@pytest.mark.parametrize("d", [700, 2049, 20483, 70001])
+@pytest.mark.parametrize("general", [False, True])
+@pytest.mark.parametrize("sizes", [True, False])
+def test_the_identity_next_to_sizes_and_a_quantiser(d, general, sizes):
+    """Level sets with the identity, a quantiser and (or not) sizes below d; every worker's difference is steered by its ||x - y||^2
+    to another level, or to none, at every step."""
+    E = _eng()
+    wl = ([(O.TOPK, max(1, d // 50)), (O.TOPK, d // 4)] if sizes else []) + [(O.QUANT, 8), (O.TOPK, d)]
+    m = len(wl)
+    n = m + 1
+    rng = np.random.default_rng(d + general)
+    # (errors and squared norms lie within [1e-3 d, 10 d])
+    tw = [(10.0 ** (-4 * (m - 1 - j)), 0.0) for j in range(m)]
+    kw = dict(n=n, d=d, gamma=0.05, worker_levels=wl, zeta_worker=0.0, worker_triggers=tw, master_levels=[(O.TOPK, max(1, d // 30)), (O.TOPK, d)],
+              zeta_master=0.0, master_triggers=[(0.0, 0.0), (0.0, 0.5)], seed=11)
+    x0 = rng.standard_normal(d).astype(np.float32)
+    orc = O.AdaCGDOracle(**kw)
+    orc.init(x0, None, O.INIT_ZERO)
+    eng = E.AdaCGD(grad_mode=E.DIFF_EXTERNAL, init_mode=E.INIT_ZERO, x0=_cuda(x0),
+                   flags=E.FLAG_ANY_LEVEL_ORDER | (E.FLAG_TWO_PASS if general else 0), **kw)
+    with until_near_tie(("identity", d, general, sizes)):
+        for t in range(2 * n):
+            want = [(i * (1 + t // n) + t) % n for i in range(n)]        # level of each worker
+            v = make_vectors(rng, n, d, "normal")
+            D = np.array([0.0 if k == m else 10.0 * d * 10.0 ** (4 * (m - 1 - k)) for k in want])
+            res, rm = orc.step(diffs=v, D=D)
+            assert [r.level for r in res] == want
+            eng.step(_cuda(v), _cuda(D))
+            compare_step(eng, orc, res, rm, ("identity", d, general, sizes, t))
+    eng.close()
