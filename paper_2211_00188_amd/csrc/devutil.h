@@ -208,7 +208,7 @@ __device__ __forceinline__ bool arrive_last(uint32_t* counters, uint32_t nblocks
   return *lds_flag != 0;
 }
 
-// The same for a few dozen blocks: one counter is enough.
+// The same for up to 64 blocks: one counter is enough.
 __device__ __forceinline__ bool arrive_last_few(uint32_t* counter, uint32_t nblocks, int* lds_flag) {
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");

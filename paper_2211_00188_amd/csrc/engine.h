@@ -148,8 +148,9 @@ struct NodeSet {
   uint32_t* ticket;     // [2][kCounterStride] next (node, chunk) to be taken by a block; zero at init; null up to kNodeParts blocks
   uint32_t* alone;      // [nn] blocks that have left a node that was given up (NB > 1); zero between launches
   uint32_t polls;       // polls before a node is given up
-  float* dense;         // [nn][d] C(v) of every node that sent a message, for k_aggregate_short and the aggregation inside
-                        //         the workers' launch of short.hip (null: the messages themselves are added)
+  float* dense;         // [nn][d] C(v) of every node that sent a message, for k_aggregate_short (which leaves the others out), and of
+                        //         every node, zeros if it sent none, for the aggregation inside the workers' launch of short.hip
+                        //         (null: the messages themselves are added)
   double* accbuf;       // [d] fp64 sums of the sparse messages (only with quantiser levels)
   // Rank-K levels (allocated only when the level set has any; c = lv.rcols, nr = lv.nr)
   int GR;               // blocks per node of the Rank-K kernels

@@ -439,7 +439,7 @@ size_t carve_all(char* base, const adacgd_config* cfg, NodeSet& W, NodeSet& M, L
   const size_t n = cfg->n, d = cfg->d;
   const size_t w0 = c.off;
   carve_nodeset(c, W);
-  // the arrays that must be zero come first in carve_nodeset: up to and including level_hist
+  // the arrays that must be zero come first in carve_nodeset: up to and including msg_count, the last before prefix
   L.w_zero = base ? (size_t)((char*)W.prefix - (char*)W.hist0) : 0;
   (void)w0;
   if (M.lv.m > 0) {

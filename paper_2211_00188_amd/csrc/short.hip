@@ -10,8 +10,9 @@
 // key, which takes less work a coordinate and more phases a size.)
 // Measured, a whole step with supplied gradients, against k_node for the workers and their aggregation and k_node for the
 // master: 4 workers x 100 coordinates, five sizes, 19.6 and 9.0 us; 20 x 300 28 and 12.5; 64 x 512 40 and 15.3; without
-// aggregation or master here, 200 x 300 38 and 32.5, 2000 x 500 147 and 143.  Not beyond 512 coordinates: 1024 threads a block
-// took 15.8 instead of 13.3 us for 64 x 1024 with one size and no master, 171 instead of 148 for 2000 x 1000.
+// aggregation or master here, 200 x 300 38 and 32.5, 2000 x 500 147 and 143.  Not beyond 512 coordinates, whatever the number of
+// workers: 1024 threads a block took 15.8 instead of 13.3 us for 64 x 1024 with one size and no master, 171 instead of 148 for
+// 2000 x 1000.  (Few workers with a master would have gained there, 1.1 to 1.4 times as fast.)
 #include "devutil.h"
 #include "engine.h"
 
