@@ -62,7 +62,7 @@ __device__ __forceinline__ void add_groups(double (&acc)[4], double* share, int 
 // kGradFold of them; of more chunks, the last of every kGradFold leaves their sum, and the last of those adds these (one
 // block adding all of them took 140 us for 1 x 4000 rows x 2048 columns, 250 chunks).  Several groups share the work, the groups'
 // sums added in their order, where that takes rounds of loads off; up to kGradFoldAll chunks are then added at once (20 x 2500
-// rows x 300 columns, 20 chunks: 18.7 us instead of 20.4).  Not more at once, since they arrive at one counter and end up in
+// rows x 300 columns, 20 chunks: 18.0 us instead of 20.4).  Not more at once, since they arrive at one counter and end up in
 // one block (128 at once: 1 x 20000 rows x 100 columns 16.2 us; 16 and then ten, 13.2, shared 12.7), and fewer are not shared
 // (50 x 700 x 100, six chunks: 12.2 us shared and 11.6 not).
 template <int RG>
@@ -211,6 +211,10 @@ __global__ __launch_bounds__(64 * CW * RG, 4) void k_grad(LogisticData ld, const
   buf_load4(make_buf(x + gc.first, 4 * gc.len), gc.off, 0, xq);
   auto label = [&](int row) { return row < rows ? ld.labels[r_begin + (uint32_t)row] : 0.f; };      // (asked for before it is needed)
   auto weight = [&](double yl, double z) { return grad_weight(yl, z, N); };
+  // The first round's labels come before its rows; later rounds ask when they need them.  Asked for when needed in the first as
+  // well, 20 x 2500 rows x 300 columns took 18.7 us (18.0) and 2000 x 8 x 2048 29.6 (27.7); asked for early in all rounds, 400 x 500 x
+  // 200, four rounds a block, 30.3 (29.2).
+  const float yl_first = !PARTED && tid < R * RG ? label(tid % R * RG + tid / R) : 0.f;
   double acc[4] = {0.0, 0.0, 0.0, 0.0};
   for (int base = 0; base < rows; base += R * RG) {
     // rows base + r RG + rg of the chunk (rows beyond its end read as zero and get weight zero)
@@ -287,7 +291,7 @@ __global__ __launch_bounds__(64 * CW * RG, 4) void k_grad(LogisticData ld, const
       double z = 0.0;
 #pragma unroll
       for (int j = 0; j < CW; ++j) z += red[g * CW + j][r];
-      s_m[g][r] = row < rows ? weight((double)label(row), z) : 0.0;
+      s_m[g][r] = row < rows ? weight((double)(base == 0 ? yl_first : label(row)), z) : 0.0;
     }
     __syncthreads();
     if (PARTED && base == 0 && __builtin_expect(s_quit, 0)) {
