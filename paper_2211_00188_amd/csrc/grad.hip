@@ -19,7 +19,7 @@ namespace adacgd {
 // come forms its sums alone.
 // Bound by the read of the features where that is long; two blocks a compute unit (16 rows x 4 columns a lane are half
 // the registers), so that one reads while the other meets.  Measured against the two kernels that read the features
-// twice: 1000 workers x 32 rows x 65536 columns 1.82 ms a gradient (2.90), 20 x 2500 x 300 17 us (29), 10 x 203 x 5003
+// twice: 1000 workers x 32 rows x 65536 columns 1.82 ms a gradient (2.90), 20 x 2500 x 300 16 us (29), 10 x 203 x 5003
 // 19 us (37), 4 x 64 x 100 4.0 us (7.9).  Blocks have no more groups of wavefronts than a shard has rows for: with eight,
 // 2000 x 8 x 300 took 24 us (18 with two kernels), now 10 us.
 // ---------------------------------------------------------------------------

@@ -42,7 +42,8 @@ def test_gradient_where_blocks_do_not_wait_for_each_other(n, d, rows, short):
 
 
 # chunk counts around those that one group of wavefronts adds, that several share, and that are added at once: 8, 9, 16, 17, 32, 33 chunks
-# and more than 32 sums of 16, in blocks of eight, four and two groups (128, 64 and 32 rows a chunk) and of one
+# and more, whose sixteens are eight, nine and seventeen sums, in blocks of eight, four and two groups (128, 64 and 32 rows a chunk)
+# and of one
 @pytest.mark.parametrize("n,d,rows", [(2, d, held * c + more) for d, held in ((100, 128), (300, 64), (1000, 32), (2048, 16))
                                       for c, more in ((1, 0), (8, 0), (8, 1), (16, 0), (16, 1), (32, 0), (32, 1), (64, 1))]
                          + [(1, 100, 16384), (1, 100, 16385), (1, 300, 4097), (1, 1024, 1024), (1, 1024, 1025), (1, 1024, 17000), (1, 700, 2000)])
